@@ -198,22 +198,11 @@ __device__ __forceinline__ M bitm(int i) {
 
 // Lane moves inside a row of 16 lanes by DPP, which stays in the vector ALU
 // (controls: quad_perm [1,0,3,2] = 0xB1 takes lane ^ 1, [2,3,0,1] = 0x4E
-// lane ^ 2, [3,2,1,0] = 0x1B reverses a quad; row_shr:n = 0x110 + n takes
-// lane - n; row_mirror = 0x140 takes lane 15 - i, row_half_mirror = 0x141
+// lane ^ 2; row_shr:n = 0x110 + n takes lane - n; row_mirror = 0x140 takes lane 15 - i, row_half_mirror = 0x141
 // lane 7 - i within each eight).  Moves across rows use the LDS permute.
 template <int CTRL>
 __device__ __forceinline__ unsigned dpp_mov(unsigned v) {
   return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-}
-// the word of lane ^ m (m is a constant once the callers' loops unroll)
-__device__ __forceinline__ unsigned xor_word(unsigned v, int m) {
-  switch (m) {
-    case 1: return dpp_mov<0xB1>(v);
-    case 2: return dpp_mov<0x4E>(v);
-    case 4: return dpp_mov<0x141>(dpp_mov<0x1B>(v));  // i -> 3 - i in the quad, then 7 - i
-    case 8: return dpp_mov<0x140>(dpp_mov<0x141>(v));  // 7 - i in the eight, then 15 - i
-    default: return (unsigned)__shfl_xor((int)v, m, 64);
-  }
 }
 // the word of lane - n (n = 1, 2, 4, 8; lanes below n of the row receive 0)
 __device__ __forceinline__ unsigned up_word(unsigned v, int n) {
@@ -224,18 +213,30 @@ __device__ __forceinline__ unsigned up_word(unsigned v, int n) {
     default: return dpp_mov<0x118>(v);
   }
 }
-// value of lane ^ m inside groups of w lanes; every lane of the group is
-// active
+// one step of a reduction over a group of w lanes: the value of the lane that
+// the step of width o = 1, 2, 4, 8, 16 combines with this one.  After the
+// steps before it, all lanes of a block of o hold the same value, so any lane
+// of the neighbouring block will do, and one DPP move finds one (within a row
+// of 16 lanes: quad_perm, row_half_mirror, row_mirror).  Every lane of the
+// group is active.
+__device__ __forceinline__ unsigned step_word(unsigned v, int o) {
+  switch (o) {
+    case 1: return dpp_mov<0xB1>(v);
+    case 2: return dpp_mov<0x4E>(v);
+    case 4: return dpp_mov<0x141>(v);
+    case 8: return dpp_mov<0x140>(v);
+    default: return (unsigned)__shfl_xor((int)v, o, 64);
+  }
+}
 template <typename T>
-__device__ __forceinline__ T shfl_xor_w(T v, int m, int w) {
+__device__ __forceinline__ T red_step(T v, int o) {
   static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two words");
-  if (m >= 16) return __shfl_xor(v, m, w);
   if constexpr (sizeof(T) == 4) {
-    return __builtin_bit_cast(T, xor_word(__builtin_bit_cast(unsigned, v), m));
+    return __builtin_bit_cast(T, step_word(__builtin_bit_cast(unsigned, v), o));
   } else {
     const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
     const unsigned long long r =
-        ((unsigned long long)xor_word((unsigned)(u >> 32), m) << 32) | xor_word((unsigned)u, m);
+        ((unsigned long long)step_word((unsigned)(u >> 32), o) << 32) | step_word((unsigned)u, o);
     return __builtin_bit_cast(T, r);
   }
 }
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   __shared__ R pnx[PD], pny[PD], pnz[PD], pnc[PD];
   __shared__ int pid[G * PMAX];
   __shared__ M omask[G * PMAX];
-  __shared__ unsigned short snew[G * PMAX];
+  __shared__ unsigned short snew[G * (PMAX + 1)];
   // free vertex slots below H, as a stack; a cut pushes the slots it removes,
   // so that its top then lists the removed triangles
   __shared__ unsigned char fstk[G * TP];
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   const int lane = threadIdx.x;
   const int g = lane / L, j = lane % L;
   const int gb = g * L;
-  const int vb = g * TP, pb = g * PMAX;
+  const int vb = g * TP, pb = g * PMAX, sb = g * (PMAX + 1);
   // XCD-aware block order (blocks are dealt round-robin over the eight XCDs):
   // launched block b clips logical block (b mod 8) per + b / 8, so each XCD
   // takes a contiguous stretch of grid-sorted cells, whose neighbours its L2
@@ -368,22 +369,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   auto group_any = [&](bool v) -> bool { return gballot(v) != 0u; };
   auto gor = [&](M v) -> M {
 #pragma unroll
-    for (int o = 1; o < L; o <<= 1) v |= shfl_xor_w(v, o, L);
+    for (int o = 1; o < L; o <<= 1) v |= red_step(v, o);
     return v;
   };
   auto gmax = [&](R v) -> R {
 #pragma unroll
-    for (int o = 1; o < L; o <<= 1) v = fmax(v, shfl_xor_w(v, o, L));
-    return v;
-  };
-  auto gmaxi = [&](int v) -> int {
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) v = max(v, shfl_xor_w(v, o, L));
+    for (int o = 1; o < L; o <<= 1) v = fmax(v, red_step(v, o));
     return v;
   };
   auto gsumd = [&](double v) -> double {
 #pragma unroll
-    for (int o = 1; o < L; o <<= 1) v += shfl_xor_w(v, o, L);
+    for (int o = 1; o < L; o <<= 1) v += red_step(v, o);
     return v;
   };
   auto gexcl = [&](int v, int& tot) -> int {
@@ -491,23 +487,25 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   int nfr = 0;  // free slots below H (fstk)
   M alive = M(0x3F);
   R R2 = fmax(lx * lx, hx * hx) + fmax(ly * ly, hy * hy) + fmax(lz * lz, hz * hz);
-  // float path: bounds on the true R^2 from each vertex's forward error bound,
-  // R2lo <= R^2 <= R2hi; a radius test is rechecked only between them
-  float R2hi, R2lo;
-  {
-    const double r = sqrt((double)R2), e = FLT_EPSILON * r;
-    R2hi = (float)((r + e) * (r + e) * (1.0 + 1e-6));
-    R2lo = (float)((r - e) * (r - e) * (1.0 - 1e-6));
-  }
-  // radius predicates of the float path: certain / uncertain (else certainly not)
-  auto rad_certain = [&](R dd2) -> bool {
-    return (double)dd2 * a.dmargin * (1.0 - a.eps) > 4.0 * (double)R2hi;
+  // float path: R2 is the largest |v|^2 of the float vertices.  The true R^2
+  // lies between bounds made from each vertex's forward error bound err,
+  // R2lo <= R^2 <= R2hi, and a radius test is rechecked only between them.
+  // By how vertices are made err <= max(16 eps, FLT_EPSILON) |v|, so both
+  // bounds lie within a relative kap of R2: a distance d^2 of at most rlo is
+  // certainly no certificate, one above rhi certainly is one, and only in
+  // between (rarely) are the bounds worked out.
+  const float verrel = fmaxf(16.0f * (float)a.eps, FLT_EPSILON);
+  const float kap = (3.5f + verrel) * verrel + 2.0f * (float)a.eps + 4e-6f;
+  float R2up = 0.0f, rlo = 0.0f, rhi = 0.0f;
+  auto set_radius = [&](R r2) {
+    R2 = r2;
+    if constexpr (RECHECK) {
+      R2up = r2 * (1.0f + kap);
+      rlo = 4.0f * r2 * (1.0f - kap);
+      rhi = 4.0f * R2up;
+    }
   };
-  auto rad_uncertain = [&](R dd2) -> bool {
-    return !rad_certain(dd2) && (double)dd2 * a.dmargin * (1.0 + a.eps) > 4.0 * (double)R2lo;
-  };
-  bool fprev = false;  // the last plane cut, and its own distance certifies the cell that it left
-  bool fmarg = false;  // ... that test was inside its recheck window
+  set_radius(R2);
   bool in_stream = false;  // the group's cell is in the stream phase (vrad kept)
   // |v| (1 + 1e-5) + 4 verr.  verr bounds each coordinate of the float
   // vertex, so the true ball's centre lies within verr per axis and its radius
@@ -545,20 +543,41 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       }
     }
 #pragma unroll
-    for (int o = 1; o < L; o <<= 1) r2 = fmax(r2, shfl_xor_w(r2, o, L));
+    for (int o = 1; o < L; o <<= 1) r2 = fmax(r2, red_step(r2, o));
     return r2;
   };
   const double kDmargin = a.dmargin;
+  // the float path's radius predicates by the bounds: bit 0 certain, bit 1
+  // uncertain (else certainly not).  Called by whole groups.
+  auto radius_bounds = [&](R dd2) -> int {
+    float hi = 0.0f, lo = 0.0f;
+    for (int t = j; t < H; t += L) {
+      float e;
+      const V3<R> v = vget_err(t, e);
+      const float n2 = (float)(v.x * v.x + v.y * v.y + v.z * v.z), n1 = (float)(fabs(v.x) + fabs(v.y) + fabs(v.z));
+      hi = fmaxf(hi, n2 + e * (2.0f * n1 + e));
+      lo = fmaxf(lo, n2 - 2.0f * e * n1);
+    }
+#pragma unroll
+    for (int o = 1; o < L; o <<= 1) {
+      hi = fmaxf(hi, red_step(hi, o));
+      lo = fmaxf(lo, red_step(lo, o));
+    }
+    hi *= 1.0f + 4.0f * FLT_EPSILON;
+    lo *= 1.0f - 4.0f * FLT_EPSILON;
+    if ((double)dd2 * kDmargin * (1.0 - a.eps) > 4.0 * (double)hi) return 1;
+    return (double)dd2 * kDmargin * (1.0 + a.eps) > 4.0 * (double)lo ? 2 : 0;
+  };
 
   // Bound on the uncertainty window of a plane test of the float clip, for
   // every vertex at once: with |v| <= r, the window eps scale + |n|_1 err of
   // the test has scale <= |n| r + c, |n|_1 <= sqrt(3) |n| and (by how vertices
   // are made) err <= max(16 eps, FLT_EPSILON) r.  A test outside it is certain;
   // one inside it works its own window out.
-  const float wv = (float)a.eps + 1.7321f * fmaxf(16.0f * (float)a.eps, FLT_EPSILON);
+  const float wv = (float)a.eps + 1.7321f * verrel;
   auto window = [&](R d2, R c) -> R {
     if constexpr (RECHECK) {
-      const float nr = __builtin_amdgcn_sqrtf(d2 * R2hi);
+      const float nr = __builtin_amdgcn_sqrtf(d2 * R2up);
       return ((float)a.eps * c + wv * nr) * (1.0f + 1e-4f);
     } else {
       return R(0);
@@ -566,29 +585,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   };
 
   // Tests plane (n, c) of candidate nb against every vertex and, if it cuts,
-  // replaces the removed triangles.  Called by every lane (wave-uniform).
+  // replaces the removed triangles; whether it did.  Called by every lane (wave-uniform).
   // Always inlined: as a call, its captures live in scratch memory.
-  auto apply_plane = [&](bool run, R nx, R ny, R nz, R c, R d2, int nb) __attribute__((always_inline)) {
+  auto apply_plane = [&](bool run, R nx, R ny, R nz, R c, R d2, int nb) __attribute__((always_inline)) -> bool {
     // ---- test the plane against every vertex
-    unsigned out = 0, near = 0;
+    unsigned out = 0;
+    R least = R(3.0e38);  // the smallest margin of this lane's tests
     if (run) {
-      fprev = fmarg = false;
-      const R w = window(d2, c);
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         if (L * s < H) {
           const V3<R> v = vget(j + L * s);
           const R sv = nx * v.x + ny * v.y + nz * v.z - c;
           if (sv > R(0)) out |= 1u << s;
-          if (RECHECK && fabs(sv) <= w) near |= 1u << s;
+          if constexpr (RECHECK) least = fmin(least, fabs(sv));
         }
       }
     }
     if constexpr (RECHECK) {
-      if (__any(near != 0u)) {
+      const bool near = run && least <= window(d2, c);
+      if (__any(near)) {
         bool unresolved = false;
-        for (unsigned left = near; left; left &= left - 1u) {
-          const int s = __ffs(left) - 1, t = j + L * s;
+        for (int s = 0; near && L * s < H; ++s) {
+          const int t = j + L * s;
           const unsigned u = tri[vb + t];
           if (u == kEmpty) continue;
           float ev;
@@ -615,7 +634,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       }
     }
     const bool cut = run && group_any(out != 0u);
-    if (!__any(cut)) return;
+    if (!__any(cut)) return false;
 
     // ---- cut: new plane slot
     int ps = -1;
@@ -678,15 +697,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
         tri[vb + t] = kEmpty;
         vput(t, R(0), R(0), R(0), 0.0f);
       }
+      // edges are listed by lane; what is no edge, and (in an inconsistent
+      // topology) an edge past the PMAX-th, goes to the spare entry PMAX
       const unsigned b0 = gballot(e0), b1 = gballot(e1), b2 = gballot(e2);
-      int o0 = btot + __popc(b0 & below) + __popc(b1 & below) + __popc(b2 & below);
+      const int o0 = btot + __popc(b0 & below) + __popc(b1 & below) + __popc(b2 & below), o1 = o0 + e0, o2 = o1 + e1;
       btot += __popc(b0) + __popc(b1) + __popc(b2);
-      // (an inconsistent topology can list more edges than there are planes)
-      if (e0 && o0 < PMAX) snew[pb + o0] = (unsigned short)(A | (B << 8));
-      o0 += e0;
-      if (e1 && o0 < PMAX) snew[pb + o0] = (unsigned short)(B | (C << 8));
-      o0 += e1;
-      if (e2 && o0 < PMAX) snew[pb + o0] = (unsigned short)(C | (A << 8));
+      snew[sb + (e0 ? min(o0, PMAX) : PMAX)] = (unsigned short)(A | (B << 8));
+      snew[sb + (e1 ? min(o1, PMAX) : PMAX)] = (unsigned short)(B | (C << 8));
+      snew[sb + (e2 ? min(o2, PMAX) : PMAX)] = (unsigned short)(C | (A << 8));
     }
     __syncthreads();
     for (int f = j; f < PMAX; f += L) omask[pb + f] = 0;
@@ -703,7 +721,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
     }
     for (int r = j; doit && r < btot; r += L) {
       const int t = r < avail ? (int)fstk[vb + avail - 1 - r] : H + r - avail;
-      const unsigned e = snew[pb + r];
+      const unsigned e = snew[sb + r];
       const int A = e & 0xFF, B = (e >> 8) & 0xFF;
       V3<R> na, nb_, v;
       R ca, cb;
@@ -733,49 +751,25 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
     __syncthreads();
     // R^2 over all slots (an empty one adds zero)
     R r2 = 0;
-    float em = 0.0f, eml = 0.0f;
     if (doit) {
       H = hnew;
       nfr = max(0, avail - btot);
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         if (L * s < H) {
-          float e;
-          const V3<R> v = vget_err(j + L * s, e);
-          const R n2 = v.x * v.x + v.y * v.y + v.z * v.z;
-          if constexpr (RECHECK) {
-            const float n1 = fabs(v.x) + fabs(v.y) + fabs(v.z);
-            em = fmaxf(em, n2 + e * (2.0f * n1 + e));
-            eml = fmaxf(eml, n2 - 2.0f * e * n1);
-          } else {
-            r2 = fmax(r2, n2);
-          }
+          const V3<R> v = vget(j + L * s);
+          r2 = fmax(r2, v.x * v.x + v.y * v.y + v.z * v.z);
         }
       }
     }
-    if constexpr (RECHECK) {
-#pragma unroll
-      for (int o = 1; o < L; o <<= 1) {
-        em = fmaxf(em, shfl_xor_w(em, o, L));
-        eml = fmaxf(eml, shfl_xor_w(eml, o, L));
-      }
-    } else {
-      r2 = gmax(r2);
-    }
+    r2 = gmax(r2);
     pr_ = gor(pr_);
     pk = gor(pk);
     if (doit) {
       alive = (alive & ~(pr_ & ~pk)) | bitm<M>(ps);
-      if constexpr (RECHECK) {
-        R2hi = em * (1.0f + 4.0f * FLT_EPSILON);
-        R2lo = eml * (1.0f - 4.0f * FLT_EPSILON);
-        fprev = rad_certain(d2);
-        fmarg = rad_uncertain(d2);
-      } else {
-        R2 = r2;
-        fprev = (R)(d2 * (R)kDmargin) > R(4) * R2;
-      }
+      set_radius(r2);
     }
+    return doit;
   };
 
   // ---- list phase.  The list is taken in batches of L planes, one per lane.
@@ -796,6 +790,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
     int mb = -L;     // list index of the batch's first plane
     int cur = L;     // first lane of the batch still to look at (L: none)
     unsigned pendb = 0, padb = 0;  // lanes whose plane may cut / lies past the list's end
+    bool again = false;  // the plane of lane cur has just cut
     int id_c = -1, id_n = !fin && j < a.k ? klist[j] : -1, id_n2 = !fin && j + L < a.k ? klist[j + L] : -1;
     Rec4 q_n = rec[id_n >= 0 ? id_n : sid];
     R cx_ = 0, cy_ = 0, cz_ = 0, cd2 = 0;  // this lane's plane of the batch
@@ -807,8 +802,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
         if (cur < L) {
           const bool on = id_c >= 0;
           if constexpr (RECHECK) {
-            certb = gballot(on && rad_certain(cd2));
-            uncb = gballot(on && rad_uncertain(cd2));
+            certb = gballot(on && cd2 > rhi);
+            uncb = 0u;
+            if (gballot(on && cd2 > rlo && cd2 <= rhi) & (~0u << cur)) {
+              const int p = radius_bounds(cd2);
+              certb = gballot(on && p == 1);
+              uncb = gballot(on && p == 2);
+              // a plane that has cut is looked at again for the certificate
+              // alone, and for a recheck only at the end of the list
+              if (again && mb + cur < a.k - 1) uncb &= ~(1u << cur);
+            }
           } else {
             certb = gballot(on && (R)(cd2 * (R)kDmargin) > R(4) * R2);
           }
@@ -817,6 +820,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
         }
         mb += L;
         cur = 0;
+        again = false;
         if (mb >= a.k) {
           fin = true;
           run = false;
@@ -834,9 +838,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
         cd2 = dist2_nc(cx_, cy_, cz_);
         const R c = R(0.5) * cd2;
         R far = -c;
-        for (int t = 0; t < H; ++t) {
-          const V3<R> v = vget(t);
-          far = fmax(far, cx_ * v.x + cy_ * v.y + cz_ * v.z);
+        for (int t = 0; t < H; t += 4) {  // (slots from H to the next multiple of 4 are empty: zeros)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const V3<R> v = vget(t + i);
+            far = fmax(far, cx_ * v.x + cy_ * v.y + cz_ * v.z);
+          }
         }
         R w;
         if constexpr (RECHECK) w = window(cd2, c);
@@ -879,33 +886,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       }
       const R nx = shfl_t(cx_, gb + i), ny = shfl_t(cy_, gb + i), nz = shfl_t(cz_, gb + i);
       const R d2 = dist2_nc(nx, ny, nz);
-      if (run) cur = i + 1;
-      run = run && ((pendb >> i) & 1u);
-      apply_plane(run, nx, ny, nz, R(0.5) * d2, d2, nb);
-      if (run && st == ST_RUN && fprev) {  // the cell that plane m left lies within half its distance
-        st = VOTESS_CELL_CERTIFIED;
-        kneed = m + 1;
-      }
-      if (run) fmarg = fmarg && m == a.k - 1;  // (only the end of the list looks at it)
+      const bool ap = run && ((pendb >> i) & 1u);
+      const bool did = apply_plane(ap, nx, ny, nz, R(0.5) * d2, d2, nb);
+      // on past plane m; if it cut, its own distance may already certify the
+      // cell that it left (with a list of m + 1)
+      again = ap && did;
+      if (run) cur = again ? i : i + 1;
+      pendb &= ~(run ? 1u << i : 0u);
     }
   }
   // ---- end of the list: certified if the list holds all others
-  if (RECHECK) {  // a marginal final radius test is redone in double
-    const bool need = st == ST_RUN && fmarg;
-    if (__any(need)) {
-      const double r64 = radius64(need);
-      if (need) {
-        const Rec4 q = rec[klist[a.k - 1]];
-        const V3<double> n64 = {(double)q.x - p64x, (double)q.y - p64y, (double)q.z - p64z};
-        const double d64 = dot(n64, n64);
-        fprev = d64 * kDmargin > 4.0 * r64;
-        if (fabs(d64 - 4.0 * r64) <= 1e-12 * d64) st = VOTESS_CELL_UNRESOLVED;
-        ++nrecheck;
-      }
-    }
-  }
   if (st == ST_RUN) {
-    if (fprev || a.k >= a.n - 1) {
+    if (a.k >= a.n - 1) {
       st = VOTESS_CELL_CERTIFIED;
       kneed = a.k;
     } else {
@@ -986,9 +978,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       }
 #pragma unroll
       for (int o = 1; o < L; o <<= 1) {
-        mn0 = fmin(mn0, shfl_xor_w(mn0, o, L)); mx0 = fmax(mx0, shfl_xor_w(mx0, o, L));
-        mn1 = fmin(mn1, shfl_xor_w(mn1, o, L)); mx1 = fmax(mx1, shfl_xor_w(mx1, o, L));
-        mn2 = fmin(mn2, shfl_xor_w(mn2, o, L)); mx2 = fmax(mx2, shfl_xor_w(mx2, o, L));
+        mn0 = fmin(mn0, red_step(mn0, o)); mx0 = fmax(mx0, red_step(mx0, o));
+        mn1 = fmin(mn1, red_step(mn1, o)); mx1 = fmax(mx1, red_step(mx1, o));
+        mn2 = fmin(mn2, red_step(mn2, o)); mx2 = fmax(mx2, red_step(mx2, o));
       }
       if (mn0 > mx0) {  // every ball inside the list's: the seed's own cell closes the scan
         mn0 = mx0 = mn1 = mx1 = mn2 = mx2 = 0.0;
@@ -1052,9 +1044,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       }
 #pragma unroll
       for (int o = 1; o < L; o <<= 1) {
-        a0 = fmin(a0, shfl_xor_w(a0, o, L)); b0 = fmax(b0, shfl_xor_w(b0, o, L));
-        a1 = fmin(a1, shfl_xor_w(a1, o, L)); b1 = fmax(b1, shfl_xor_w(b1, o, L));
-        a2 = fmin(a2, shfl_xor_w(a2, o, L)); b2 = fmax(b2, shfl_xor_w(b2, o, L));
+        a0 = fmin(a0, red_step(a0, o)); b0 = fmax(b0, red_step(b0, o));
+        a1 = fmin(a1, red_step(a1, o)); b1 = fmax(b1, red_step(b1, o));
+        a2 = fmin(a2, red_step(a2, o)); b2 = fmax(b2, red_step(b2, o));
       }
       bl0 = a0; bl1 = a1; bl2 = a2; bh0 = b0; bh1 = b1; bh2 = b2;
     };
@@ -1352,7 +1344,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
             const Rec4 q = rec[jj];
             const R d2c = dist2_nc((R)q.x - px, (R)q.y - py, (R)q.z - pz);
             const bool beyond_list = d2c > dk2 || (d2c == dk2 && jj > ik);
-            pass = beyond_list && d2c * skip_scale <= R(4) * (RECHECK ? (R)R2hi : R2);
+            pass = beyond_list && d2c * skip_scale <= R(4) * (RECHECK ? (R)R2up : R2);
             if (pass) {
               const R ex = (R)q.x - px, ey = (R)q.y - py, ez = (R)q.z - pz;
               const R sup = fmax(ex * bl0, ex * bh0) + fmax(ey * bl1, ey * bh1) + fmax(ez * bl2, ez * bh2);
@@ -1404,8 +1396,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       int bl = j;
 #pragma unroll
       for (int o = 1; o < L; o <<= 1) {
-        const R ob = shfl_xor_w(best, o, L);
-        const int ol = shfl_xor_w(bl, o, L);
+        const R ob = red_step(best, o);
+        const int ol = red_step(bl, o);
         if (ob < best || (ob == best && ol < bl)) { best = ob; bl = ol; }
       }
       const int nb2 = __shfl(myj, gb + bl, 64);
@@ -1419,7 +1411,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
         d2 = dist2_nc(nx, ny, nz);
         c = R(0.5) * d2;
         // the radius may have shrunk since the batch was filtered
-        if (d2 * skip_scale > R(4) * (RECHECK ? (R)R2hi : R2)) run2 = false;
+        if (d2 * skip_scale > R(4) * (RECHECK ? (R)R2up : R2)) run2 = false;
       }
       const M alive_prev = alive;
       apply_plane(run2, nx, ny, nz, c, d2, nb2);
@@ -1511,12 +1503,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   // from them, so its outputs are recomputed from vertices solved in double.
   bool refine = false;
   if (RECHECK) {
-    R2 = 0;  // (only its bounds are kept up by the cuts)
-    for (int t = j; t < H; t += L) {
-      const V3<R> v = vget(t);
-      R2 = fmax(R2, v.x * v.x + v.y * v.y + v.z * v.z);
-    }
-    R2 = gmax(R2);
     refine = cert && (double)R2 * sqrt((double)R2) > 16.0 * vol;
     if (__any(refine)) {
       const double v2 = cell_volume(refine, true);
@@ -1653,7 +1639,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   if (RECHECK) {
     int rc = nrecheck;
 #pragma unroll
-    for (int o = 1; o < L; o <<= 1) rc += shfl_xor_w(rc, o, L);
+    for (int o = 1; o < L; o <<= 1) rc += red_step(rc, o);
     nrecheck = rc;
   }
   if (have && j == 0) {
@@ -1670,7 +1656,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       a.centroid[(size_t)row * 3 + 2] = ok ? cmz : 0.0;
     }
     if (a.kneeded) a.kneeded[row] = kneed;
-    if (a.r2out) a.r2out[row] = fin == VOTESS_CELL_CERTIFIED ? (RECHECK ? (double)R2hi : (double)R2) : 0.0;
+    if (a.r2out) a.r2out[row] = fin == VOTESS_CELL_CERTIFIED ? (RECHECK ? (double)R2up : (double)R2) : 0.0;
     if (a.vcount) a.vcount[row] = fin == VOTESS_CELL_CERTIFIED ? vtot : 0;
     if (a.counters) {
       if (nrecheck) atomicAdd(&a.counters[0], (unsigned long long)nrecheck);
