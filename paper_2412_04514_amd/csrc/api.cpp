@@ -319,6 +319,7 @@ votess_status votess_clip_cells(votess_ctx* ctx, const void* sorted, votess_dtyp
   a.area = area;
   a.centroid = centroid;
   a.counters = nullptr;
+  a.own_rows = !(cells && opts->out_by_id);
   a.stream = opts->stream;
   if (opts->stream) {
     if (!opts->grid || !opts->cell_start) return fail(VOTESS_EINVAL, "clip: stream needs grid and cell_start");

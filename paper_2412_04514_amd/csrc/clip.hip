@@ -7,6 +7,10 @@
 // MI355X design
 //  * A group of L lanes owns one cell; a 64-lane wave (= one workgroup) holds
 //    64/L cells.  Lane j of a group handles vertex slots t = j, j+L, ...
+//  * Two launches: the list kernel (8 lanes per cell) clips every cell by its
+//    list; cells that the list does not certify go on, with the polyhedron it
+//    left, in the stream kernel (16 lanes per cell).  Vector instructions bind
+//    the first (VALU busy 75-95%), loads and enumeration the second.
 //  * The polyhedron is kept in dual form in LDS: a list of clipping planes
 //    (box walls + bisectors, at most PMAX alive at once, slots recycled) and a
 //    list of triangles, one per vertex, each naming its three planes in
@@ -37,6 +41,7 @@
 #include "internal.h"
 #include "device_common.h"
 
+#include <algorithm>
 #include <cfloat>
 
 namespace votess {
@@ -70,6 +75,10 @@ struct ClipArgs {
   double* centroid;  // [rows, 3] (nullable)
   double* r2out;     // [rows] (nullable): R^2 of the certified cell (an upper bound on the float path)
   unsigned long long* counters;
+  // passing cells on from the list kernel to a second launch (see k_clip):
+  int rest;  // 1: only the cells that the list kernel left
+  int mark;  // statuses of cells that the list kernel leaves, as a bit mask
+  int save;  // 1 (list kernel): uncertified cells leave their state in nbr
   // stream phase (cells the list did not certify keep clipping by grid rings)
   int stream;
   const int* cell_start;
@@ -268,12 +277,26 @@ __device__ __forceinline__ void plane64_of(int id, const Rec4* rec, double px, d
   }
 }
 
-// The fast kernels (TMAX = 64) are held to 3 waves per SIMD: the compiler
-// would otherwise give the stream variants ~225 VGPRs (2 waves), and with
-// the third wave hiding load latency they run ~20% faster despite ~90 bytes
-// per lane of spills.
+// State of a cell between the list kernel and the stream kernel, in the
+// cell's own neighbour row: the plane ids by slot (32 words; n and c follow
+// from the id), the alive mask, the number of triangles, and the triangles as
+// three 5-bit plane slots in 16 bits, in the order (a, b, last applied), from
+// which the stream kernel solves the same vertices again, bit for bit.
+constexpr uint8_t kLeft = 0x80;  // in a status: the list kernel left the cell to the second launch
+constexpr int kListLanes = 8, kListVert = 48;  // lanes per cell and vertex slots of the list kernel
+constexpr int kStateAlive = 32, kStateCount = 33, kStateTri = 34, kStateWords = kStateTri + kListVert / 2;
+
+// blocks that a launch over nc cells needs, G cells each (with `rest`: 64 / G
+// for each 64 cells)
+__host__ __device__ __forceinline__ int clip_blocks(int nc, int G, int rest) {
+  return rest ? (nc + 63) / 64 * (64 / G) : (nc + G - 1) / G;
+}
+
+// Clips 64 / L cells, one per group of L lanes: cell t_idx of the launch (no
+// cell when !have), from its box or, when `resume`, from the state that the
+// list kernel left.
 template <typename P, typename R, int L, int TMAX, int PMAX, bool RECHECK, bool STREAM>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ? 3 : 1))) void k_clip(ClipArgs a) {
+__device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, bool have, bool resume) {
   using Rec4 = typename Rec<P>::type;
   using M = typename std::conditional<(PMAX <= 32), unsigned, unsigned long long>::type;
   constexpr int G = 64 / L;
@@ -303,16 +326,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   // free vertex slots below H, as a stack; a cut pushes the slots it removes,
   // so that its top then lists the removed triangles
   __shared__ unsigned char fstk[G * TP];
-  // stream phase of the float clip: radius of each vertex's ball through the
-  // seed, widened past the vertex's error bound and the rounding of the tests
-  // that use it (the double clip recomputes it where needed: measured faster)
-  constexpr bool kVrad = STREAM && RECHECK;
-  constexpr int VRD = kVrad ? G * TP : 1;
-  __shared__ float vrad[VRD];
-  // stream phase: vertex slots whose ball can reach the current grid row /
-  // dense cell (see below)
-  constexpr int RL = STREAM ? G * TMAX : 1;
-  __shared__ unsigned char relR[RL], relD[RL];
+  // stream phase: the vertices in reach and their balls, and those of them
+  // whose ball meets the dense cell being scanned (see below)
+  constexpr int kReach = TMAX <= 64 ? 48 : TMAX;
+  constexpr int RVN = STREAM ? G * kReach : 1;
+  __shared__ float4 reachv[RVN];
+  __shared__ unsigned char relD[RVN];
   // stream phase: geometry of the dense cell being scanned (cell corner,
   // sub-grid origin and sub-cell widths), per group
   constexpr int DG = STREAM ? G * 9 : 1;
@@ -321,19 +340,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   // dense cell is entered, so it need not occupy registers)
   constexpr int FWG = STREAM ? G * 6 : 1;
   __shared__ double fwbox[FWG];
-  // stream phase: point ranges of up to L sub-rows of the dense cell being
-  // scanned (offsets into the cell), per group
+  // stream phase: listed parts of the ring, and point ranges of up to L
+  // sub-rows of the dense cell being scanned (offsets into the cell), per group
   constexpr int SRL = STREAM ? G * L : 1;
-  __shared__ int2 srl[SRL];
+  __shared__ int2 rowlist[SRL], srl[SRL];
   // stream phase: the group's enumeration state (grid ring, x-run, dense
   // sub-block, flower box in cells).  Every value is the same for all lanes
   // of a group; held here rather than in registers, which the rest of the
   // kernel needs.
   struct Enum {
     int fb0, fb1, fb2, fb3, fb4, fb5;
-    int rr, zz, yy, part, zhi, ylo, yhi;
-    int rx, rx1, rrow;
-    int dm, dm0, dm1, dbase, dsx0, dsx1, dsy0, dsy1, dsz0, dsz1, dsto;
+    int rr, pq, np, zlo, ylo, nyr, rln, rlp;
+    int rx, rx1, rrow, yy, zz;
+    int dm, dm0, dm1, dm2, dbase, dsx0, dsx1, dsy0, dsy1, dsz0, dsz1, dsto;
     int dq1, dq2, kyn, kzn, dq, dqn, srn, srp;
   };
   __shared__ Enum senum[STREAM ? G : 1];
@@ -343,15 +362,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   const int g = lane / L, j = lane % L;
   const int gb = g * L;
   const int vb = g * TP, pb = g * PMAX, sb = g * (PMAX + 1);
-  // XCD-aware block order (blocks are dealt round-robin over the eight XCDs):
-  // launched block b clips logical block (b mod 8) per + b / 8, so each XCD
-  // takes a contiguous stretch of grid-sorted cells, whose neighbours its L2
-  // then holds
-  const int nblk = (a.nc + G - 1) / G, per = (nblk + 7) / 8;
-  const int lblk = (int)(blockIdx.x % 8u) * per + (int)(blockIdx.x / 8u);
-  if (lblk >= nblk) return;  // the whole (one-wave) block
-  const long long t_idx = (long long)lblk * G + g;
-  const bool have = t_idx < a.nc;
   const int sid = have ? (a.cells ? a.cells[t_idx] : (int)t_idx) : 0;
   const int row = a.out_by_id ? sid : (int)t_idx;
   const Rec4 pr = rec[sid];
@@ -475,13 +485,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
     vput(v, X0, Y0, Z0,
          RECHECK ? FLT_EPSILON * (float)fmax(fabs((double)X0), fmax(fabs((double)Y0), fabs((double)Z0))) : 0.0f);
   }
-  for (int f = j; f < 6; f += L) {
-    const int ax = f >> 1;
-    const bool hi = f & 1;
+  // box wall w (x-, x+, y-, y+, z-, z+) into plane slot f
+  auto wall = [&](int f, int w) {
+    const int ax = w >> 1;
+    const bool hi = w & 1;
     const R sgn = hi ? R(1) : R(-1);
     pput(f, ax == 0 ? sgn : R(0), ax == 1 ? sgn : R(0), ax == 2 ? sgn : R(0),
-         ax == 0 ? (hi ? hx : -lx) : (ax == 1 ? (hi ? hy : -ly) : (hi ? hz : -lz)), -(f + 1));
-  }
+         ax == 0 ? (hi ? hx : -lx) : (ax == 1 ? (hi ? hy : -ly) : (hi ? hz : -lz)), -(w + 1));
+  };
+  for (int f = j; f < 6; f += L) wall(f, f);
   int st = have ? ST_RUN : VOTESS_CELL_CERTIFIED;
   int H = 8;   // slots in use lie below H
   int nfr = 0;  // free slots below H (fstk)
@@ -506,7 +518,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
     }
   };
   set_radius(R2);
-  bool in_stream = false;  // the group's cell is in the stream phase (vrad kept)
   // |v| (1 + 1e-5) + 4 verr.  verr bounds each coordinate of the float
   // vertex, so the true ball's centre lies within verr per axis and its radius
   // within sqrt(3) verr: 4 verr > (1 + sqrt(3)) verr covers both; the relative
@@ -517,14 +528,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       return sqrtf(X * X + Y * Y + Z * Z) * (1.0f + 1e-5f) + 4.0f * e;
     } else {
       return sqrt(X * X + Y * Y + Z * Z) * (1.0 + 1e-5);
-    }
-  };
-  // the ball radius of vertex slot t (at X, Y, Z)
-  auto vball = [&](int t, R X, R Y, R Z) -> R {
-    if constexpr (kVrad) {
-      return vrad[vb + t];
-    } else {
-      return ball_rad(X, Y, Z, 0.0f);
     }
   };
   int kneed = 0;
@@ -547,6 +550,76 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
     return r2;
   };
   const double kDmargin = a.dmargin;
+  // Vertex of planes A, B and the later one (n, c) in slot C.  A float vertex
+  // comes with its error bound, and from double when that is too large.
+  auto vertex = [&](int A, int B, int C, R nx, R ny, R nz, R c, float& ev, bool& redone) -> V3<R> {
+    V3<R> na, nb_, v;
+    R ca, cb;
+    pget(A, na, ca);
+    pget(B, nb_, cb);
+    ev = 0.0f;
+    redone = false;
+    if constexpr (RECHECK) {
+      v = solve3_err(na, ca, nb_, cb, {nx, ny, nz}, c, ev);
+      const float vm = fmaxf(fabsf(v.x), fmaxf(fabsf(v.y), fabsf(v.z)));
+      if (!(ev <= 16.0 * a.eps * vm)) {
+        // ill-conditioned float vertex: solve it in double from the exact
+        // planes and keep the rounded value (bound: one ulp)
+        const V3<double> w = vertex64((unsigned)A | ((unsigned)B << 8) | ((unsigned)C << 16));
+        v = {(float)w.x, (float)w.y, (float)w.z};
+        ev = FLT_EPSILON * (float)fmax(fabs(w.x), fmax(fabs(w.y), fabs(w.z)));
+        redone = true;
+      }
+    } else {
+      v = solve3<R>(na, ca, nb_, cb, {nx, ny, nz}, c);
+    }
+    return v;
+  };
+  if constexpr (STREAM) {
+    if (resume) {
+      const int* w = a.nbr + (size_t)row * a.max_nbr;
+      H = w[kStateCount];
+      alive = (M)(unsigned)w[kStateAlive];
+      for (int f = j; f < 32; f += L) {
+        const int id = w[f];
+        if (!((alive >> f) & 1)) continue;
+        if (id >= 0) {
+          const Rec4 q = rec[id];
+          const R nx = (R)q.x - px, ny = (R)q.y - py, nz = (R)q.z - pz;
+          pput(f, nx, ny, nz, R(0.5) * dist2_nc(nx, ny, nz), id);
+        } else {
+          wall(f, -id - 1);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      const unsigned short* tr = (const unsigned short*)(w + kStateTri);
+      R r2 = 0;
+      for (int t = j; t < (H + L - 1) / L * L; t += L) {
+        if (t < H) {
+          const unsigned x = tr[t];
+          const int A = x & 31, B = (x >> 5) & 31, C = (x >> 10) & 31;
+          V3<R> n, v;
+          R c;
+          float e;
+          bool redone;
+          pget(C, n, c);
+          v = vertex(A, B, C, n.x, n.y, n.z, c, e, redone);
+          if (pid[pb + A] < 0 && pid[pb + B] < 0 && pid[pb + C] < 0) {
+            e = FLT_EPSILON * (float)fmax(fabs((double)v.x), fmax(fabs((double)v.y), fabs((double)v.z)));  // a box corner
+          }
+          vput(t, v.x, v.y, v.z, e);
+          tri[vb + t] = (unsigned)A | ((unsigned)B << 8) | ((unsigned)C << 16);
+          r2 = fmax(r2, v.x * v.x + v.y * v.y + v.z * v.z);
+        } else if (t < TMAX) {
+          tri[vb + t] = kEmpty;
+          vput(t, R(0), R(0), R(0), 0.0f);
+        }
+      }
+      set_radius(gmax(r2));
+      st = VOTESS_CELL_RADIUS;
+    }
+    __syncthreads();
+  }
   // the float path's radius predicates by the bounds: bit 0 certain, bit 1
   // uncertain (else certainly not).  Called by whole groups.
   auto radius_bounds = [&](R dd2) -> int {
@@ -723,29 +796,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       const int t = r < avail ? (int)fstk[vb + avail - 1 - r] : H + r - avail;
       const unsigned e = snew[sb + r];
       const int A = e & 0xFF, B = (e >> 8) & 0xFF;
-      V3<R> na, nb_, v;
-      R ca, cb;
-      pget(A, na, ca);
-      pget(B, nb_, cb);
-      float ev = 0.0f;
-      if constexpr (RECHECK) {
-        v = solve3_err(na, ca, nb_, cb, {nx, ny, nz}, c, ev);
-        const float vm = fmaxf(fabsf(v.x), fmaxf(fabsf(v.y), fabsf(v.z)));
-        if (!(ev <= 16.0 * a.eps * vm)) {
-          // ill-conditioned float vertex: solve it in double from the exact
-          // planes and keep the rounded value (bound: one ulp)
-          const V3<double> w = vertex64((unsigned)A | ((unsigned)B << 8) | ((unsigned)ps << 16));
-          v = {(float)w.x, (float)w.y, (float)w.z};
-          ev = FLT_EPSILON * (float)fmax(fabs(w.x), fmax(fabs(w.y), fabs(w.z)));
-          ++nrecheck;
-        }
-      } else {
-        v = solve3<R>(na, ca, nb_, cb, {nx, ny, nz}, c);
-      }
+      float ev;
+      bool redone;
+      const V3<R> v = vertex(A, B, ps, nx, ny, nz, c, ev, redone);
+      if (redone) ++nrecheck;
       vput(t, v.x, v.y, v.z, ev);
-      if constexpr (kVrad) {
-        if (in_stream) vrad[vb + t] = ball_rad(v.x, v.y, v.z, ev);
-      }
       tri[vb + t] = (unsigned)A | ((unsigned)B << 8) | ((unsigned)ps << 16);
     }
     __syncthreads();
@@ -786,7 +841,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   // float, with batches 20.2 ms; 3M clustered points in double 145 and 131 ms.)
   const int* klist = a.knn + (size_t)(have ? (a.knn_by_id ? (long long)sid : t_idx) : 0) * a.kstride;
   {
-    bool fin = !have || a.k == 0;
+    bool fin = !have || resume || a.k == 0;
     int mb = -L;     // list index of the batch's first plane
     int cur = L;     // first lane of the batch still to look at (L: none)
     unsigned pendb = 0, padb = 0;  // lanes whose plane may cut / lies past the list's end
@@ -904,7 +959,30 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       st = VOTESS_CELL_RADIUS;
     }
   }
-
+  if constexpr (!STREAM && TMAX == kListVert) {
+    if (a.save) {  // the stream kernel goes on from here
+      const bool sv = have && st == VOTESS_CELL_RADIUS;
+      int* w = a.nbr + (size_t)row * a.max_nbr;
+      unsigned short* tr = (unsigned short*)(w + kStateTri);
+      if (sv)
+        for (int f = j; f < 32; f += L) w[f] = pid[pb + f];
+      int cnt = 0;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const unsigned u = tri[vb + j + L * s];
+        const bool on = sv && u != kEmpty;
+        const unsigned gbits = gballot(on);
+        if (on)
+          tr[cnt + __popc(gbits & below)] =
+              (unsigned short)((u & 31) | (((u >> 8) & 31) << 5) | (((u >> 16) & 31) << 10));
+        cnt += __popc(gbits);
+      }
+      if (sv && j == 0) {
+        w[kStateAlive] = (int)(unsigned)alive;
+        w[kStateCount] = cnt;
+      }
+    }
+  }
 
   // ---- stream phase: a cell its list did not certify keeps clipping by grid
   // rings around its seed, restricted to the bounding box of its "flower" (the
@@ -921,17 +999,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
     const int ik0 = (have && st == VOTESS_CELL_RADIUS && !nolist) ? klist[a.k - 1] : -1;
     const bool strm = have && st == VOTESS_CELL_RADIUS && (nolist || ik0 >= 0);  // a full list that did not certify
     if (strm) st = ST_RUN;
-    if constexpr (kVrad) {
-      // ball radii of the current vertices (kept up to date from here on)
-      in_stream = strm;
-      for (int t = j; t < H; t += L)
-        if (strm && tri[vb + t] != kEmpty) {
-          float e;
-          const V3<R> v = vget_err(t, e);
-          vrad[vb + t] = ball_rad(v.x, v.y, v.z, e);
-        }
-      __syncthreads();
-    }
     if (strm && j == 0 && a.counters) atomicAdd(&a.counters[5], 1ull);
     const GridDev& Gd = a.grid;
     const int cx = axis_cell(p64x, Gd.lo0, Gd.ih0, Gd.g0);
@@ -945,36 +1012,85 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       const Rec4 q = rec[ik];
       dk2 = dist2_nc((R)q.x - px, (R)q.y - py, (R)q.z - pz);
     }
-    // A box (seed-relative bounds, already widened by gmarg) that lies inside
-    // the list's ball holds list members only: every point in it is closer
-    // than the list's last one even after the rounding of d^2.
-    const double dk2in = (double)dk2 * (1.0 - 1e-6);
-    auto in_list_ball = [&](double ax, double bx, double ay, double by, double az, double bz) -> bool {
-      const double f = fmax(ax * ax, bx * bx) + fmax(ay * ay, by * by) + fmax(az * az, bz * bz);
-      return f < dk2in;
-    };
     // A vertex whose widened ball reaches less than the list's ball from the
     // seed (twice its radius below that ball's) can only hold list members:
-    // the flower box and the per-box vertex lists leave it out.
+    // the flower box and the reach list leave it out.
+    const double dk2in = (double)dk2 * (1.0 - 1e-6);
     const R rlim = dk2in > 0.0 ? (R)(0.5 * sqrt(dk2in) * (1.0 - 1e-6)) : R(-1);
-    // flower box in grid cells, from the current vertices whose ball leaves
-    // the list's ball (group reduction)
+    // Boxes of candidates are tested in float, relative to the seed, their
+    // bounds widened by gmarg and rounded outward.
+    struct Box {
+      float x0, x1, y0, y1, z0, z1;
+    };
+    auto round_out = [](double x0, double x1, double y0, double y1, double z0, double z1) -> Box {
+      auto next = [](float f, int up) -> float {  // the next float below (up = -1) or above (+1) f
+        const int b = __float_as_int(f);
+        return f == 0.0f ? up * FLT_MIN : __int_as_float(b + (b < 0 ? -up : up));
+      };
+      auto lo = [&](double v) -> float { const float f = (float)v; return (double)f > v ? next(f, -1) : f; };
+      auto hi = [&](double v) -> float { const float f = (float)v; return (double)f < v ? next(f, 1) : f; };
+      return {lo(x0), hi(x1), lo(y0), hi(y1), lo(z0), hi(z1)};
+    };
+    // A box that lies inside the list's ball holds list members only: every
+    // point in it is closer than the list's last one even after the rounding
+    // of d^2.
+    auto in_list_ball = [&](double x0, double x1, double y0, double y1, double z0, double z1) -> bool {
+      return fmax(x0 * x0, x1 * x1) + fmax(y0 * y0, y1 * y1) + fmax(z0 * z0, z1 * z1) < dk2in;
+    };
+    // The reach list: the vertices whose ball leaves the list's ball, as
+    // (position, ball radius).  A point cuts the cell iff it lies in the ball
+    // of some vertex v through the seed (centre v, radius |v|), so a box that
+    // meets none of these balls holds no cutting point, and a candidate is
+    // tested against these vertices alone.  Rebuilt after a cut; should it not
+    // fit, every test passes (reach_all), which costs time only.
+    float4* rv = reachv + (STREAM ? g * kReach : 0);
+    int nrv = 0;
+    bool reach_ok = false, reach_all = false;
+    auto reach = [&]() {
+      int n = 0;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        if (L * s >= H) continue;
+        const int t = j + L * s;
+        float e;
+        const V3<R> v = vget_err(t, e);
+        const R r = ball_rad(v.x, v.y, v.z, e);
+        const bool on = tri[vb + t] != kEmpty && r >= rlim;
+        const unsigned gbits = gballot(on);
+        const int w = n + __popc(gbits & below);
+        // (double positions and radii are rounded to float: 4e-6 covers that)
+        if (on && w < kReach)
+          rv[w] = make_float4((float)v.x, (float)v.y, (float)v.z, RECHECK ? (float)r : (float)r * (1.0f + 4e-6f));
+        n += __popc(gbits);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      reach_all = n > kReach;
+      nrv = min(n, kReach);
+      reach_ok = true;
+    };
+    auto meets = [](const Box& b, const float4& v) -> bool {
+      const float gx = fmaxf(0.0f, fmaxf(b.x0 - v.x, v.x - b.x1)), gy = fmaxf(0.0f, fmaxf(b.y0 - v.y, v.y - b.y1)),
+                  gz = fmaxf(0.0f, fmaxf(b.z0 - v.z, v.z - b.z1));
+      return gx * gx + gy * gy + gz * gz <= v.w * v.w;
+    };
+    // The flower box (of the union of those balls), in coordinates and in grid
+    // cells.  Candidates are enumerated inside it, ring by ring of grid cells.
     Enum& E_ = senum[STREAM ? g : 0];
     int &fb0 = E_.fb0, &fb1 = E_.fb1, &fb2 = E_.fb2, &fb3 = E_.fb3, &fb4 = E_.fb4, &fb5 = E_.fb5;
-    fb0 = 0; fb1 = -1; fb2 = 0; fb3 = -1; fb4 = 0; fb5 = -1;
-    double* fwb = fwbox + (STREAM ? g * 6 : 0);  // the same box in coordinates
+    double* fwb = fwbox + (STREAM ? g * 6 : 0);
+    bool flower_ok = false;
     auto flower_box = [&]() {
       double mn0 = 1e300, mn1 = 1e300, mn2 = 1e300, mx0 = -1e300, mx1 = -1e300, mx2 = -1e300;
       for (int t = j; t < H; t += L) {
         if (tri[vb + t] == kEmpty) continue;
-        const V3<R> v = vget(t);
-        const R rv = vball(t, v.x, v.y, v.z);
-        if (rv < rlim) continue;
-        const double X = v.x, Y = v.y, Z = v.z;
-        const double rad = rv;
-        mn0 = fmin(mn0, X - rad); mx0 = fmax(mx0, X + rad);
-        mn1 = fmin(mn1, Y - rad); mx1 = fmax(mx1, Y + rad);
-        mn2 = fmin(mn2, Z - rad); mx2 = fmax(mx2, Z + rad);
+        float e;
+        const V3<R> v = vget_err(t, e);
+        const R rad = ball_rad(v.x, v.y, v.z, e);
+        if (rad < rlim) continue;
+        const double X = v.x, Y = v.y, Z = v.z, r = rad;
+        mn0 = fmin(mn0, X - r); mx0 = fmax(mx0, X + r);
+        mn1 = fmin(mn1, Y - r); mx1 = fmax(mx1, Y + r);
+        mn2 = fmin(mn2, Z - r); mx2 = fmax(mx2, Z + r);
       }
 #pragma unroll
       for (int o = 1; o < L; o <<= 1) {
@@ -998,18 +1114,58 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       fb3 = axis_cell(fw3, Gd.lo1, Gd.ih1, Gd.g1);
       fb4 = axis_cell(fw4, Gd.lo2, Gd.ih2, Gd.g2);
       fb5 = axis_cell(fw5, Gd.lo2, Gd.ih2, Gd.g2);
+      flower_ok = true;
     };
-    int &rr = E_.rr, &zz = E_.zz, &yy = E_.yy, &part = E_.part, &zhi = E_.zhi, &ylo = E_.ylo, &yhi = E_.yhi;
-    rr = -1; zz = 0; yy = 0; part = 0; zhi = -1; ylo = 0; yhi = -1;
+    // (Row parts taken one by one by the whole group, with a vertex list each,
+    // cost most of a streamed cell: of 2^20 uniform points 82k stream and see
+    // 52 parts, 16 vertex lists, 10 batches and 45 candidates each; the stream
+    // kernel took 3.16 ms for them, with the parts spread over the lanes and
+    // the small ones merged into batches 1.32 ms; 16M clustered points, 4.9M
+    // streamed cells: 190 and 129 ms.)
+    // The ring's row parts (z, y, then the row's x-run on the ring's faces, or
+    // its two end cells), by ordinal: tested and looked up one per lane; the
+    // ones that can hold a cutting point are listed in order.  A part of at
+    // most kSubMin points holds no dense cell and is listed as its points
+    // [x, x + y); another one as -1 - ordinal in y, to be walked by itself.
+    int &rr = E_.rr, &pq = E_.pq, &np = E_.np, &zlo = E_.zlo, &ylo = E_.ylo, &nyr = E_.nyr, &rln = E_.rln, &rlp = E_.rlp;
+    rr = -1; pq = 0; np = 0; zlo = 0; ylo = 0; nyr = 1; rln = 0; rlp = 0;
+    int2* rowl = rowlist + (STREAM ? g * L : 0);
+    auto row_part = [&](int q, int& x0, int& x1, int& y, int& z) -> bool {
+      const int row = q >> 1;
+      const int zi = row / nyr;
+      z = zlo + zi;
+      y = ylo + (row - zi * nyr);
+      const int dz = z - cz, dy = y - cy;
+      if (dz == rr || dz == -rr || dy == rr || dy == -rr) {  // on a face of the ring
+        x0 = max(cx - rr, fb0);
+        x1 = min(cx + rr, fb1);
+        return !(q & 1) && x0 <= x1;
+      }
+      x0 = x1 = (q & 1) ? cx + rr : cx - rr;
+      return (q & 1) ? x1 <= fb1 : x0 >= fb0;
+    };
+    // can row part [x0, x1] of row (y, z) hold a cutting point: not inside the
+    // list's ball, and meeting the ball of a vertex in reach?  (one part per
+    // lane, or the same one in every lane)
+    auto part_reached = [&](int x0, int x1, int y, int z) -> bool {
+      const double ax = Gd.lo0 + x0 * Gd.h0 - p64x, ay = Gd.lo1 + y * Gd.h1 - p64y, az = Gd.lo2 + z * Gd.h2 - p64z;
+      const double bx = ax + (x1 - x0 + 1) * Gd.h0, by = ay + Gd.h1, bz = az + Gd.h2;
+      const double m = 2.0 * gmarg;  // (also covers the rounding of these sums)
+      if (in_list_ball(ax - m, bx + m, ay - m, by + m, az - m, bz + m)) return false;
+      const Box b = round_out(ax - m, bx + m, ay - m, by + m, az - m, bz + m);
+      bool any = reach_all;
+      for (int i = 0; i < nrv; ++i) any = any || meets(b, rv[i]);
+      return any;
+    };
     int jcur = 0, jend = 0;
     // the x-run being split at dense cells, and the sub-block of the dense
     // cell being scanned (sub-cells that meet the flower box)
-    int &rx = E_.rx, &rx1 = E_.rx1, &rrow = E_.rrow;
-    rx = 1; rx1 = 0; rrow = 0;
+    int &rx = E_.rx, &rx1 = E_.rx1, &rrow = E_.rrow, &yy = E_.yy, &zz = E_.zz;
+    rx = 1; rx1 = 0; rrow = 0; yy = 0; zz = 0;
     // dense cell rows: z and y outward from the seed's row (0, +1, -1, +2, ...)
-    int &dm = E_.dm, &dm0 = E_.dm0, &dm1 = E_.dm1, &dbase = E_.dbase, &dsx0 = E_.dsx0, &dsx1 = E_.dsx1,
+    int &dm = E_.dm, &dm0 = E_.dm0, &dm1 = E_.dm1, &dm2 = E_.dm2, &dbase = E_.dbase, &dsx0 = E_.dsx0, &dsx1 = E_.dsx1,
         &dsy0 = E_.dsy0, &dsy1 = E_.dsy1, &dsz0 = E_.dsz0, &dsz1 = E_.dsz1;
-    dm = 0; dm0 = 0; dm1 = 0; dbase = 0; dsx0 = 0; dsx1 = -1; dsy0 = 0; dsy1 = -1; dsz0 = 0; dsz1 = -1;
+    dm = 0; dm0 = 0; dm1 = 0; dm2 = 0; dbase = 0; dsx0 = 0; dsx1 = -1; dsy0 = 0; dsy1 = -1; dsz0 = 0; dsz1 = -1;
     int &dq1 = E_.dq1, &dq2 = E_.dq2, &kyn = E_.kyn, &kzn = E_.kzn;
     dq1 = 0; dq2 = 0; kyn = 0; kzn = 0;
     // next sub-row ordinal, their count; listed ranges, next one
@@ -1017,408 +1173,312 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
     dq = 0; dqn = 0; srn = 0; srp = 0;
     int& dsto = E_.dsto;  // the dense cell's sub-grid record: a.sub.start + dsto
     dsto = 0;
-    unsigned pend = 0;
-    int myj = -1;
-    R myd2 = R(0);
-    const R skip_scale = RECHECK ? R(1) - R(2e-6) : R(1) - R(1e-12);
-    // box of the current vertices whose ball leaves the list's ball
-    // (relative to the seed, widened by their error bounds): a candidate d
-    // beyond the list can cut only if such a vertex v has d.v > |d|^2 / 2,
-    // and max_v d.v <= sum_a max(d_a lo_a, d_a hi_a).  The cell only
-    // shrinks: a d that cuts the smaller cell cuts the larger one at some
-    // vertex, whose ball then holds d, a point beyond the list, so that
-    // vertex was in the older box, which is still a valid bound.
-    R bl0 = 0, bl1 = 0, bl2 = 0, bh0 = 0, bh1 = 0, bh2 = 0;
-    bool box_ok = false;
-    auto vertex_box = [&]() {
-      R a0 = R(3.0e38), a1 = R(3.0e38), a2 = R(3.0e38), b0 = R(-3.0e38), b1 = R(-3.0e38), b2 = R(-3.0e38);
-      for (int t = j; t < H; t += L) {
-        if (tri[vb + t] == kEmpty) continue;
-        float e;
-        const V3<R> v = vget_err(t, e);
-        const R X = v.x, Y = v.y, Z = v.z;
-        if (vball(t, X, Y, Z) < rlim) continue;
-        a0 = fmin(a0, X - e); b0 = fmax(b0, X + e);
-        a1 = fmin(a1, Y - e); b1 = fmax(b1, Y + e);
-        a2 = fmin(a2, Z - e); b2 = fmax(b2, Z + e);
-      }
-#pragma unroll
-      for (int o = 1; o < L; o <<= 1) {
-        a0 = fmin(a0, red_step(a0, o)); b0 = fmax(b0, red_step(b0, o));
-        a1 = fmin(a1, red_step(a1, o)); b1 = fmax(b1, red_step(b1, o));
-        a2 = fmin(a2, red_step(a2, o)); b2 = fmax(b2, red_step(b2, o));
-      }
-      bl0 = a0; bl1 = a1; bl2 = a2; bh0 = b0; bh1 = b1; bh2 = b2;
-    };
-    // relative slack of that test: above the rounding of the plane tests
-    // (and of the float path's rechecks)
-    const R sup_slack = RECHECK ? R(4e-6) : R(1e-12);
-    // A point cuts the cell iff it lies in the ball of some vertex v through
-    // the seed (centre v, radius |v|).  For a box of candidates (a grid row or
-    // a dense cell's sub-block), the vertices whose ball meets the box are
-    // listed in `out`; none: the box cannot hold a cutting point.  The balls
-    // are widened past rounding and the float path's vertex error bounds.
-    // Lists name vertex slots, so a cut (which reuses slots) invalidates them.
-    // Box bounds enter the tests in the clip's precision rounded outward, so
-    // that the box only grows.
-    auto out_lo = [](double v) -> R {
-      if constexpr (sizeof(R) == 4) {
-        const float f = (float)v;
-        return (double)f > v ? nextafterf(f, -INFINITY) : f;
-      } else {
-        return v;
-      }
-    };
-    auto out_hi = [](double v) -> R {
-      if constexpr (sizeof(R) == 4) {
-        const float f = (float)v;
-        return (double)f < v ? nextafterf(f, INFINITY) : f;
-      } else {
-        return v;
-      }
-    };
-    auto relevant = [&](unsigned char* out, double x0, double x1, double y0, double y1, double z0,
-                        double z1) -> int {
-      if (in_list_ball(x0 - p64x - gmarg, x1 - p64x + gmarg, y0 - p64y - gmarg, y1 - p64y + gmarg, z0 - p64z - gmarg,
-                       z1 - p64z + gmarg))
-        return 0;  // (group-uniform)
-      const R ax = out_lo(x0 - p64x - gmarg), bx = out_hi(x1 - p64x + gmarg);
-      const R ay = out_lo(y0 - p64y - gmarg), by = out_hi(y1 - p64y + gmarg);
-      const R az = out_lo(z0 - p64z - gmarg), bz = out_hi(z1 - p64z + gmarg);
-      unsigned bits = 0;
-#pragma unroll
-      for (int s2 = 0; s2 < S; ++s2) {
-        const int t = j + L * s2;
-        if (t < H && tri[vb + t] != kEmpty) {
-          const V3<R> v = vget(t);
-          const R X = v.x, Y = v.y, Z = v.z;
-          const R rv = vball(t, X, Y, Z);
-          const R gx = fmax(R(0), fmax(ax - X, X - bx)), gy = fmax(R(0), fmax(ay - Y, Y - by)),
-                  gz = fmax(R(0), fmax(az - Z, Z - bz));
-          if (rv >= rlim && gx * gx + gy * gy + gz * gz <= rv * rv) bits |= 1u << s2;
-        }
-      }
-      int tot;
-      int w = gexcl(__popc(bits), tot);
-#pragma unroll
-      for (int s2 = 0; s2 < S; ++s2)
-        if ((bits >> s2) & 1u) out[g * TMAX + w++] = (unsigned char)(j + L * s2);
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      return tot;
-    };
-    int nR = 0, nD = 0;
-    bool okR = false, okD = false;  // lists valid for the current vertices
+    // entries of the reach list whose ball meets the dense cell's sub-block
+    // (valid for the vertices they were listed for)
+    unsigned char* rd = relD + (STREAM ? g * kReach : 0);
+    int nD = 0;
+    bool okD = false;
     // can sub-row (sy, sz) of the dense cell's sub-block hold a cutting point:
     // not inside the list's ball, and (while the dense cell's vertex list is
     // valid) meeting the ball of a listed vertex?  (one sub-row per lane)
     auto sub_row_relevant = [&](int sy, int sz) -> bool {
       const double* dgp = dgeo + g * 9;
-      const int m2 = a.sub.start[dsto + 2];
       const double X0 = dsx0 == 0 ? dgp[0] : dgp[3] + dsx0 * dgp[6];
       const double X1 = dsx1 == dm0 - 1 ? dgp[0] + Gd.h0 : dgp[3] + (dsx1 + 1) * dgp[6];
       const double Y0 = sy == 0 ? dgp[1] : dgp[4] + sy * dgp[7];
       const double Y1 = sy == dm1 - 1 ? dgp[1] + Gd.h1 : dgp[4] + (sy + 1) * dgp[7];
       const double Z0 = sz == 0 ? dgp[2] : dgp[5] + sz * dgp[8];
-      const double Z1 = sz == m2 - 1 ? dgp[2] + Gd.h2 : dgp[5] + (sz + 1) * dgp[8];
-      if (in_list_ball(X0 - p64x - gmarg, X1 - p64x + gmarg, Y0 - p64y - gmarg, Y1 - p64y + gmarg, Z0 - p64z - gmarg,
-                       Z1 - p64z + gmarg))
-        return false;
-      if (!okD) return true;
-      const R ax = out_lo(X0 - p64x - gmarg), bx = out_hi(X1 - p64x + gmarg);
-      const R ay = out_lo(Y0 - p64y - gmarg), by = out_hi(Y1 - p64y + gmarg);
-      const R az = out_lo(Z0 - p64z - gmarg), bz = out_hi(Z1 - p64z + gmarg);
-      for (int i = 0; i < nD; ++i) {
-        const int t = relD[g * TMAX + i];
-        const V3<R> v = vget(t);
-        const R X = v.x, Y = v.y, Z = v.z;
-        const R rv = vball(t, X, Y, Z);
-        const R gx = fmax(R(0), fmax(ax - X, X - bx)), gy = fmax(R(0), fmax(ay - Y, Y - by)),
-                gz = fmax(R(0), fmax(az - Z, Z - bz));
-        if (gx * gx + gy * gy + gz * gz <= rv * rv) return true;
-      }
-      return false;
+      const double Z1 = sz == dm2 - 1 ? dgp[2] + Gd.h2 : dgp[5] + (sz + 1) * dgp[8];
+      const double ax = X0 - p64x - gmarg, bx = X1 - p64x + gmarg, ay = Y0 - p64y - gmarg, by = Y1 - p64y + gmarg,
+                   az = Z0 - p64z - gmarg, bz = Z1 - p64z + gmarg;
+      if (in_list_ball(ax, bx, ay, by, az, bz)) return false;
+      const Box b = round_out(ax, bx, ay, by, az, bz);
+      bool any = !okD || reach_all;
+      for (int i = 0; i < nD; ++i) any = any || meets(b, rv[rd[i]]);
+      return any;
     };
     bool rdense = false;  // the current range lies in a dense cell
+    // The next batch of up to L candidates, one per lane: jj, and tag, the
+    // order among the ranges of the batch (planes of a lower tag are applied
+    // first).  False when the scan is complete.  (Each step is taken by a whole
+    // group.)
+    auto next_batch = [&](int& jj, int& tag) -> bool {
+      jj = -1;
+      tag = 0;
+      for (;;) {
+        if (jcur < jend) {
+          // the rest of the current range, then (in a dense cell) the
+          // following listed sub-rows
+          int nb = 0;
+          for (;;) {
+            const int take = min(L - nb, jend - jcur);
+            if (j >= nb && j < nb + take) jj = jcur + (j - nb);
+            nb += take;
+            jcur += take;
+            if (nb == L || !rdense || srp >= srn) return true;
+            const int2 rg = srl[g * L + srp];
+            ++srp;
+            jcur = dbase + rg.x;
+            jend = dbase + rg.y;
+          }
+        }
+        if (dm > 0) {
+          // the dense cell's sub-rows inside the flower box, one x-run
+          // each, rows nearer the seed first: the next L of them are
+          // tested and their ranges read at once, one per lane, and the
+          // non-empty ranges listed
+          if (srp >= srn) {
+            if (dq >= dqn) {
+              dm = 0;
+              continue;
+            }
+            const int q = dq + j;
+            dq += L;
+            bool keep = false;
+            int lo = 0, hi = 0;
+            if (q < dqn) {
+              const int qz = q / kyn, qy = q - qz * kyn;
+              const int sz = dq2 + ((qz & 1) ? (qz + 1) >> 1 : -(qz >> 1));
+              const int sy = dq1 + ((qy & 1) ? (qy + 1) >> 1 : -(qy >> 1));
+              if (sz >= dsz0 && sz <= dsz1 && sy >= dsy0 && sy <= dsy1 && sub_row_relevant(sy, sz)) {
+                const int rowb = kSubHead + dm0 * (sy + dm1 * sz);
+                lo = a.sub.start[dsto + rowb + dsx0];
+                hi = a.sub.start[dsto + rowb + dsx1 + 1];
+                keep = lo < hi;
+              }
+            }
+            const unsigned kb = gballot(keep);
+            if (keep) srl[g * L + __popc(kb & below)] = make_int2(lo, hi);
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            srn = __popc(kb);
+            srp = 0;
+            continue;
+          }
+          const int2 rg = srl[g * L + srp];
+          ++srp;
+          jcur = dbase + rg.x;
+          jend = dbase + rg.y;
+          rdense = true;
+          continue;
+        }
+        if (rx <= rx1) {
+          int xe = rx1 + 1;
+          if (a.sub.info) {
+            // the stretch of cells without sub-grids: the group reads L
+            // consecutive cells' records at once and ends it at the
+            // first dense one
+            xe = rx;
+            for (;;) {
+              const int xc = xe + j;
+              const bool dn = xc <= rx1 && a.sub.info[rrow + xc].x >= 0;
+              const unsigned dmask = gballot(dn);
+              if (dmask) {
+                xe += __ffs(dmask) - 1;
+                break;
+              }
+              xe += L;
+              if (xe > rx1) {
+                xe = rx1 + 1;
+                break;
+              }
+            }
+          }
+          if (xe > rx) {
+            jcur = a.cell_start[rrow + rx];
+            jend = a.cell_start[rrow + xe];
+            rx = xe;
+            rdense = false;
+            continue;
+          }
+          // dense cell rx: its sub-cells inside the flower box
+          const int2 info = a.sub.info[rrow + rx];
+          const SubCell sc = sub_cell(a.sub.start + info.x);
+          dsx0 = sub_axis(fwb[0], sc.lo0, sc.ih0, sc.m0);
+          dsx1 = sub_axis(fwb[1], sc.lo0, sc.ih0, sc.m0);
+          dsy0 = sub_axis(fwb[2], sc.lo1, sc.ih1, sc.m1);
+          dsy1 = sub_axis(fwb[3], sc.lo1, sc.ih1, sc.m1);
+          dsz0 = sub_axis(fwb[4], sc.lo2, sc.ih2, sc.m2);
+          dsz1 = sub_axis(fwb[5], sc.lo2, sc.ih2, sc.m2);
+          {
+            // the sub-block's box (edge sub-cells reach the cell's faces)
+            const double cxl = Gd.lo0 + rx * Gd.h0, cyl = Gd.lo1 + yy * Gd.h1, czl = Gd.lo2 + zz * Gd.h2;
+            const double w0 = 1.0 / sc.ih0, w1 = 1.0 / sc.ih1, w2 = 1.0 / sc.ih2;
+            const double X0 = dsx0 == 0 ? cxl : sc.lo0 + dsx0 * w0;
+            const double X1 = dsx1 == sc.m0 - 1 ? cxl + Gd.h0 : sc.lo0 + (dsx1 + 1) * w0;
+            const double Y0 = dsy0 == 0 ? cyl : sc.lo1 + dsy0 * w1;
+            const double Y1 = dsy1 == sc.m1 - 1 ? cyl + Gd.h1 : sc.lo1 + (dsy1 + 1) * w1;
+            const double Z0 = dsz0 == 0 ? czl : sc.lo2 + dsz0 * w2;
+            const double Z1 = dsz1 == sc.m2 - 1 ? czl + Gd.h2 : sc.lo2 + (dsz1 + 1) * w2;
+            const double ax = X0 - p64x - gmarg, bx = X1 - p64x + gmarg, ay = Y0 - p64y - gmarg,
+                         by = Y1 - p64y + gmarg, az = Z0 - p64z - gmarg, bz = Z1 - p64z + gmarg;
+            nD = 0;
+            okD = true;
+            bool hit = false;
+            if (!in_list_ball(ax, bx, ay, by, az, bz)) {
+              const Box b = round_out(ax, bx, ay, by, az, bz);
+              for (int i0 = 0; i0 < nrv; i0 += L) {
+                const bool on = i0 + j < nrv && meets(b, rv[i0 + j]);
+                const unsigned gbits = gballot(on);
+                if (on) rd[nD + __popc(gbits & below)] = (unsigned char)(i0 + j);
+                nD += __popc(gbits);
+              }
+              hit = nD > 0 || reach_all;
+            }
+            if (j == 0) {
+              double* dgp = dgeo + g * 9;
+              dgp[0] = cxl; dgp[1] = cyl; dgp[2] = czl;
+              dgp[3] = sc.lo0; dgp[4] = sc.lo1; dgp[5] = sc.lo2;
+              dgp[6] = w0; dgp[7] = w1; dgp[8] = w2;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            dm = hit ? 1 : 0;
+          }
+          if (dm) {
+            dsto = info.x;
+            dbase = a.cell_start[rrow + rx];
+            dm0 = sc.m0;
+            dm1 = sc.m1;
+            dm2 = sc.m2;
+            dq1 = min(max(sub_axis(p64y, sc.lo1, sc.ih1, sc.m1), dsy0), dsy1);
+            dq2 = min(max(sub_axis(p64z, sc.lo2, sc.ih2, sc.m2), dsz0), dsz1);
+            // offsets 0, +1, -1, ... up to the farther end of each range
+            kyn = 2 * max(dq1 - dsy0, dsy1 - dq1) + 1;
+            kzn = 2 * max(dq2 - dsz0, dsz1 - dq2) + 1;
+            dq = 0;
+            dqn = kyn * kzn;
+            srn = srp = 0;
+          }
+          ++rx;
+          continue;
+        }
+        if (rlp < rln) {
+          // whole listed parts while they fit the batch
+          int nb = 0;
+          while (rlp < rln) {
+            const int2 e = rowl[rlp];
+            if (e.y < 0 || nb + e.y > L) break;
+            if (j >= nb && j < nb + e.y) {
+              jj = e.x + (j - nb);
+              tag = rlp;
+            }
+            nb += e.y;
+            ++rlp;
+          }
+          rdense = false;
+          if (nb > 0) return true;
+          // a part with more points: tested again for the vertices as they are
+          int x0, x1;
+          row_part(-1 - rowl[rlp].y, x0, x1, yy, zz);
+          ++rlp;
+          if (part_reached(x0, x1, yy, zz)) {
+            rrow = Gd.g0 * (yy + Gd.g1 * zz);
+            rx = x0;
+            rx1 = x1;
+          }
+          continue;
+        }
+        if (pq < np) {
+          const int q = pq + j;
+          pq += L;
+          bool keep = false;
+          int lo = 0, len = 0, x0, x1, y, z;
+          if (q < np && row_part(q, x0, x1, y, z) && part_reached(x0, x1, y, z)) {
+            const int row = Gd.g0 * (y + Gd.g1 * z);
+            lo = a.cell_start[row + x0];
+            len = a.cell_start[row + x1 + 1] - lo;
+            keep = len > 0;
+          }
+          const unsigned kb = gballot(keep);
+          if (keep) rowl[__popc(kb & below)] = make_int2(lo, len <= kSubMin ? len : -1 - q);
+          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+          rln = __popc(kb);
+          rlp = 0;
+          continue;
+        }
+        // ring rr finished (or none yet): final when the block contains the flower box
+        if (!flower_ok) flower_box();
+        if (rr >= 0 && cx - rr <= fb0 && cx + rr >= fb1 && cy - rr <= fb2 && cy + rr >= fb3 && cz - rr <= fb4 &&
+            cz + rr >= fb5)
+          return false;
+        ++rr;
+        zlo = max(cz - rr, fb4);
+        ylo = max(cy - rr, fb2);
+        nyr = min(cy + rr, fb3) - ylo + 1;
+        pq = 0;
+        np = nyr > 0 ? max(0, min(cz + rr, fb5) - zlo + 1) * nyr * 2 : 0;
+      }
+    };
+    unsigned pend = 0;
+    int myj = -1, mytag = 0;
+    R myx = R(0), myy = R(0), myz = R(0), myd2 = R(0);
+    const R skip_scale = RECHECK ? R(1) - R(2e-6) : R(1) - R(1e-12);
     while (__any(strm && st == ST_RUN)) {
       const bool act = strm && st == ST_RUN;
-      // refill this group's batch of candidates (group-uniform loop)
-      if (act && pend == 0u) {
-        if (!box_ok) {
-          vertex_box();
-          box_ok = true;
-        }
-        bool done = false;
-        while (!done) {
-          if (jcur >= jend) {
-            // next contiguous range of points: a sub-cell x-run of a dense
-            // cell, a stretch of sparse cells of the current x-run, or the
-            // ring's next x-run of grid cells
-            bool have_run = false;
-            while (!have_run) {
-              if (dm > 0) {
-                // the dense cell's sub-rows inside the flower box, one x-run
-                // each, rows nearer the seed first: the next L of them are
-                // tested and their ranges read at once, one per lane, and the
-                // non-empty ranges listed
-                if (srp >= srn) {
-                  if (dq >= dqn) {
-                    dm = 0;
-                    continue;
-                  }
-                  const int q = dq + j;
-                  dq += L;
-                  bool keep = false;
-                  int lo = 0, hi = 0;
-                  if (q < dqn) {
-                    const int qz = q / kyn, qy = q - qz * kyn;
-                    const int sz = dq2 + ((qz & 1) ? (qz + 1) >> 1 : -(qz >> 1));
-                    const int sy = dq1 + ((qy & 1) ? (qy + 1) >> 1 : -(qy >> 1));
-                    if (sz >= dsz0 && sz <= dsz1 && sy >= dsy0 && sy <= dsy1 && sub_row_relevant(sy, sz)) {
-                      const int rowb = kSubHead + dm0 * (sy + dm1 * sz);
-                      lo = a.sub.start[dsto + rowb + dsx0];
-                      hi = a.sub.start[dsto + rowb + dsx1 + 1];
-                      keep = lo < hi;
-                    }
-                  }
-                  int tot;
-                  const int w = gexcl(keep ? 1 : 0, tot);
-                  if (keep) srl[g * L + w] = make_int2(lo, hi);
-                  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                  srn = tot;
-                  srp = 0;
-                  continue;
-                }
-                const int2 rg = srl[g * L + srp];
-                ++srp;
-                jcur = dbase + rg.x;
-                jend = dbase + rg.y;
-                have_run = true;
-                rdense = true;
-                continue;
-              }
-              if (rx <= rx1) {
-                int xe = rx1 + 1;
-                if (a.sub.info) {
-                  // the stretch of cells without sub-grids: the group reads L
-                  // consecutive cells' records at once and ends it at the
-                  // first dense one
-                  xe = rx;
-                  for (;;) {
-                    const int xc = xe + j;
-                    const bool dn = xc <= rx1 && a.sub.info[rrow + xc].x >= 0;
-                    const unsigned long long dmask = (__ballot(dn) >> gb) & LOWL;
-                    if (dmask) {
-                      xe += __ffsll((long long)dmask) - 1;
-                      break;
-                    }
-                    xe += L;
-                    if (xe > rx1) {
-                      xe = rx1 + 1;
-                      break;
-                    }
-                  }
-                }
-                if (xe > rx) {
-                  jcur = a.cell_start[rrow + rx];
-                  jend = a.cell_start[rrow + xe];
-                  rx = xe;
-                  have_run = jcur < jend;
-                  rdense = false;
-                  continue;
-                }
-                // dense cell rx: its sub-cells inside the flower box
-                const int2 info = a.sub.info[rrow + rx];
-                const SubCell sc = sub_cell(a.sub.start + info.x);
-                dsx0 = sub_axis(fwb[0], sc.lo0, sc.ih0, sc.m0);
-                dsx1 = sub_axis(fwb[1], sc.lo0, sc.ih0, sc.m0);
-                dsy0 = sub_axis(fwb[2], sc.lo1, sc.ih1, sc.m1);
-                dsy1 = sub_axis(fwb[3], sc.lo1, sc.ih1, sc.m1);
-                dsz0 = sub_axis(fwb[4], sc.lo2, sc.ih2, sc.m2);
-                dsz1 = sub_axis(fwb[5], sc.lo2, sc.ih2, sc.m2);
-                {
-                  // the sub-block's box (edge sub-cells reach the cell's faces)
-                  const double cxl = Gd.lo0 + rx * Gd.h0, cyl = Gd.lo1 + yy * Gd.h1, czl = Gd.lo2 + zz * Gd.h2;
-                  const double w0 = 1.0 / sc.ih0, w1 = 1.0 / sc.ih1, w2 = 1.0 / sc.ih2;
-                  const double X0 = dsx0 == 0 ? cxl : sc.lo0 + dsx0 * w0;
-                  const double X1 = dsx1 == sc.m0 - 1 ? cxl + Gd.h0 : sc.lo0 + (dsx1 + 1) * w0;
-                  const double Y0 = dsy0 == 0 ? cyl : sc.lo1 + dsy0 * w1;
-                  const double Y1 = dsy1 == sc.m1 - 1 ? cyl + Gd.h1 : sc.lo1 + (dsy1 + 1) * w1;
-                  const double Z0 = dsz0 == 0 ? czl : sc.lo2 + dsz0 * w2;
-                  const double Z1 = dsz1 == sc.m2 - 1 ? czl + Gd.h2 : sc.lo2 + (dsz1 + 1) * w2;
-                  nD = relevant(relD, X0, X1, Y0, Y1, Z0, Z1);
-                  okD = true;
-                  if (j == 0) {
-                    double* dgp = dgeo + g * 9;
-                    dgp[0] = cxl; dgp[1] = cyl; dgp[2] = czl;
-                    dgp[3] = sc.lo0; dgp[4] = sc.lo1; dgp[5] = sc.lo2;
-                    dgp[6] = w0; dgp[7] = w1; dgp[8] = w2;
-                  }
-                  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                  if (nD == 0) {
-                    ++rx;
-                    continue;
-                  }
-                }
-                dsto = info.x;
-                dbase = a.cell_start[rrow + rx];
-                dm = 1;
-                dm0 = sc.m0;
-                dm1 = sc.m1;
-                dq1 = min(max(sub_axis(p64y, sc.lo1, sc.ih1, sc.m1), dsy0), dsy1);
-                dq2 = min(max(sub_axis(p64z, sc.lo2, sc.ih2, sc.m2), dsz0), dsz1);
-                // offsets 0, +1, -1, ... up to the farther end of each range
-                kyn = 2 * max(dq1 - dsy0, dsy1 - dq1) + 1;
-                kzn = 2 * max(dq2 - dsz0, dsz1 - dq2) + 1;
-                dq = 0;
-                dqn = kyn * kzn;
-                srn = srp = 0;
-                ++rx;
-                continue;
-              }
-              if (rr < 0 || zz > zhi) {
-                // ring rr finished (or none yet): final when the block contains the flower box
-                flower_box();
-                if (rr >= 0 && cx - rr <= fb0 && cx + rr >= fb1 && cy - rr <= fb2 && cy + rr >= fb3 &&
-                    cz - rr <= fb4 && cz + rr >= fb5) {
-                  done = true;
-                  break;
-                }
-                ++rr;
-                zz = max(cz - rr, fb4);
-                zhi = min(cz + rr, fb5);
-                ylo = max(cy - rr, fb2);
-                yhi = min(cy + rr, fb3);
-                yy = ylo;
-                part = 0;
-                if (ylo > yhi) zz = zhi + 1;  // empty ring
-                continue;
-              }
-              const bool face = zz == cz - rr || zz == cz + rr || yy == cy - rr || yy == cy + rr;
-              int x0 = 1, x1 = 0;
-              if (part == 0) {
-                if (face) { x0 = max(cx - rr, fb0); x1 = min(cx + rr, fb1); }
-                else if (cx - rr >= fb0) { x0 = x1 = cx - rr; }
-                part = 1;
-              } else if (part == 1) {
-                if (!face && rr > 0 && cx + rr <= fb1) { x0 = x1 = cx + rr; }
-                part = 2;
-              } else {
-                part = 0;
-                if (++yy > yhi) { yy = ylo; ++zz; }
-                continue;
-              }
-              if (x0 <= x1) {
-                const double Y0 = Gd.lo1 + yy * Gd.h1, Z0 = Gd.lo2 + zz * Gd.h2;
-                nR = relevant(relR, Gd.lo0 + x0 * Gd.h0, Gd.lo0 + (x1 + 1) * Gd.h0, Y0, Y0 + Gd.h1, Z0, Z0 + Gd.h2);
-                okR = true;
-                if (nR > 0) {
-                  rrow = Gd.g0 * (yy + Gd.g1 * zz);
-                  rx = x0;
-                  rx1 = x1;
-                }
-              }
-            }
-            if (done) break;
-          }
-          // batch of up to L candidates, one per lane: the rest of the current
-          // range, then (in a dense cell) the following listed sub-rows;
-          // filtered by list key and radius
-          int jj = -1;
-          {
-            int nb = 0;
-            for (;;) {
-              const int take = min(L - nb, jend - jcur);
-              if (j >= nb && j < nb + take) jj = jcur + (j - nb);
-              nb += take;
-              jcur += take;
-              if (nb == L || !rdense || srp >= srn) break;
-              const int2 rg = srl[g * L + srp];
-              ++srp;
-              jcur = dbase + rg.x;
-              jend = dbase + rg.y;
-            }
-          }
-          bool pass = false;
-          myj = -1;
-          if (jj >= 0 && jj != sid) {
-            const Rec4 q = rec[jj];
-            const R d2c = dist2_nc((R)q.x - px, (R)q.y - py, (R)q.z - pz);
-            const bool beyond_list = d2c > dk2 || (d2c == dk2 && jj > ik);
-            pass = beyond_list && d2c * skip_scale <= R(4) * (RECHECK ? (R)R2up : R2);
-            if (pass) {
-              const R ex = (R)q.x - px, ey = (R)q.y - py, ez = (R)q.z - pz;
-              const R sup = fmax(ex * bl0, ex * bh0) + fmax(ey * bl1, ey * bh1) + fmax(ez * bl2, ez * bh2);
-              const R mag = fabs(ex) * fmax(fabs(bl0), fabs(bh0)) + fabs(ey) * fmax(fabs(bl1), fabs(bh1)) +
-                            fabs(ez) * fmax(fabs(bl2), fabs(bh2));
-              pass = sup >= R(0.5) * d2c - sup_slack * (mag + d2c);
-              if (pass) {
-                // exact: some vertex on the far side of the bisector (up to
-                // the plane test's own uncertainty window), against the
-                // vertices listed for this range, or all of them
-                const R cc = R(0.5) * d2c;
-                const R nrm1 = fabs(ex) + fabs(ey) + fabs(ez);
-                auto side = [&](int t) -> bool {
-                  float ev;
-                  const V3<R> v = vget_err(t, ev);
-                  const R X = v.x, Y = v.y, Z = v.z;
-                  const R sv = ex * X + ey * Y + ez * Z - cc;
-                  const R scale = fabs(ex * X) + fabs(ey * Y) + fabs(ez * Z) + cc;
-                  const R win = RECHECK ? (R)a.eps * scale + nrm1 * ev : R(1e-12) * scale;
-                  return sv > -win;
-                };
-                bool cuts = false;
-                if (rdense ? okD : okR) {
-                  const unsigned char* rl = rdense ? relD : relR;
-                  const int nr = rdense ? nD : nR;
-                  for (int i = 0; i < nr && !cuts; ++i) cuts = side(rl[g * TMAX + i]);
-                } else {
-                  for (int t = 0; t < H && !cuts; ++t)
-                    if (tri[vb + t] != kEmpty) cuts = side(t);
-                }
-                pass = cuts;
-              }
-            }
-            myj = jj;
-            myd2 = d2c;
-          }
-          pend = (unsigned)((__ballot(pass) >> gb) & LOWL);
-          if (!pass) myj = -1;
-          if (pend) break;
-        }
-        if (done) {
+      // the group's next batch with a candidate that may cut (group-uniform
+      // loop); filtered by list key and radius, and by whether some vertex in
+      // reach lies on the far side of the bisector, up to a bound on the plane
+      // test's own uncertainty (and on the float arithmetic here)
+      while (act && pend == 0u) {
+        if (!reach_ok) reach();
+        if (!next_batch(myj, mytag)) {
           st = VOTESS_CELL_CERTIFIED;
           kneed = a.k + 1;
+          break;
+        }
+        bool pass = false;
+        if (myj >= 0 && myj != sid) {
+          const Rec4 q = rec[myj];
+          myx = (R)q.x - px;
+          myy = (R)q.y - py;
+          myz = (R)q.z - pz;
+          myd2 = dist2_nc(myx, myy, myz);
+          const bool beyond_list = myd2 > dk2 || (myd2 == dk2 && myj > ik);
+          pass = beyond_list && myd2 * skip_scale <= R(4) * (RECHECK ? (R)R2up : R2);
+        }
+        if (pass && !reach_all) {
+          const float ex = (float)myx, ey = (float)myy, ez = (float)myz, c = 0.5f * (float)myd2;
+          float far = -c;
+          if (rdense && okD) {
+            for (int i = 0; i < nD; ++i) {
+              const float4 v = rv[rd[i]];
+              far = fmaxf(far, ex * v.x + ey * v.y + ez * v.z);
+            }
+          } else {
+            for (int i = 0; i < nrv; ++i) {
+              const float4 v = rv[i];
+              far = fmaxf(far, ex * v.x + ey * v.y + ez * v.z);
+            }
+          }
+          const float r2 = RECHECK ? R2up : (float)R2;
+          const float w = (wv + 2e-6f) * (c + __builtin_amdgcn_sqrtf(2.0f * c * r2));
+          pass = !(far < c - w);
+        }
+        pend = gballot(pass);
+      }
+      // nearest pending candidate of the group, range by range
+      bool run2 = act && st == ST_RUN && pend != 0u;
+      int bl = run2 ? __ffs(pend) - 1 : j;
+      if (__any(run2 && (pend & (pend - 1u)) != 0u)) {
+        const bool on = run2 && ((pend >> j) & 1u);
+        R best = on ? myd2 : R(3.0e38);
+        int bt = on ? mytag : 0x7FFFFFFF;
+        bl = j;
+#pragma unroll
+        for (int o = 1; o < L; o <<= 1) {
+          const R ob = red_step(best, o);
+          const int ot = red_step(bt, o), ol = red_step(bl, o);
+          if (ot < bt || (ot == bt && (ob < best || (ob == best && ol < bl)))) { best = ob; bt = ot; bl = ol; }
         }
       }
-      // nearest pending candidate of the group
-      bool run2 = act && st == ST_RUN && pend != 0u;
-      R best = (run2 && myj >= 0 && ((pend >> j) & 1u)) ? myd2 : R(3.0e38);
-      int bl = j;
-#pragma unroll
-      for (int o = 1; o < L; o <<= 1) {
-        const R ob = red_step(best, o);
-        const int ol = red_step(bl, o);
-        if (ob < best || (ob == best && ol < bl)) { best = ob; bl = ol; }
-      }
       const int nb2 = __shfl(myj, gb + bl, 64);
-      R nx = 0, ny = 0, nz = 0, c = 0, d2 = 0;
+      const R nx = shfl_t(myx, gb + bl), ny = shfl_t(myy, gb + bl), nz = shfl_t(myz, gb + bl);
+      const R d2 = dist2_nc(nx, ny, nz), c = R(0.5) * d2;
       if (run2) {
         pend &= ~(1u << bl);
-        const Rec4 q = rec[nb2];
-        nx = (R)q.x - px;
-        ny = (R)q.y - py;
-        nz = (R)q.z - pz;
-        d2 = dist2_nc(nx, ny, nz);
-        c = R(0.5) * d2;
         // the radius may have shrunk since the batch was filtered
         if (d2 * skip_scale > R(4) * (RECHECK ? (R)R2up : R2)) run2 = false;
       }
-      const M alive_prev = alive;
-      apply_plane(run2, nx, ny, nz, c, d2, nb2);
-      if (alive != alive_prev) {
-        box_ok = false;
-        okR = okD = false;
-      }
+      if (apply_plane(run2, nx, ny, nz, c, d2, nb2)) reach_ok = okD = flower_ok = false;
     }
     if (strm && st == VOTESS_CELL_CERTIFIED && j == 0 && a.counters) atomicAdd(&a.counters[4], 1ull);
   }
@@ -1646,7 +1706,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
     int fin = st;
     if (fin == VOTESS_CELL_CERTIFIED && (ntot > a.max_nbr || (a.max_vert > 0 && vtot > a.max_vert)))
       fin = VOTESS_CELL_CAPACITY;
-    a.status[row] = (uint8_t)fin;
+    a.status[row] = (uint8_t)fin | (a.rest || ((a.mark >> fin) & 1) ? kLeft : (uint8_t)0);
     a.nbr_count[row] = fin == VOTESS_CELL_CERTIFIED ? ntot : 0;
     a.volume[row] = fin == VOTESS_CELL_CERTIFIED ? vol : 0.0;
     if (a.centroid) {
@@ -1667,14 +1727,99 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
   }
 }
 
+// One wave (= one block) clips 64 / L cells, one per group.  With `rest`, the
+// list kernel has been over the launch's cells and left some: cells that
+// outgrew it (taken again from the box) and, when this is the stream kernel,
+// cells that their lists did not certify (resumed).  They are picked out by
+// the mark in their status and packed within each 64 cells: the L waves that
+// share 64 cells take the first 64 / L cells left, the next ones, ..., and most
+// waves find nothing and end.  The marks stay until k_unmark, so that all of
+// these waves see the same ones.  (A wave that loops over its 64 cells instead
+// keeps so many invariants of the loop in registers that it spills.)
+// Blocks run in an XCD-aware order (they are dealt round-robin over the eight
+// XCDs): launched block b takes logical block (b mod 8) per + b / 8, so each
+// XCD clips a contiguous stretch of grid-sorted cells, whose neighbours its L2
+// then holds.
+// Held to 3 waves per SIMD but for the large kernel: the compiler would
+// otherwise give the stream variants ~225 VGPRs (2 waves), and with the third
+// wave hiding load latency they run ~20% faster despite some spills.
+template <typename P, typename R, int L, int TMAX, int PMAX, bool RECHECK, bool STREAM>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ? 3 : 1))) void k_clip(ClipArgs a) {
+  constexpr int G = 64 / L;
+  const int nblk = clip_blocks(a.nc, G, a.rest), per = (nblk + 7) / 8;
+  const int lblk = (int)(blockIdx.x % 8u) * per + (int)(blockIdx.x / 8u);
+  if (lblk >= nblk) return;  // the whole (one-wave) block
+  const int lane = threadIdx.x, g = lane / L;
+  long long t_idx;
+  bool have, resume = false;
+  if (a.rest) {
+    const long long base = (long long)(lblk / L) * 64;
+    int stat = 0;
+    if (base + lane < a.nc) stat = a.status[a.out_by_id && a.cells ? (long long)a.cells[base + lane] : base + lane];
+    unsigned long long todo = __ballot((stat & kLeft) != 0);
+    const int first = lblk % L * G;
+    if (__popcll(todo) <= first) return;
+    for (int i = 0; i < first; ++i) todo &= todo - 1ull;
+    int at = -1;
+#pragma unroll
+    for (int i = 0; i < G; ++i) {  // the i-th of the cells left goes to group i
+      if (todo && g == i) at = __ffsll((long long)todo) - 1;
+      todo &= todo - 1ull;
+    }
+    have = at >= 0;
+    t_idx = base + (have ? at : 0);
+    resume = STREAM && have && __shfl(stat, have ? at : 0, 64) == (kLeft | VOTESS_CELL_RADIUS);
+  } else {
+    t_idx = (long long)lblk * G + g;
+    have = t_idx < a.nc;
+    if (!have) t_idx = 0;
+  }
+  clip_group<P, R, L, TMAX, PMAX, RECHECK, STREAM>(a, t_idx, have, resume);
+}
+
+// takes the marks off again
+__global__ void k_unmark(uint8_t* status, const int* cells, int nc) {
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= nc) return;
+  uint8_t* p = status + (cells ? (long long)cells[t] : t);
+  const uint8_t v = *p;
+  if (v & kLeft) *p = v & (uint8_t)~kLeft;
+}
+
+template <typename P, typename R, int L, int TMAX, int PMAX, bool RECHECK, bool STREAM>
+void launch(ClipArgs ca, bool rest, hipStream_t st) {
+  ca.rest = rest;
+  const unsigned blocks = (unsigned)(8 * ((clip_blocks(ca.nc, 64 / L, rest) + 7) / 8));
+  k_clip<P, R, L, TMAX, PMAX, RECHECK, STREAM><<<blocks, 64, 0, st>>>(ca);
+}
+
 template <typename P, typename R, int L, int TMAX, int PMAX, bool RECHECK>
 votess_status run(const ClipArgs& ca, hipStream_t st) {
-  constexpr int G = 64 / L;
-  const unsigned blocks = (unsigned)(8 * (((ca.nc + G - 1) / G + 7) / 8));
   if (ca.stream)
-    k_clip<P, R, L, TMAX, PMAX, RECHECK, true><<<blocks, 64, 0, st>>>(ca);
+    launch<P, R, L, TMAX, PMAX, RECHECK, true>(ca, false, st);
   else
-    k_clip<P, R, L, TMAX, PMAX, RECHECK, false><<<blocks, 64, 0, st>>>(ca);
+    launch<P, R, L, TMAX, PMAX, RECHECK, false>(ca, false, st);
+  VT_HIP(hipGetLastError());
+  return VOTESS_OK;
+}
+
+// The fast kernels.  Lists are clipped by 8 lanes per cell with 48 vertex
+// slots; what is left goes to 16 lanes per cell with 64 slots.  A stream cell
+// waits on loads and its batches of candidates fill 16 lanes; list cells are
+// bound by vector instructions, and 8 lanes waste fewer of them (a cut makes
+// about 6 new vertices).
+template <typename P, typename R, bool RECHECK>
+votess_status run_fast(ClipArgs ca, bool split, hipStream_t st) {
+  if (!split) return run<P, R, 16, 64, 32, RECHECK>(ca, st);
+  ca.save = ca.stream;
+  ca.mark = 1 << VOTESS_CELL_CAPACITY | (ca.stream ? 1 << VOTESS_CELL_RADIUS : 0);
+  launch<P, R, kListLanes, kListVert, 32, RECHECK, false>(ca, false, st);
+  ca.save = ca.mark = 0;
+  if (ca.stream)
+    launch<P, R, 16, 64, 32, RECHECK, true>(ca, true, st);
+  else
+    launch<P, R, 16, 64, 32, RECHECK, false>(ca, true, st);
+  k_unmark<<<(unsigned)(((long long)ca.nc + 255) / 256), 256, 0, st>>>(ca.status, ca.out_by_id ? ca.cells : nullptr, ca.nc);
   VT_HIP(hipGetLastError());
   return VOTESS_OK;
 }
@@ -1722,12 +1867,14 @@ votess_status launch_clip(const ClipLaunch& a, hipStream_t st) {
   if (a.stream && (a.knn_dist == VOTESS_F32) != f32)
     return fail(VOTESS_EINVAL, "clip: the stream phase needs k-lists built in the clip precision");
   if (a.stream && !a.cell_start) return fail(VOTESS_EINVAL, "clip: the stream phase needs cell_start");
-  // the fast kernel: 16 lanes per cell, measured faster than 8 (fewer cells
-  // per wave diverge in the stream phase) and than 4 or 32
+  c.rest = c.mark = c.save = 0;
   if (a.capacity == 0) {
-    if (f32) return run<float, float, 16, 64, 32, true>(c, st);
-    if (a.dtype == VOTESS_F32) return run<float, double, 16, 64, 32, false>(c, st);
-    return run<double, double, 16, 64, 32, false>(c, st);
+    // two launches, unless there is no list, the state of a cell has no room
+    // in its neighbour row, or two cells may share one
+    const bool split = a.k > 0 && (!a.stream || a.max_nbr >= kStateWords) && a.own_rows;
+    if (f32) return run_fast<float, float, true>(c, split, st);
+    if (a.dtype == VOTESS_F32) return run_fast<float, double, false>(c, split, st);
+    return run_fast<double, double, false>(c, split, st);
   }
   // the large-capacity kernel: 32 lanes per cell (two cells per wave keep its
   // LDS per workgroup low enough for more than one wave per SIMD)

@@ -138,6 +138,7 @@ struct ClipLaunch {
   double* r2out = nullptr;       // [rows] R^2 of each certified cell (nullable; an upper bound on the float path)
   unsigned long long* counters;  // [8]: rechecks, unresolved, capacity, refined, streamed (certified by the
                                  // stream phase), stream entries -- nullable
+  int own_rows = 1;              // 0: `cells` may name a cell twice with out_by_id
   int stream = 0;                // 1: uncertified cells continue by grid rings
   const int32_t* cell_start = nullptr;
   GridDev grid{};
