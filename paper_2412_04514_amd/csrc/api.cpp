@@ -499,7 +499,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
   VT_TRY(alloc_buf(ctx, vol, nn * 8));
   VT_TRY(alloc_buf(ctx, cells, nn * 4));
   VT_TRY(alloc_buf(ctx, cells2, nn * 4));
-  VT_TRY(alloc_buf(ctx, counters, 64));
+  VT_TRY(alloc_buf(ctx, counters, 8 * kClipCounters));
   if (wantv) {
     VT_TRY(alloc_buf(ctx, vcount, nn * 4));
     VT_TRY(alloc_buf(ctx, verts, nn * kMaxVert * 3 * 8));
@@ -511,7 +511,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
   }
   VT_TRY(ctx->ws.reserve(std::max(grid_sort_workspace(n, grid.ncells), scan_workspace(n) + nn * 4 + 4096)));
   VT_HIP(hipMemsetAsync(ctx->d_err, 0, 4, st));
-  VT_HIP(hipMemsetAsync(counters.p, 0, 64, st));
+  VT_HIP(hipMemsetAsync(counters.p, 0, 8 * kClipCounters, st));
 
   // ---- a1-a3 grid sort
   {
@@ -563,20 +563,69 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
   int nretry = 0;
   for (int kk = k_first; !fused && nretry < P.max_gpu_retries && kk < kMaxK; ++nretry) kk = std::min(2 * kk, kMaxK);
 
-  // cells that entered the stream phase so far (device counter 5)
-  auto stream_entries = [&](int64_t& out_v) -> votess_status {
-    unsigned long long v = 0;
-    VT_HIP(hipMemcpyAsync(&v, counters.get<unsigned long long>() + 5, 8, hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
-    out_v = (int64_t)v;
-    return VOTESS_OK;
-  };
-  int64_t entered = 0, entered_before = 0;
-  // ---- first pass over all cells
-  int k = P.k0;
+  // The passes whose lists hold at most 64 entries are clipped as one: every
+  // cell gets the list of the last of them, whose first entries are the lists
+  // of the earlier ones, and the clip counts what those would have left.  (A
+  // pass at k0 = 32 certifies 14% of clustered and 22% of uniform cells; the
+  // others were listed and clipped again from the start: 2^20 uniform points,
+  // float, 16.3 ms in two passes and 12.2 ms in one; 3M clustered points in
+  // double 108 and 87 ms.)
+  int k = P.k0, merged = 0, level[kLevels] = {0, 0, 0};
+  if (!P.kmodel && !fused && P.force_fail_every == 0)
+    while (merged < std::min(nretry, kLevels) && 2 * k <= 64 && valid_k(2 * k)) {
+      level[merged++] = k;
+      k *= 2;
+    }
+  int64_t entered = 0;  // cells that entered the stream phase before the current pass
   int nfail = 0;
+  bool all_listed = false;  // knn holds the k-list of every cell, by sorted index
   int32_t* cur = cells.get<int32_t>();
   int32_t* nxt = cells2.get<int32_t>();
+  // entry of a pass in the statistics, after its clip (and the passes that it took in)
+  auto record_pass = [&](int64_t cells_in, int taken) -> votess_status {
+    unsigned long long cnt[kClipCounters];
+    VT_HIP(hipMemcpyAsync(cnt, counters.p, sizeof(cnt), hipMemcpyDeviceToHost, st));
+    VT_HIP(hipStreamSynchronize(st));
+    for (int i = 0; i <= taken && S.npasses < VOTESS_MAX_PASSES; ++i, ++S.npasses) {
+      const bool last = i == taken;
+      const int64_t left = last ? nfail : (int64_t)cnt[kLevelCounter + i];
+      S.pass_k[S.npasses] = last ? k : level[i];
+      S.pass_cells[S.npasses] = cells_in;
+      S.pass_failed[S.npasses] = left;
+      S.pass_streamed[S.npasses] = last ? (int64_t)cnt[5] - entered : 0;
+      cells_in = left;
+    }
+    entered = (int64_t)cnt[5];
+    return VOTESS_OK;
+  };
+  // cells that overflowed the fast kernel rerun in the large-capacity kernel
+  auto capacity_pass = [&](const int32_t* ids, int cnt, int kk, bool strm) -> votess_status {
+    int ncap = 0;
+    VT_TRY(launch_compact_failed(status.get<uint8_t>(), ids, cnt, nxt, ctx->d_counter, 1u << VOTESS_CELL_CAPACITY,
+                                 ctx->ws, st));
+    VT_HIP(hipMemcpyAsync(&ncap, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
+    VT_HIP(hipStreamSynchronize(st));
+    if (ncap == 0) return VOTESS_OK;
+    S.capacity_cells += ncap;
+    Buf knn2;
+    if (kk > 0 && !all_listed) {  // (no list in the fused form: the large kernel streams from ring 0 too)
+      VT_TRY(alloc_buf(ctx, knn2, (size_t)ncap * kk * 4));
+      Timer T(st, &S.ms_knn);
+      VT_TRY(launch_knn(ctx, sorted.p, dtype, n, GD, cell_start.get<int32_t>(), SG, nxt, ncap, kk, dist,
+                        knn2.get<int32_t>(), st));
+    }
+    Timer T(st, &S.ms_clip);
+    ClipLaunch c2 = base;
+    c2.cells = nxt;
+    c2.nc = ncap;
+    c2.knn = all_listed ? knn.get<int32_t>() : knn2.get<int32_t>();
+    c2.knn_by_id = all_listed ? 1 : 0;
+    c2.k = kk;
+    c2.capacity = 1;
+    c2.stream = strm ? 1 : 0;
+    return launch_clip(c2, st);
+  };
+  // ---- first pass over all cells
   if (n > 0) {
     if (P.kmodel) {
       VT_TRY(learned_first_pass(ctx, P.kmodel, P.tau, sorted.p, n, grid, cell_start.get<int32_t>(), base,
@@ -588,6 +637,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
         Timer T(st, &S.ms_knn);
         VT_TRY(launch_knn(ctx, sorted.p, dtype, n, GD, cell_start.get<int32_t>(), SG, nullptr, n, k, dist,
                           knn.get<int32_t>(), st));
+        all_listed = true;
       }
       {
         Timer T(st, &S.ms_clip);
@@ -596,11 +646,10 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
         c.nc = n;
         c.knn = fused ? nullptr : knn.get<int32_t>();
         c.k = k;
-        c.stream = stream_last && nretry == 0;
+        c.stream = stream_last && nretry == merged;
+        for (int i = 0; i < merged; ++i) c.level[i] = level[i];
         VT_TRY(launch_clip(c, st));
       }
-      S.pass_k[S.npasses] = k;
-      S.pass_cells[S.npasses] = n;
     }
     VT_TRY(votess_ctx_errors(ctx, stream, &errs));
     if (errs & ERR_DUPLICATE) return fail(VOTESS_EDUPLICATE, "two points coincide exactly");
@@ -608,48 +657,25 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
       k_force_fail<<<(n + 255) / 256, 256, 0, st>>>(status.get<uint8_t>(), n, P.force_fail_every);
       VT_HIP(hipGetLastError());
     }
+    if (merged > 0) VT_TRY(capacity_pass(nullptr, n, k, stream_last && nretry == merged));
     // radius failures retry at 2k; capacity overflows go to the large kernel
     VT_TRY(launch_compact_failed(status.get<uint8_t>(), nullptr, n, cur, ctx->d_counter,
                                  (1u << VOTESS_CELL_RADIUS) | (1u << VOTESS_CELL_CAPACITY), ctx->ws, st));
     VT_HIP(hipMemcpyAsync(&nfail, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
     VT_HIP(hipStreamSynchronize(st));
-    if (!P.kmodel && S.npasses < VOTESS_MAX_PASSES) {
-      VT_TRY(stream_entries(entered));
-      S.pass_streamed[S.npasses] = entered - entered_before;
-      entered_before = entered;
-      S.pass_failed[S.npasses++] = nfail;
+    if (P.kmodel) {
+      unsigned long long v = 0;
+      VT_HIP(hipMemcpyAsync(&v, counters.get<unsigned long long>() + 5, 8, hipMemcpyDeviceToHost, st));
+      VT_HIP(hipStreamSynchronize(st));
+      entered = (int64_t)v;
+    } else {
+      VT_TRY(record_pass(n, merged));
     }
-    if (P.kmodel) VT_TRY(stream_entries(entered_before));
   }
-  // ---- GPU retry ladder: cells whose radius test failed retry at doubled k;
-  // cells that overflowed the fast kernel rerun in the large-capacity kernel
-  auto capacity_pass = [&](const int32_t* ids, int cnt, int kk, bool strm) -> votess_status {
-    int ncap = 0;
-    VT_TRY(launch_compact_failed(status.get<uint8_t>(), ids, cnt, nxt, ctx->d_counter, 1u << VOTESS_CELL_CAPACITY,
-                                 ctx->ws, st));
-    VT_HIP(hipMemcpyAsync(&ncap, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
-    if (ncap == 0) return VOTESS_OK;
-    S.capacity_cells += ncap;
-    Buf knn2;
-    if (kk > 0) {  // (no list in the fused form: the large kernel streams from ring 0 too)
-      VT_TRY(alloc_buf(ctx, knn2, (size_t)ncap * kk * 4));
-      Timer T(st, &S.ms_knn);
-      VT_TRY(launch_knn(ctx, sorted.p, dtype, n, GD, cell_start.get<int32_t>(), SG, nxt, ncap, kk, dist,
-                        knn2.get<int32_t>(), st));
-    }
-    Timer T(st, &S.ms_clip);
-    ClipLaunch c2 = base;
-    c2.cells = nxt;
-    c2.nc = ncap;
-    c2.knn = knn2.get<int32_t>();
-    c2.k = kk;
-    c2.capacity = 1;
-    c2.stream = strm ? 1 : 0;
-    return launch_clip(c2, st);
-  };
-  for (int r = 0; r < nretry && nfail > 0 && P.force_fail_every == 0 && k < kMaxK; ++r) {
+  // ---- GPU retry ladder: cells whose radius test failed retry at doubled k
+  for (int r = merged; r < nretry && nfail > 0 && P.force_fail_every == 0 && k < kMaxK; ++r) {
     k = std::min(2 * k, kMaxK);
+    all_listed = false;
     VT_TRY(alloc_buf(ctx, knn, (size_t)nfail * k * 4));
     {
       Timer T(st, &S.ms_knn);
@@ -672,14 +698,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
                                  (1u << VOTESS_CELL_RADIUS) | (1u << VOTESS_CELL_CAPACITY), ctx->ws, st));
     VT_HIP(hipMemcpyAsync(&nfail, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
     VT_HIP(hipStreamSynchronize(st));
-    if (S.npasses < VOTESS_MAX_PASSES) {
-      VT_TRY(stream_entries(entered));
-      S.pass_k[S.npasses] = k;
-      S.pass_cells[S.npasses] = cells_in;
-      S.pass_streamed[S.npasses] = entered - entered_before;
-      entered_before = entered;
-      S.pass_failed[S.npasses++] = nfail;
-    }
+    VT_TRY(record_pass(cells_in, 0));
     std::swap(cur, nxt);
   }
   // capacity overflows that no retry revisited (no retries left, or k at its maximum)

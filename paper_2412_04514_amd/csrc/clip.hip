@@ -75,6 +75,7 @@ struct ClipArgs {
   double* centroid;  // [rows, 3] (nullable)
   double* r2out;     // [rows] (nullable): R^2 of the certified cell (an upper bound on the float path)
   unsigned long long* counters;
+  int level[kLevels];
   // passing cells on from the list kernel to a second launch (see k_clip):
   int rest;  // 1: only the cells that the list kernel left
   int mark;  // statuses of cells that the list kernel leaves, as a bit mask
@@ -530,6 +531,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       return sqrt(X * X + Y * Y + Z * Z) * (1.0 + 1e-5);
     }
   };
+  bool streamed = false;  // the cell has entered the stream phase
   int kneed = 0;
   int nrecheck = 0;
   __syncthreads();
@@ -999,7 +1001,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     const int ik0 = (have && st == VOTESS_CELL_RADIUS && !nolist) ? klist[a.k - 1] : -1;
     const bool strm = have && st == VOTESS_CELL_RADIUS && (nolist || ik0 >= 0);  // a full list that did not certify
     if (strm) st = ST_RUN;
-    if (strm && j == 0 && a.counters) atomicAdd(&a.counters[5], 1ull);
+    streamed = strm;
     const GridDev& Gd = a.grid;
     const int cx = axis_cell(p64x, Gd.lo0, Gd.ih0, Gd.g0);
     const int cy = axis_cell(p64y, Gd.lo1, Gd.ih1, Gd.g1);
@@ -1480,7 +1482,6 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       }
       if (apply_plane(run2, nx, ny, nz, c, d2, nb2)) reach_ok = okD = flower_ok = false;
     }
-    if (strm && st == VOTESS_CELL_CERTIFIED && j == 0 && a.counters) atomicAdd(&a.counters[4], 1ull);
   }
 
   // ---- outputs
@@ -1696,14 +1697,8 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       }
     }
   }
-  if (RECHECK) {
-    int rc = nrecheck;
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) rc += red_step(rc, o);
-    nrecheck = rc;
-  }
+  int fin = st;
   if (have && j == 0) {
-    int fin = st;
     if (fin == VOTESS_CELL_CERTIFIED && (ntot > a.max_nbr || (a.max_vert > 0 && vtot > a.max_vert)))
       fin = VOTESS_CELL_CAPACITY;
     a.status[row] = (uint8_t)fin | (a.rest || ((a.mark >> fin) & 1) ? kLeft : (uint8_t)0);
@@ -1718,12 +1713,35 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     if (a.kneeded) a.kneeded[row] = kneed;
     if (a.r2out) a.r2out[row] = fin == VOTESS_CELL_CERTIFIED ? (RECHECK ? (double)R2up : (double)R2) : 0.0;
     if (a.vcount) a.vcount[row] = fin == VOTESS_CELL_CERTIFIED ? vtot : 0;
-    if (a.counters) {
-      if (nrecheck) atomicAdd(&a.counters[0], (unsigned long long)nrecheck);
-      if (fin == VOTESS_CELL_UNRESOLVED) atomicAdd(&a.counters[1], 1ull);
-      if (fin == VOTESS_CELL_CAPACITY) atomicAdd(&a.counters[2], 1ull);
-      if (refine && fin == VOTESS_CELL_CERTIFIED) atomicAdd(&a.counters[3], 1ull);
+  }
+  // counters: one addition per wave (all of them meet at one address)
+  if (a.counters) {
+    const bool lead = have && j == 0;
+    auto add = [&](int c, bool v) {
+      const unsigned long long b = __ballot(lead && v);
+      if (lane == 0 && b) atomicAdd(&a.counters[c], (unsigned long long)__popcll(b));
+    };
+    add(1, fin == VOTESS_CELL_UNRESOLVED);
+    add(2, fin == VOTESS_CELL_CAPACITY);
+    add(5, streamed);
+    add(4, streamed && st == VOTESS_CELL_CERTIFIED);
+    if constexpr (RECHECK) {
+      add(3, refine && fin == VOTESS_CELL_CERTIFIED);
+      int rc = nrecheck;
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) rc += red_step(rc, o);
+      rc += __shfl_xor(rc, 16, 64);
+      rc += __shfl_xor(rc, 32, 64);
+      if (lane == 0 && rc) atomicAdd(&a.counters[0], (unsigned long long)rc);
     }
+    // cells that a list of level[i] does not certify, counted by the launch
+    // that has the last word on the cell's list
+    const bool mine = !resume && !(fin == VOTESS_CELL_CAPACITY && ((a.mark >> fin) & 1));
+#pragma unroll
+    for (int i = 0; i < kLevels; ++i)
+      if (a.level[i])
+        add(kLevelCounter + i, mine && (fin == VOTESS_CELL_CERTIFIED ? kneed > a.level[i]
+                                                                     : fin != VOTESS_CELL_UNRESOLVED));
   }
 }
 
@@ -1858,6 +1876,7 @@ votess_status launch_clip(const ClipLaunch& a, hipStream_t st) {
   c.centroid = a.centroid;
   c.r2out = a.r2out;
   c.counters = a.counters;
+  for (int i = 0; i < kLevels; ++i) c.level[i] = a.level[i];
   c.stream = a.stream;
   c.cell_start = a.cell_start;
   c.grid = a.grid;

@@ -110,6 +110,9 @@ votess_status launch_knn(votess_ctx* ctx, const void* sorted, votess_dtype dt, i
                          votess_dtype dist, int32_t* knn, hipStream_t st);
 
 // clipping (clip.hip)
+constexpr int kLevels = 3;        // shorter lists whose outcome a clip counts
+constexpr int kLevelCounter = 6;  // their first counter
+constexpr int kClipCounters = kLevelCounter + kLevels;
 struct ClipLaunch {
   const void* sorted;
   votess_dtype dtype;
@@ -136,8 +139,10 @@ struct ClipLaunch {
   double* area = nullptr;        // [rows, max_nbr] face areas next to nbr (nullable)
   double* centroid = nullptr;    // [rows, 3] cell centroids (nullable)
   double* r2out = nullptr;       // [rows] R^2 of each certified cell (nullable; an upper bound on the float path)
-  unsigned long long* counters;  // [8]: rechecks, unresolved, capacity, refined, streamed (certified by the
-                                 // stream phase), stream entries -- nullable
+  unsigned long long* counters;  // [kClipCounters]: rechecks, unresolved, capacity, refined, streamed (certified
+                                 // by the stream phase), stream entries, cells not certified by the first
+                                 // level[i] entries of their list -- nullable
+  int level[kLevels] = {0, 0, 0};  // (0: not counted)
   int own_rows = 1;              // 0: `cells` may name a cell twice with out_by_id
   int stream = 0;                // 1: uncertified cells continue by grid rings
   const int32_t* cell_start = nullptr;

@@ -252,8 +252,8 @@ votess_status tessellate_periodic(votess_ctx* ctx, const void* pts, votess_dtype
     VT_TRY(nbr.alloc(ctx, (size_t)nc * kPerNbr * 4));
     VT_TRY(cvol.alloc(ctx, (size_t)nc * 8));
     VT_TRY(r2.alloc(ctx, (size_t)nc * 8));
-    VT_TRY(counters.alloc(ctx, 64));
-    VT_HIP(hipMemsetAsync(counters.p, 0, 64, st));
+    VT_TRY(counters.alloc(ctx, 8 * kClipCounters));
+    VT_HIP(hipMemsetAsync(counters.p, 0, 8 * kClipCounters, st));
     if (wantf) {
       VT_TRY(carea.alloc(ctx, (size_t)nc * kPerNbr * 8));
       VT_TRY(ccen.alloc(ctx, (size_t)nc * 3 * 8));
