@@ -48,7 +48,19 @@
 namespace votess {
 namespace {
 
-constexpr unsigned kEmpty = 0xFFFFFFFFu;
+// A triangle's three plane slots in one word: 5 bits each in 16 bits where 32
+// planes are enough, else 8 bits each.
+template <int PMAX>
+struct TriCode {
+  using T = typename std::conditional<(PMAX <= 32), unsigned short, unsigned>::type;
+  static constexpr int kShift = PMAX <= 32 ? 5 : 8;
+  static constexpr unsigned kMask = (1u << kShift) - 1u;
+  static constexpr unsigned kEmpty = PMAX <= 32 ? 0xFFFFu : 0xFFFFFFFFu;
+  __device__ static unsigned make(unsigned a, unsigned b, unsigned c) { return a | (b << kShift) | (c << 2 * kShift); }
+  __device__ static int a(unsigned u) { return (int)(u & kMask); }
+  __device__ static int b(unsigned u) { return (int)((u >> kShift) & kMask); }
+  __device__ static int c(unsigned u) { return (int)((u >> 2 * kShift) & kMask); }
+};
 constexpr int ST_RUN = -1;
 
 struct ClipArgs {
@@ -180,26 +192,38 @@ __device__ __forceinline__ V3<double> solve3_refined(const V3<double>& na, doubl
 
 // Float vertex of three planes with a first-order forward error bound (max
 // norm): rounding of the cross products, the sums, the division and of the
-// plane data (normals may be off by an ulp, offsets by two).
-__device__ __forceinline__ V3<float> solve3_err(const V3<float>& na, float ca, const V3<float>& nb, float cb,
-                                                const V3<float>& nc, float cc, float& err) {
-  const V3<float> bc = cross(nb, nc), ca_ = cross(nc, na), ab = cross(na, nb);
-  auto perm = [](const V3<float>& a, const V3<float>& b) {
-    return V3<float>{fabsf(a.y * b.z) + fabsf(a.z * b.y), fabsf(a.z * b.x) + fabsf(a.x * b.z),
-                     fabsf(a.x * b.y) + fabsf(a.y * b.x)};
-  };
-  const V3<float> pbc = perm(nb, nc), pca = perm(nc, na), pab = perm(na, nb);
-  const float det = dot(na, bc);
+// plane data (normals may be off by an ulp, offsets by two).  Which products
+// are fused is written out rather than left to the compiler, whose choice
+// moves with the code around it (it fuses a cross product's first product;
+// the order of the sums' first two terms is fixed, if not the same for z):
+// the kernels of a clip and the state passed between them must agree on every
+// bit of a vertex, and so must one build with the next.
+__device__ __forceinline__ V3<float> solve3_err(const V3<float>& a, float ca, const V3<float>& b, float cb,
+                                                const V3<float>& c, float cc, float& err) {
+#pragma clang fp contract(off)
+  auto fma = [](float x, float y, float z) { return __builtin_fmaf(x, y, z); };
+  const float b1 = b.z * c.y, b2 = b.x * c.z, b3 = b.y * c.x;
+  const V3<float> bc = {fma(b.y, c.z, -b1), fma(b.z, c.x, -b2), fma(b.x, c.y, -b3)};
+  const float c1 = c.z * a.y, c2 = c.x * a.z, c3 = c.y * a.x;
+  const V3<float> cx = {fma(c.y, a.z, -c1), fma(c.z, a.x, -c2), fma(c.x, a.y, -c3)};
+  const float a1 = a.z * b.y, a2 = a.x * b.z, a3 = a.y * b.x;
+  const V3<float> ab = {fma(a.y, b.z, -a1), fma(a.z, b.x, -a2), fma(a.x, b.y, -a3)};
+  const V3<float> pbc = {fabsf(b.y * c.z) + fabsf(b1), fabsf(b.z * c.x) + fabsf(b2), fabsf(b.x * c.y) + fabsf(b3)};
+  const V3<float> pca = {fabsf(c.y * a.z) + fabsf(c1), fabsf(c.z * a.x) + fabsf(c2), fabsf(c.x * a.y) + fabsf(c3)};
+  const V3<float> pab = {fabsf(a.y * b.z) + fabsf(a1), fabsf(a.z * b.x) + fabsf(a2), fabsf(a.x * b.y) + fabsf(a3)};
+  const float det = fma(a.z, bc.z, fma(a.y, bc.y, a.x * bc.x));
   const float inv = 1.0f / det;
-  const V3<float> v = {(ca * bc.x + cb * ca_.x + cc * ab.x) * inv, (ca * bc.y + cb * ca_.y + cc * ab.y) * inv,
-                       (ca * bc.z + cb * ca_.z + cc * ab.z) * inv};
+  const V3<float> v = {fma(cc, ab.x, fma(cb, cx.x, ca * bc.x)) * inv, fma(cc, ab.y, fma(cb, cx.y, ca * bc.y)) * inv,
+                       fma(cc, ab.z, fma(ca, bc.z, cb * cx.z)) * inv};
   const float u8 = 8.0f * (0.5f * FLT_EPSILON);
-  const float dD = u8 * (fabsf(na.x) * pbc.x + fabsf(na.y) * pbc.y + fabsf(na.z) * pbc.z);
-  const float aa = fabsf(ca), ab_ = fabsf(cb), ac = fabsf(cc);
+  const float dD = u8 * fma(fabsf(a.z), pbc.z, fma(fabsf(a.y), pbc.y, fabsf(a.x) * pbc.x));
+  const float ka = fabsf(ca), kb = fabsf(cb), kc = fabsf(cc);
   const float ai = fabsf(inv);
-  const float ex = (u8 * (aa * pbc.x + ab_ * pca.x + ac * pab.x) + fabsf(v.x) * dD) * ai + FLT_EPSILON * fabsf(v.x);
-  const float ey = (u8 * (aa * pbc.y + ab_ * pca.y + ac * pab.y) + fabsf(v.y) * dD) * ai + FLT_EPSILON * fabsf(v.y);
-  const float ez = (u8 * (aa * pbc.z + ab_ * pca.z + ac * pab.z) + fabsf(v.z) * dD) * ai + FLT_EPSILON * fabsf(v.z);
+  const float sx = fma(kc, pab.x, fma(kb, pca.x, ka * pbc.x)), sy = fma(kc, pab.y, fma(kb, pca.y, ka * pbc.y)),
+              sz = fma(kc, pab.z, fma(ka, pbc.z, kb * pca.z));
+  const float ex = fma(FLT_EPSILON, fabsf(v.x), fma(u8, sx, fabsf(v.x) * dD) * ai);
+  const float ey = fma(FLT_EPSILON, fabsf(v.y), fma(u8, sy, fabsf(v.y) * dD) * ai);
+  const float ez = fma(FLT_EPSILON, fabsf(v.z), fma(u8, sz, fabsf(v.z) * dD) * ai);
   err = fmaxf(ex, fmaxf(ey, ez));
   return v;
 }
@@ -286,14 +310,15 @@ __device__ __forceinline__ void plane64_of(int id, const Rec4* rec, double px, d
 // from the id), the alive mask, the number of triangles, and the triangles as
 // three 5-bit plane slots in 16 bits, in the order (a, b, last applied), from
 // which the stream kernel solves the same vertices again, bit for bit.
-constexpr uint8_t kLeft = 0x80;  // in a status: the list kernel left the cell to the second launch
+// Mark in a status: the list kernel left the cell to the second launch.
+constexpr uint8_t kLeft = 0x80;
 constexpr int kListLanes = 8, kListVert = 48;  // lanes per cell and vertex slots of the list kernel
 constexpr int kStateAlive = 32, kStateCount = 33, kStateTri = 34, kStateWords = kStateTri + kListVert / 2;
 
 // blocks that a launch over nc cells needs, `per` cells each (with `rest`:
 // 64 / per for each 64 cells)
 __host__ __device__ __forceinline__ int clip_blocks(int nc, int per, int rest) {
-  return rest ? (int)(((long long)nc + 63) / 64 * (64 / per)) : (int)(((long long)nc + per - 1) / per);
+  return (int)(rest ? ((long long)nc + 63) / 64 * (64 / per) : ((long long)nc + per - 1) / per);
 }
 
 // Clips 64 / L cells, one per group of L lanes: cell t_idx of the launch (no
@@ -309,6 +334,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   constexpr unsigned long long LOWL = (L == 64) ? ~0ull : ((1ull << L) - 1);
   constexpr M PFULL = (PMAX == 8 * (int)sizeof(M)) ? ~M(0) : ((M(1) << PMAX) - 1);
   static_assert(S <= 32, "slot mask is 32 bits");
+  static_assert(TMAX % L == 0 && TMAX % 4 == 0, "the slots are taken L at a time, or 4");
   static_assert(L <= 32, "a group's ballot is taken from one word");
   static_assert(RECHECK == (sizeof(R) == 4), "the float clip rechecks, the double one does not");
   static_assert(TMAX <= 256, "vertex slots are numbered in one byte");
@@ -319,12 +345,18 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   constexpr int V4 = RECHECK ? G * TP : 1, VD = RECHECK ? 1 : G * TP;
   __shared__ float4 vtx[V4];
   __shared__ R vx[VD], vy[VD], vz[VD];
-  __shared__ unsigned tri[G * TP];
-  // planes: float ones as (n, c), one 16-byte read
-  constexpr int P4 = RECHECK ? G * PMAX : 1, PD = RECHECK ? 1 : G * PMAX;
+  using TC = TriCode<PMAX>;
+  constexpr unsigned kEmpty = TC::kEmpty;
+  __shared__ typename TC::T tri[G * TP];
+  // planes: a bisector's normal and the id of its point, float ones as 16
+  // bytes; with float points a double clip keeps the point itself (exact, and
+  // half the size).  The offset follows from the normal.  Of a wall only the
+  // id is read.
+  constexpr bool kPoint = sizeof(P) == 4 && sizeof(R) == 8;
+  constexpr int P4 = sizeof(P) == 4 ? G * PMAX : 1, PD = sizeof(P) == 4 ? 1 : G * PMAX;
   __shared__ float4 pn4[P4];
-  __shared__ R pnx[PD], pny[PD], pnz[PD], pnc[PD];
-  __shared__ int pid[G * PMAX];
+  __shared__ double pnx[PD], pny[PD], pnz[PD];
+  __shared__ int pidd[PD];
   __shared__ M omask[G * PMAX];
   __shared__ unsigned short snew[G * (PMAX + 1)];
   // free vertex slots below H, as a stack; a cut pushes the slots it removes,
@@ -336,9 +368,8 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   constexpr int RVN = STREAM ? G * kReach : 1;
   __shared__ float4 reachv[RVN];
   __shared__ unsigned char relD[RVN];
-  // stream phase: geometry of the dense cell being scanned (cell corner,
-  // sub-grid origin and sub-cell widths), per group
-  constexpr int DG = STREAM ? G * 9 : 1;
+  // stream phase: sub-cell widths of the dense cell being scanned, per group
+  constexpr int DG = STREAM ? G * 3 : 1;
   __shared__ double dgeo[DG];
   // stream phase: the flower box in coordinates, per group (read only when a
   // dense cell is entered, so it need not occupy registers)
@@ -396,6 +427,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     for (int o = 1; o < L; o <<= 1) v += red_step(v, o);
     return v;
   };
+  // exclusive prefix sum over the group's lanes, and the total
   auto gexcl = [&](int v, int& tot) -> int {
     int x = v;
 #pragma unroll
@@ -403,21 +435,28 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       const int y = L <= 16 ? (int)up_word((unsigned)x, o) : __shfl_up(x, o, L);
       if (j >= o) x += y;
     }
-    tot = __shfl(x, L - 1, L);
+    tot = v;
+#pragma unroll
+    for (int o = 1; o < L; o <<= 1) tot += red_step(tot, o);
     return x - v;
   };
 
+  // the id of the plane in slot f: a point's, or -1 - wall
+  auto pid = [&](int f) -> int {
+    if constexpr (sizeof(P) == 4) return __float_as_int(pn4[pb + f].w);
+    else return pidd[pb + f];
+  };
   // FP64 plane of slot f, from the exact inputs (used by the recheck).
   const double blo0 = a.lo0, blo1 = a.lo1, blo2 = a.lo2, bhi0 = a.hi0, bhi1 = a.hi1, bhi2 = a.hi2;
   auto plane64 = [&](int f, V3<double>& n, double& c) {
-    plane64_of(pid[pb + f], rec, p64x, p64y, p64z, blo0, blo1, blo2, bhi0, bhi1, bhi2, n, c);
+    plane64_of(pid(f), rec, p64x, p64y, p64z, blo0, blo1, blo2, bhi0, bhi1, bhi2, n, c);
   };
   auto vertex64 = [&](unsigned u) -> V3<double> {
     V3<double> na, nb, nc;
     double ca, cb, cc;
-    plane64(u & 0xFF, na, ca);
-    plane64((u >> 8) & 0xFF, nb, cb);
-    plane64((u >> 16) & 0xFF, nc, cc);
+    plane64(TC::a(u), na, ca);
+    plane64(TC::b(u), nb, cb);
+    plane64(TC::c(u), nc, cc);
     return solve3<double>(na, ca, nb, cb, nc, cc);
   };
 
@@ -449,30 +488,42 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     }
   };
   auto pget = [&](int f, V3<R>& n, R& c) {
-    if constexpr (RECHECK) {
+    int id;
+    if constexpr (sizeof(P) == 4) {
       const float4 q = pn4[pb + f];
-      n = {q.x, q.y, q.z};
-      c = q.w;
+      id = __float_as_int(q.w);
+      if constexpr (kPoint) n = {(R)q.x - px, (R)q.y - py, (R)q.z - pz};
+      else n = {(R)q.x, (R)q.y, (R)q.z};
     } else {
-      n = {pnx[pb + f], pny[pb + f], pnz[pb + f]};
-      c = pnc[pb + f];
+      n = {(R)pnx[pb + f], (R)pny[pb + f], (R)pnz[pb + f]};
+      id = pidd[pb + f];
+    }
+    c = R(0.5) * dist2_nc(n.x, n.y, n.z);
+    if (id < 0) {
+      V3<double> w;
+      double cw;
+      plane64_of(id, rec, p64x, p64y, p64z, blo0, blo1, blo2, bhi0, bhi1, bhi2, w, cw);
+      n = {(R)w.x, (R)w.y, (R)w.z};
+      c = (R)cw;
     }
   };
-  auto pput = [&](int f, R nx, R ny, R nz, R c, int id) {
-    if constexpr (RECHECK) {
-      pn4[pb + f] = make_float4(nx, ny, nz, c);
+  // the bisector with point id, whose normal is (nx, ny, nz) and, where points
+  // are kept, its position (qx, qy, qz)
+  auto pput = [&](int f, R nx, R ny, R nz, float qx, float qy, float qz, int id) {
+    if constexpr (sizeof(P) == 4) {
+      if constexpr (kPoint) pn4[pb + f] = make_float4(qx, qy, qz, __int_as_float(id));
+      else pn4[pb + f] = make_float4((float)nx, (float)ny, (float)nz, __int_as_float(id));
     } else {
       pnx[pb + f] = nx;
       pny[pb + f] = ny;
       pnz[pb + f] = nz;
-      pnc[pb + f] = c;
+      pidd[pb + f] = id;
     }
-    pid[pb + f] = id;
   };
 
   // ---- initial cell: the box, in seed-relative coordinates
   for (int t = j; t < TMAX; t += L) {
-    tri[vb + t] = kEmpty;
+    tri[vb + t] = (typename TC::T)kEmpty;
     vput(t, R(0), R(0), R(0), 0.0f);
   }
   for (int f = j; f < PMAX; f += L) omask[pb + f] = 0;
@@ -485,19 +536,11 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     const unsigned X = bx, Y = 2 + by, Z = 4 + bz;
     // (X, Y, Z) is counter-clockwise seen from outside iff an odd number of
     // the three coordinates are on the high side
-    tri[vb + v] = ((bx + by + bz) & 1) ? (X | (Y << 8) | (Z << 16)) : (X | (Z << 8) | (Y << 16));
+    tri[vb + v] = (typename TC::T)(((bx + by + bz) & 1) ? TC::make(X, Y, Z) : TC::make(X, Z, Y));
     vput(v, X0, Y0, Z0,
          RECHECK ? FLT_EPSILON * (float)fmax(fabs((double)X0), fmax(fabs((double)Y0), fabs((double)Z0))) : 0.0f);
   }
-  // box wall w (x-, x+, y-, y+, z-, z+) into plane slot f
-  auto wall = [&](int f, int w) {
-    const int ax = w >> 1;
-    const bool hi = w & 1;
-    const R sgn = hi ? R(1) : R(-1);
-    pput(f, ax == 0 ? sgn : R(0), ax == 1 ? sgn : R(0), ax == 2 ? sgn : R(0),
-         ax == 0 ? (hi ? hx : -lx) : (ax == 1 ? (hi ? hy : -ly) : (hi ? hz : -lz)), -(w + 1));
-  };
-  for (int f = j; f < 6; f += L) wall(f, f);
+  for (int f = j; f < 6; f += L) pput(f, R(0), R(0), R(0), 0.0f, 0.0f, 0.0f, -(f + 1));
   int st = have ? ST_RUN : VOTESS_CELL_CERTIFIED;
   int H = 8;   // slots in use lie below H
   int nfr = 0;  // free slots below H (fstk)
@@ -570,7 +613,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       if (!(ev <= 16.0 * a.eps * vm)) {
         // ill-conditioned float vertex: solve it in double from the exact
         // planes and keep the rounded value (bound: one ulp)
-        const V3<double> w = vertex64((unsigned)A | ((unsigned)B << 8) | ((unsigned)C << 16));
+        const V3<double> w = vertex64(TC::make(A, B, C));
         v = {(float)w.x, (float)w.y, (float)w.z};
         ev = FLT_EPSILON * (float)fmax(fabs(w.x), fmax(fabs(w.y), fabs(w.z)));
         redone = true;
@@ -588,13 +631,8 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       for (int f = j; f < 32; f += L) {
         const int id = w[f];
         if (!((alive >> f) & 1)) continue;
-        if (id >= 0) {
-          const Rec4 q = rec[id];
-          const R nx = (R)q.x - px, ny = (R)q.y - py, nz = (R)q.z - pz;
-          pput(f, nx, ny, nz, R(0.5) * dist2_nc(nx, ny, nz), id);
-        } else {
-          wall(f, -id - 1);
-        }
+        const Rec4 q = rec[id >= 0 ? id : sid];
+        pput(f, (R)q.x - px, (R)q.y - py, (R)q.z - pz, (float)q.x, (float)q.y, (float)q.z, id);
       }
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       const unsigned short* tr = (const unsigned short*)(w + kStateTri);
@@ -602,21 +640,21 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       for (int t = j; t < (H + L - 1) / L * L; t += L) {
         if (t < H) {
           const unsigned x = tr[t];
-          const int A = x & 31, B = (x >> 5) & 31, C = (x >> 10) & 31;
+          const int A = TriCode<32>::a(x), B = TriCode<32>::b(x), C = TriCode<32>::c(x);
           V3<R> n, v;
           R c;
           float e;
           bool redone;
           pget(C, n, c);
           v = vertex(A, B, C, n.x, n.y, n.z, c, e, redone);
-          if (pid[pb + A] < 0 && pid[pb + B] < 0 && pid[pb + C] < 0) {
+          if (pid(A) < 0 && pid(B) < 0 && pid(C) < 0) {
             e = FLT_EPSILON * (float)fmax(fabs((double)v.x), fmax(fabs((double)v.y), fabs((double)v.z)));  // a box corner
           }
           vput(t, v.x, v.y, v.z, e);
-          tri[vb + t] = (unsigned)A | ((unsigned)B << 8) | ((unsigned)C << 16);
+          tri[vb + t] = (typename TC::T)TC::make(A, B, C);
           r2 = fmax(r2, v.x * v.x + v.y * v.y + v.z * v.z);
         } else if (t < TMAX) {
-          tri[vb + t] = kEmpty;
+          tri[vb + t] = (typename TC::T)kEmpty;
           vput(t, R(0), R(0), R(0), 0.0f);
         }
       }
@@ -734,19 +772,21 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         ps = (sizeof(M) == 4) ? (__ffs((unsigned)fr) - 1) : (__ffsll((unsigned long long)fr) - 1);
       }
     }
-    if (doit && j == 0) pput(ps, nx, ny, nz, c, nb);
+    if (doit && j == 0) {
+      if constexpr (kPoint) {
+        const Rec4 q = rec[nb];
+        pput(ps, nx, ny, nz, (float)q.x, (float)q.y, (float)q.z, nb);
+      } else {
+        pput(ps, nx, ny, nz, 0.0f, 0.0f, 0.0f, nb);
+      }
+    }
     if (!doit) out = 0;
     // removed slots onto the free stack, which then lists them for the steps
     // below, one removed triangle per lane
     int rem = 0;
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const bool o = (out >> s) & 1u;
-      if (__any(o)) {
-        const unsigned gbits = gballot(o);
-        if (o) fstk[vb + nfr + rem + __popc(gbits & below)] = (unsigned char)(j + L * s);
-        rem += __popc(gbits);
-      }
+    {
+      int w = nfr + gexcl(__popc(out), rem);
+      for (unsigned left = out; left; left &= left - 1u) fstk[vb + w++] = (unsigned char)(j + L * (__ffs(left) - 1));
     }
     const bool many = __any(rem > L);
     __syncthreads();
@@ -755,7 +795,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     for (int r0 = 0; __any(r0 < rem); r0 += L) {
       if (r0 + j < rem) {
         u = tri[vb + fstk[vb + nfr + r0 + j]];
-        const int A = u & 0xFF, B = (u >> 8) & 0xFF, C = (u >> 16) & 0xFF;
+        const int A = TC::a(u), B = TC::b(u), C = TC::c(u);
         atomicOr(&omask[pb + A], bitm<M>(B));
         atomicOr(&omask[pb + B], bitm<M>(C));
         atomicOr(&omask[pb + C], bitm<M>(A));
@@ -774,13 +814,13 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       if (on) {
         const int t = fstk[vb + nfr + r0 + j];
         if (many) u = tri[vb + t];
-        A = u & 0xFF, B = (u >> 8) & 0xFF, C = (u >> 16) & 0xFF;
+        A = TC::a(u), B = TC::b(u), C = TC::c(u);
         e0 = !((omask[pb + B] >> A) & 1);
         e1 = !((omask[pb + C] >> B) & 1);
         e2 = !((omask[pb + A] >> C) & 1);
         pr_ |= bitm<M>(A) | bitm<M>(B) | bitm<M>(C);
         pk |= (e0 ? bitm<M>(A) : M(0)) | (e1 ? bitm<M>(B) : M(0)) | (e2 ? bitm<M>(C) : M(0));
-        tri[vb + t] = kEmpty;
+        tri[vb + t] = (typename TC::T)kEmpty;
         vput(t, R(0), R(0), R(0), 0.0f);
       }
       // edges are listed by lane; what is no edge, and (in an inconsistent
@@ -814,7 +854,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       const V3<R> v = vertex(A, B, ps, nx, ny, nz, c, ev, redone);
       if (redone) ++nrecheck;
       vput(t, v.x, v.y, v.z, ev);
-      tri[vb + t] = (unsigned)A | ((unsigned)B << 8) | ((unsigned)ps << 16);
+      tri[vb + t] = (typename TC::T)TC::make(A, B, ps);
     }
     __syncthreads();
     // R^2 over all slots (an empty one adds zero)
@@ -978,7 +1018,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       int* w = a.nbr + (size_t)row * a.max_nbr;
       unsigned short* tr = (unsigned short*)(w + kStateTri);
       if (sv)
-        for (int f = j; f < 32; f += L) w[f] = pid[pb + f];
+        for (int f = j; f < 32; f += L) w[f] = pid(f);
       int cnt = 0;
 #pragma unroll
       for (int s = 0; s < S; ++s) {
@@ -986,8 +1026,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         const bool on = sv && u != kEmpty;
         const unsigned gbits = gballot(on);
         if (on)
-          tr[cnt + __popc(gbits & below)] =
-              (unsigned short)((u & 31) | (((u >> 8) & 31) << 5) | (((u >> 16) & 31) << 10));
+          tr[cnt + __popc(gbits & below)] = (unsigned short)u;
         cnt += __popc(gbits);
       }
       if (sv && j == 0) {
@@ -1200,13 +1239,15 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     // not inside the list's ball, and (while the dense cell's vertex list is
     // valid) meeting the ball of a listed vertex?  (one sub-row per lane)
     auto sub_row_relevant = [&](int sy, int sz) -> bool {
-      const double* dgp = dgeo + g * 9;
-      const double X0 = dsx0 == 0 ? dgp[0] : dgp[3] + dsx0 * dgp[6];
-      const double X1 = dsx1 == dm0 - 1 ? dgp[0] + Gd.h0 : dgp[3] + (dsx1 + 1) * dgp[6];
-      const double Y0 = sy == 0 ? dgp[1] : dgp[4] + sy * dgp[7];
-      const double Y1 = sy == dm1 - 1 ? dgp[1] + Gd.h1 : dgp[4] + (sy + 1) * dgp[7];
-      const double Z0 = sz == 0 ? dgp[2] : dgp[5] + sz * dgp[8];
-      const double Z1 = sz == dm2 - 1 ? dgp[2] + Gd.h2 : dgp[5] + (sz + 1) * dgp[8];
+      const double* dgp = dgeo + g * 3;
+      const SubCell sc = sub_cell(a.sub.start + dsto);
+      const double cxl = Gd.lo0 + (rx - 1) * Gd.h0, cyl = Gd.lo1 + yy * Gd.h1, czl = Gd.lo2 + zz * Gd.h2;
+      const double X0 = dsx0 == 0 ? cxl : sc.lo0 + dsx0 * dgp[0];
+      const double X1 = dsx1 == dm0 - 1 ? cxl + Gd.h0 : sc.lo0 + (dsx1 + 1) * dgp[0];
+      const double Y0 = sy == 0 ? cyl : sc.lo1 + sy * dgp[1];
+      const double Y1 = sy == dm1 - 1 ? cyl + Gd.h1 : sc.lo1 + (sy + 1) * dgp[1];
+      const double Z0 = sz == 0 ? czl : sc.lo2 + sz * dgp[2];
+      const double Z1 = sz == dm2 - 1 ? czl + Gd.h2 : sc.lo2 + (sz + 1) * dgp[2];
       const double ax = X0 - p64x - gmarg, bx = X1 - p64x + gmarg, ay = Y0 - p64y - gmarg, by = Y1 - p64y + gmarg,
                    az = Z0 - p64z - gmarg, bz = Z1 - p64z + gmarg;
       if (in_list_ball(ax, bx, ay, by, az, bz)) return false;
@@ -1343,10 +1384,8 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
               hit = nD > 0 || reach_all;
             }
             if (j == 0) {
-              double* dgp = dgeo + g * 9;
-              dgp[0] = cxl; dgp[1] = cyl; dgp[2] = czl;
-              dgp[3] = sc.lo0; dgp[4] = sc.lo1; dgp[5] = sc.lo2;
-              dgp[6] = w0; dgp[7] = w1; dgp[8] = w2;
+              double* dgp = dgeo + g * 3;
+              dgp[0] = w0; dgp[1] = w1; dgp[2] = w2;
             }
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             dm = hit ? 1 : 0;
@@ -1529,12 +1568,12 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   // planes with the vertex solved and refined in double
   auto corner_geom = [&](unsigned u, int t, bool exact, V3<double>& na, double& ca, V3<double>& nb_, double& cb,
                          V3<double>& nc, double& cc, V3<double>& v, bool refined = false) {
-    const int A = u & 0xFF, B = (u >> 8) & 0xFF, C = (u >> 16) & 0xFF;
+    const int A = TC::a(u), B = TC::b(u), C = TC::c(u);
     if (exact) {
       plane64(A, na, ca);
       plane64(B, nb_, cb);
       plane64(C, nc, cc);
-      v = refined ? solve3_refined(na, ca, pid[pb + A] >= 0, nb_, cb, pid[pb + B] >= 0, nc, cc, pid[pb + C] >= 0)
+      v = refined ? solve3_refined(na, ca, pid(A) >= 0, nb_, cb, pid(B) >= 0, nc, cc, pid(C) >= 0)
                   : solve3<double>(na, ca, nb_, cb, nc, cc);
     } else {
       V3<R> ra, rb, rc;
@@ -1552,8 +1591,8 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         // bisector offsets are taken exactly only where the cached plane holds
         // the exact normal (double planes)
         constexpr bool kExactN = sizeof(R) == 8;
-        v = solve3_refined(na, ca, kExactN && pid[pb + A] >= 0, nb_, cb, kExactN && pid[pb + B] >= 0, nc, cc,
-                           kExactN && pid[pb + C] >= 0);
+        v = solve3_refined(na, ca, kExactN && pid(A) >= 0, nb_, cb, kExactN && pid(B) >= 0, nc, cc,
+                           kExactN && pid(C) >= 0);
       } else {
         const V3<R> w = vget(t);
         v = {(double)w.x, (double)w.y, (double)w.z};
@@ -1658,7 +1697,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     for (int t = 0; t < H; ++t) {
       const unsigned u = tri[vb + t];
       if (u == kEmpty) continue;
-      const int A = u & 0xFF, B = (u >> 8) & 0xFF, C = (u >> 16) & 0xFF;
+      const int A = TC::a(u), B = TC::b(u), C = TC::c(u);
       const bool oa = A % L == j, ob = B % L == j, oc = C % L == j;
       if (!(oa || ob || oc)) continue;
       V3<double> na, nb_, nc, v;
@@ -1680,16 +1719,16 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   }
   // neighbours: alive bisector planes
   int nnb = 0;
-  for (int f = j; f < PMAX; f += L) nnb += cert && ((alive >> f) & 1) && pid[pb + f] >= 0;
+  for (int f = j; f < PMAX; f += L) nnb += cert && ((alive >> f) & 1) && pid(f) >= 0;
   int ntot;
   int noff = gexcl(nnb, ntot);
   if (cert) {
 #pragma unroll
     for (int q = 0; q < FO; ++q) {
       const int f = j + q * L;
-      if (((alive >> f) & 1) && pid[pb + f] >= 0) {
+      if (((alive >> f) & 1) && pid(f) >= 0) {
         if (noff < a.max_nbr) {
-          a.nbr[(size_t)row * a.max_nbr + noff] = pid[pb + f];
+          a.nbr[(size_t)row * a.max_nbr + noff] = pid(f);
           if (a.area) a.area[(size_t)row * a.max_nbr + noff] = farea[q];
         }
         ++noff;
@@ -1714,9 +1753,9 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
           a.verts[o + 0] = p64x + v.x;
           a.verts[o + 1] = p64y + v.y;
           a.verts[o + 2] = p64z + v.z;
-          a.vplanes[o + 0] = pid[pb + (u & 0xFF)];
-          a.vplanes[o + 1] = pid[pb + ((u >> 8) & 0xFF)];
-          a.vplanes[o + 2] = pid[pb + ((u >> 16) & 0xFF)];
+          a.vplanes[o + 0] = pid(TC::a(u));
+          a.vplanes[o + 1] = pid(TC::b(u));
+          a.vplanes[o + 2] = pid(TC::c(u));
         }
         ++voff;
       }
@@ -1726,7 +1765,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   if (have && j == 0) {
     if (fin == VOTESS_CELL_CERTIFIED && (ntot > a.max_nbr || (a.max_vert > 0 && vtot > a.max_vert)))
       fin = VOTESS_CELL_CAPACITY;
-    a.status[row] = (uint8_t)fin | (a.rest || ((a.mark >> fin) & 1) ? kLeft : (uint8_t)0);
+    a.status[row] = (uint8_t)(fin | (a.rest || ((a.mark >> fin) & 1) ? kLeft : 0));
     a.nbr_count[row] = fin == VOTESS_CELL_CERTIFIED ? ntot : 0;
     a.volume[row] = fin == VOTESS_CELL_CERTIFIED ? vol : 0.0;
     if (a.centroid) {
@@ -1773,37 +1812,40 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
 // One wave (= one block) clips `per` cells, one per group.  With `rest`, the
 // list kernel has been over the launch's cells and left some: cells that
 // outgrew it (taken again from the box) and, when this is the stream kernel,
-// cells that their lists did not certify (resumed).  They are picked out by
-// the mark in their status and packed within each 64 cells: the waves that
-// share 64 cells take the first cells left, the next ones, ..., and most waves
-// find nothing and end.  The marks stay until k_unmark, so that all of
-// these waves see the same ones.  (A wave that loops over its 64 cells instead
-// keeps so many invariants of the loop in registers that it spills.)
+// cells that their lists did not certify (resumed).
+// Marked cells are packed within each 64: the waves that share 64 cells take
+// the first ones, the next ones, ..., and most waves find nothing and end.
+// (A wave that loops over its cells keeps so many invariants of the loop in
+// registers that it spills.)  The marks stay until k_unmark, so that all of
+// these waves see the same ones.
 // Blocks run in an XCD-aware order (they are dealt round-robin over the eight
 // XCDs): launched block b takes logical block (b mod 8) per + b / 8, so each
 // XCD clips a contiguous stretch of grid-sorted cells, whose neighbours its L2
 // then holds.
-// Held to 3 waves per SIMD but for the large kernel: the compiler would
-// otherwise give the stream variants ~225 VGPRs (2 waves), and with the third
-// wave hiding load latency they run ~20% faster despite some spills.
+// The fast kernels are held to 3 waves per SIMD, as many as their LDS lets a
+// CU hold: with triangles in 16 bits and planes without their offsets a list
+// wave takes 13.1 KB (double clip of float points 16.2, of double ones 19.3)
+// and a CU holds 12 (10, 8); with 32-bit triangles and offsets 14.9 (22.1) KB
+// and 10 (7).  Clip times with those and now: 3M clustered points in double
+// 58.9 and 51.1 ms, 16M in float 215.9 and 202.6 ms, 1M uniform 6.99 and 6.39.
 template <typename P, typename R, int L, int TMAX, int PMAX, bool RECHECK, bool STREAM>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ? 3 : 1))) void k_clip(ClipArgs a) {
   constexpr int G = 64 / L;
-  const int nblk = clip_blocks(a.nc, a.per, a.rest), per = (nblk + 7) / 8;
-  const int lblk = (int)(blockIdx.x % 8u) * per + (int)(blockIdx.x / 8u);
+  const int waves = 64 / a.per;  // that share 64 cells
+  const int nblk = clip_blocks(a.nc, a.per, a.rest), per8 = (nblk + 7) / 8;
+  const int lblk = (int)(blockIdx.x % 8u) * per8 + (int)(blockIdx.x / 8u);
   if (lblk >= nblk) return;  // the whole (one-wave) block
   const int lane = threadIdx.x, g = lane / L;
-  long long t_idx;
-  bool have, resume = false;
+  long long t_idx = (long long)lblk * a.per + g;
+  bool have = g < a.per && t_idx < a.nc, resume = false;
   if (a.rest) {
-    const int waves = 64 / a.per;  // waves that share 64 cells
     const long long base = (long long)(lblk / waves) * 64;
     int stat = 0;
     if (base + lane < a.nc) stat = a.status[a.out_by_id && a.cells ? (long long)a.cells[base + lane] : base + lane];
     unsigned long long todo = __ballot((stat & kLeft) != 0);
-    const int first = lblk % waves * a.per;
-    if (__popcll(todo) <= first) return;
-    for (int i = 0; i < first; ++i) todo &= todo - 1ull;
+    const int skip = lblk % waves * a.per;  // cells that the waves before this one take
+    if (__popcll(todo) <= skip) return;
+    for (int i = 0; i < skip; ++i) todo &= todo - 1ull;
     int at = -1;
 #pragma unroll
     for (int i = 0; i < G; ++i) {  // the i-th of the cells left goes to group i
@@ -1811,14 +1853,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ?
       todo &= todo - 1ull;
     }
     have = at >= 0;
-    t_idx = base + (have ? at : 0);
-    resume = STREAM && have && __shfl(stat, have ? at : 0, 64) == (kLeft | VOTESS_CELL_RADIUS);
-  } else {
-    t_idx = (long long)lblk * a.per + g;
-    have = g < a.per && t_idx < a.nc;
-    if (!have) t_idx = 0;
+    t_idx = base + at;
+    const int from = __shfl(stat, have ? at : 0, 64);  // by every lane: a shuffle reads active lanes only
+    resume = STREAM && have && from == (kLeft | VOTESS_CELL_RADIUS);
   }
-  clip_group<P, R, L, TMAX, PMAX, RECHECK, STREAM>(a, t_idx, have, resume);
+  clip_group<P, R, L, TMAX, PMAX, RECHECK, STREAM>(a, have ? t_idx : 0, have, resume);
 }
 
 constexpr int kFillWaves = 2048;
@@ -1843,37 +1882,46 @@ void launch(ClipArgs ca, bool rest, hipStream_t st) {
   // double 1.24, 1.14 and 1.28 ms; 8k uniform ones, float 0.26, 0.32 and 0.34.
   ca.per = 64 / L;
   while (ca.per > 1 && ca.nc / ca.per < kFillWaves) ca.per /= 2;
-  const unsigned blocks = (unsigned)(8 * ((clip_blocks(ca.nc, ca.per, rest) + 7) / 8));
-  k_clip<P, R, L, TMAX, PMAX, RECHECK, STREAM><<<blocks, 64, 0, st>>>(ca);
+  const int n = clip_blocks(ca.nc, ca.per, rest);
+  k_clip<P, R, L, TMAX, PMAX, RECHECK, STREAM><<<(unsigned)(8 * ((n + 7) / 8)), 64, 0, st>>>(ca);
 }
 
 template <typename P, typename R, int L, int TMAX, int PMAX, bool RECHECK>
-votess_status run(const ClipArgs& ca, hipStream_t st) {
+void launch_all(const ClipArgs& ca, bool rest, hipStream_t st) {
   if (ca.stream)
-    launch<P, R, L, TMAX, PMAX, RECHECK, true>(ca, false, st);
+    launch<P, R, L, TMAX, PMAX, RECHECK, true>(ca, rest, st);
   else
-    launch<P, R, L, TMAX, PMAX, RECHECK, false>(ca, false, st);
+    launch<P, R, L, TMAX, PMAX, RECHECK, false>(ca, rest, st);
+}
+
+// The fast kernels.  Lists are clipped by 8 lanes per cell: list cells are
+// bound by vector instructions, and 8 lanes waste fewer of them than 16 (a cut
+// makes about 6 new vertices); 48 vertex slots let more waves fit a CU.  A
+// stream cell waits on loads, and its batches of candidates fill 16 lanes; 48
+// slots and fewer vertices in reach would let 4 waves fit a SIMD rather than
+// 3, but clustered cells overflow them (16M points: 208 -> 312 ms).  Cells that
+// outgrow the list kernel share the second launch: in one of their own they
+// leave the chip half empty (1.2M filament points: 36.3 ms together, 29.9 and
+// 10.2 ms apart).
+template <typename P, typename R, bool RECHECK>
+votess_status run_fast(ClipArgs ca, bool split, hipStream_t st) {
+  if (split) {
+    ca.save = ca.stream;
+    ca.mark = 1 << VOTESS_CELL_CAPACITY | (ca.stream ? 1 << VOTESS_CELL_RADIUS : 0);
+    launch<P, R, kListLanes, kListVert, 32, RECHECK, false>(ca, false, st);
+    ca.save = ca.mark = 0;
+  }
+  launch_all<P, R, 16, 64, 32, RECHECK>(ca, split, st);
+  if (split)
+    k_unmark<<<(unsigned)(((long long)ca.nc + 255) / 256), 256, 0, st>>>(ca.status, ca.out_by_id ? ca.cells : nullptr,
+                                                                        ca.nc);
   VT_HIP(hipGetLastError());
   return VOTESS_OK;
 }
 
-// The fast kernels.  Lists are clipped by 8 lanes per cell with 48 vertex
-// slots; what is left goes to 16 lanes per cell with 64 slots.  A stream cell
-// waits on loads and its batches of candidates fill 16 lanes; list cells are
-// bound by vector instructions, and 8 lanes waste fewer of them (a cut makes
-// about 6 new vertices).
 template <typename P, typename R, bool RECHECK>
-votess_status run_fast(ClipArgs ca, bool split, hipStream_t st) {
-  if (!split) return run<P, R, 16, 64, 32, RECHECK>(ca, st);
-  ca.save = ca.stream;
-  ca.mark = 1 << VOTESS_CELL_CAPACITY | (ca.stream ? 1 << VOTESS_CELL_RADIUS : 0);
-  launch<P, R, kListLanes, kListVert, 32, RECHECK, false>(ca, false, st);
-  ca.save = ca.mark = 0;
-  if (ca.stream)
-    launch<P, R, 16, 64, 32, RECHECK, true>(ca, true, st);
-  else
-    launch<P, R, 16, 64, 32, RECHECK, false>(ca, true, st);
-  k_unmark<<<(unsigned)(((long long)ca.nc + 255) / 256), 256, 0, st>>>(ca.status, ca.out_by_id ? ca.cells : nullptr, ca.nc);
+votess_status run_large(const ClipArgs& ca, hipStream_t st) {
+  launch_all<P, R, 32, 256, 64, RECHECK>(ca, false, st);
   VT_HIP(hipGetLastError());
   return VOTESS_OK;
 }
@@ -1927,7 +1975,7 @@ votess_status launch_clip(const ClipLaunch& a, hipStream_t st) {
   if (a.stream && !a.cell_start) return fail(VOTESS_EINVAL, "clip: the stream phase needs cell_start");
   c.rest = c.mark = c.save = 0;
   if (a.capacity == 0) {
-    // two launches, unless there is no list, the state of a cell has no room
+    // in two launches, unless there is no list, the state of a cell has no room
     // in its neighbour row, or two cells may share one
     const bool split = a.k > 0 && (!a.stream || a.max_nbr >= kStateWords) && a.own_rows;
     if (f32) return run_fast<float, float, true>(c, split, st);
@@ -1936,9 +1984,9 @@ votess_status launch_clip(const ClipLaunch& a, hipStream_t st) {
   }
   // the large-capacity kernel: 32 lanes per cell (two cells per wave keep its
   // LDS per workgroup low enough for more than one wave per SIMD)
-  if (f32) return run<float, float, 32, 256, 64, true>(c, st);
-  if (a.dtype == VOTESS_F32) return run<float, double, 32, 256, 64, false>(c, st);
-  return run<double, double, 32, 256, 64, false>(c, st);
+  if (f32) return run_large<float, float, true>(c, st);
+  if (a.dtype == VOTESS_F32) return run_large<float, double, false>(c, st);
+  return run_large<double, double, false>(c, st);
 }
 
 }  // namespace votess
