@@ -446,13 +446,29 @@ __global__ __launch_bounds__(64) void k_mlp(MlpArgs a) {
 }
 
 
-// Fixed-order sum of per-block partials: grads[p] = sum_b partial[b][p].
-__global__ void k_reduce(const float* __restrict__ partial, int blocks, float* __restrict__ out) {
+// Fixed-order sum of per-block partials: out[p] = sum_b partial[b][p], and the
+// same to the caller's buffers (nullable): the gradient and, last, the loss.
+// Waits on loads, one partial after the other if they are added as they come
+// (30 us for 128 blocks): 16 are loaded at a time, then added in order, and
+// one-wave blocks spread the 5448 sums over the chip.
+constexpr int kReduceAhead = 16;
+__global__ __launch_bounds__(64) void k_reduce(const float* __restrict__ partial, int blocks, float* __restrict__ out,
+                                               float* __restrict__ grads, float* __restrict__ loss) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p > NPARAM) return;
   float acc = 0.0f;
-  for (int b = 0; b < blocks; ++b) acc += partial[(size_t)b * (NPARAM + 1) + p];
+  int b = 0;
+  for (; b + kReduceAhead <= blocks; b += kReduceAhead) {
+    float v[kReduceAhead];
+#pragma unroll
+    for (int i = 0; i < kReduceAhead; ++i) v[i] = partial[(size_t)(b + i) * (NPARAM + 1) + p];
+#pragma unroll
+    for (int i = 0; i < kReduceAhead; ++i) acc += v[i];
+  }
+  for (; b < blocks; ++b) acc += partial[(size_t)b * (NPARAM + 1) + p];
   out[p] = acc;
+  if (p < NPARAM && grads) grads[p] = acc;
+  if (p == NPARAM && loss) *loss = acc;
 }
 
 __global__ void k_adam(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
@@ -555,7 +571,8 @@ votess_status run_choose(votess_kmodel* km, const float* feats, int nq, float ta
   return VOTESS_OK;
 }
 
-static votess_status run_grad(votess_kmodel* km, const float* feats, const uint8_t* labels, int nb, hipStream_t st) {
+static votess_status run_grad(votess_kmodel* km, const float* feats, const uint8_t* labels, int nb, float* grads,
+                              float* loss, hipStream_t st) {
   const int blocks = (nb + kSamplesPerBlock - 1) / kSamplesPerBlock;
   if (blocks > km->partial_blocks) {
     dev_free(km->ctx, km->partial);
@@ -573,7 +590,7 @@ static votess_status run_grad(votess_kmodel* km, const float* feats, const uint8
   a.partial = km->partial;
   k_mlp<1><<<blocks, 64, 0, st>>>(a);
   VT_HIP(hipGetLastError());
-  k_reduce<<<(NPARAM + 1 + 255) / 256, 256, 0, st>>>(km->partial, blocks, km->grads);
+  k_reduce<<<(NPARAM + 1 + 63) / 64, 64, 0, st>>>(km->partial, blocks, km->grads, grads, loss);
   VT_HIP(hipGetLastError());
   return VOTESS_OK;
 }
@@ -889,10 +906,7 @@ votess_status votess_kmodel_grad(votess_kmodel* km, const float* feats, const ui
   if (nb < 1 || nb >= (1LL << 31) - 1) return fail(VOTESS_EINVAL, "kmodel_grad: bad batch");
   VT_HIP(hipSetDevice(km->ctx->device));
   hipStream_t st = (hipStream_t)stream;
-  VT_TRY(run_grad(km, feats, labels, (int)nb, st));
-  VT_HIP(hipMemcpyAsync(grads, km->grads, NPARAM * 4, hipMemcpyDeviceToDevice, st));
-  VT_HIP(hipMemcpyAsync(loss, km->grads + NPARAM, 4, hipMemcpyDeviceToDevice, st));
-  return VOTESS_OK;
+  return run_grad(km, feats, labels, (int)nb, grads, loss, st);
 }
 
 votess_status votess_kmodel_train_step(votess_kmodel* km, const float* feats, const uint8_t* labels, int64_t nb,
@@ -901,12 +915,11 @@ votess_status votess_kmodel_train_step(votess_kmodel* km, const float* feats, co
   if (nb < 1 || nb >= (1LL << 31) - 1 || !(lr > 0.0f)) return fail(VOTESS_EINVAL, "kmodel_train_step: bad batch/lr");
   VT_HIP(hipSetDevice(km->ctx->device));
   hipStream_t st = (hipStream_t)stream;
-  VT_TRY(run_grad(km, feats, labels, (int)nb, st));
+  VT_TRY(run_grad(km, feats, labels, (int)nb, nullptr, loss, st));
   km->step += 1;
   const float c1 = 1.0f - std::pow(0.9f, (float)km->step), c2 = 1.0f - std::pow(0.999f, (float)km->step);
   k_adam<<<(NPARAM + 255) / 256, 256, 0, st>>>(km->theta, km->m, km->v, km->grads, lr, c1, c2);
   VT_HIP(hipGetLastError());
-  if (loss) VT_HIP(hipMemcpyAsync(loss, km->grads + NPARAM, 4, hipMemcpyDeviceToDevice, st));
   return VOTESS_OK;
 }
 
