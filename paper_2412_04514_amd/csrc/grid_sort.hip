@@ -9,6 +9,8 @@
 #include "internal.h"
 #include "device_common.h"
 
+#include <algorithm>
+
 namespace votess {
 
 GridDev to_dev(const votess_grid& g) {
@@ -27,6 +29,9 @@ namespace {
 
 constexpr int kLdsSortMax = 4096; // larger cells sort their keys in global memory
 constexpr int kDenseBlocks = 2048; // blocks of the dense-cell pass (grid-stride over the dense cells)
+constexpr int kWavePoints = 256;   // dense cells of up to this many points are ordered by one wave each
+constexpr int kWaveBlocks = 8192;  // waves of that pass
+constexpr int kSmallCells = 1024;  // cells, one per thread, of a block of k_order_small
 
 template <typename T>
 __global__ void k_cell_rank(const T* __restrict__ pts, int n, GridDev G, int* __restrict__ count,
@@ -50,29 +55,94 @@ __global__ void k_scatter(const T* __restrict__ pts, int n, const int2* __restri
   tmp[cell_start[c.x] + c.y] = Rec<T>::make(pts[3 * (size_t)i], pts[3 * (size_t)i + 1], pts[3 * (size_t)i + 2], i);
 }
 
-// One thread per grid cell: rank-by-count reorder of small cells; large cells
-// are queued for k_order_big.
+// Position of a dense cell's record in sub_start: a function of the cell's
+// first point b, so that the cells need not agree on it.  A cell of len > 16
+// points spans 4 floor(7 len / 17) words or more from its position to the next
+// one's, and its record takes (kSubHead + len / 2 + 1, rounded up to 4) <= that;
+// all of them end before 28 n / 17 < sub_capacity(n).
+__device__ __forceinline__ int sub_offset(int b) { return 4 * (int)((long long)b * 7 / 17); }
+
+// Orders small cells (up to kSubMin points) and lists the dense ones: those of
+// up to `split` points from the end of the list backwards, for k_order_mid,
+// the others from its front.  A wave takes 64 consecutive cells and goes over
+// their points as they lie in memory, one per lane, in chunks of whole cells; a
+// point's rank in its cell is the number of its smaller indices.  12M filament
+// points, f32: 0.14 ms (one thread per cell and an addition to the list's
+// length per wave: 0.73 ms, as much with these chunks, since additions to one
+// address take about 10 ns each; one per 256, 512 and 1024 cells leave the
+// whole sort at 1.46, 1.36 and 1.33 ms).
 template <typename T>
-__global__ void k_order_small(const typename Rec<T>::type* __restrict__ tmp, const int* __restrict__ cell_start,
-                              int ncells, typename Rec<T>::type* __restrict__ out, int* __restrict__ perm,
-                              int* __restrict__ big, int* __restrict__ nbig, int2* __restrict__ subinfo) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= ncells) return;
-  const int b = cell_start[c], e = cell_start[c + 1];
-  const int len = e - b;
-  if (subinfo) subinfo[c] = make_int2(-1, 0);
-  if (len == 0) return;
-  if (len > kSubMin) {  // dense cell: sub-grid order, one block per cell
-    big[atomicAdd(nbig, 1)] = c;
-    return;
+__global__ __launch_bounds__(kSmallCells) void k_order_small(const typename Rec<T>::type* __restrict__ tmp,
+                                                             const int* __restrict__ cell_start, int ncells,
+                                                             typename Rec<T>::type* __restrict__ out,
+                                                             int* __restrict__ perm, int* __restrict__ list,
+                                                             int* __restrict__ nlist, int split,
+                                                             int2* __restrict__ subinfo) {
+  __shared__ int heads_of[kSmallCells], ids_of[kSmallCells], ndense[2][kSmallCells / 64], at_[2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = blockIdx.x * kSmallCells + threadIdx.x;
+  int b = 0, len = 0;
+  if (c < ncells) {
+    b = cell_start[c];
+    len = cell_start[c + 1] - b;
+    if (subinfo) subinfo[c] = make_int2(-1, 0);
   }
-  for (int t = b; t < e; ++t) {
-    const auto r = tmp[t];
+  const unsigned long long below = (1ull << lane) - 1ull;
+  const bool mid = len > kSubMin && len <= split, large = len > kSubMin && !mid;
+  const unsigned long long mlarge = __ballot(large), mmid = __ballot(mid);
+  if (lane < 2) ndense[lane][wave] = __popcll(lane ? mmid : mlarge);
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    int sum = 0;
+    for (int w = 0; w < kSmallCells / 64; ++w) {
+      const int v = ndense[threadIdx.x][w];
+      ndense[threadIdx.x][w] = sum;
+      sum += v;
+    }
+    at_[threadIdx.x] = sum ? atomicAdd(&nlist[threadIdx.x], sum) : 0;
+  }
+  __syncthreads();
+  if (large) list[at_[0] + ndense[0][wave] + __popcll(mlarge & below)] = c;
+  if (mid) list[ncells - 1 - (at_[1] + ndense[1][wave] + __popcll(mmid & below))] = c;
+  if (mid || large) len = 0;
+  // each wave for itself from here on
+  int* head = heads_of + 64 * wave;
+  int* ids = ids_of + 64 * wave;
+  auto fence = [] {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  // position of each cell's points among those of the wave's small cells
+  int end = len;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(end, o, 64);
+    if (lane >= o) end += y;
+  }
+  const int total = __shfl(end, 63, 64);
+  for (int from = 0; from < total;) {
+    const bool in = end > from && end <= from + 64;  // the cell lies in this chunk
+    head[lane] = -1;
+    fence();
+    if (in && len > 0) head[end - len - from] = lane;
+    fence();
+    const int to = __shfl(end, 63 - __clzll((long long)__ballot(in)), 64);
+    const bool on = from + lane < to;
+    const unsigned long long heads = __ballot(head[lane] >= 0);
+    const int h = 63 - __clzll((long long)(heads & (below | (1ull << lane))));  // where this point's cell begins
+    const int k = head[h];
+    const int kb = __shfl(b, k, 64), klen = __shfl(len, k, 64);
+    const auto r = tmp[kb + min(lane - h, klen - 1)];  // past the chunk: a point of its last cell
     const int id = Rec<T>::id(r);
-    int rank = 0;
-    for (int u = b; u < e; ++u) rank += Rec<T>::id(tmp[u]) < id;
-    out[b + rank] = r;
-    perm[b + rank] = id;
+    ids[lane] = id;
+    fence();
+    if (on) {
+      int rank = 0;
+      for (int u = 0; u < klen; ++u) rank += ids[h + u] < id;
+      out[kb + rank] = r;
+      perm[kb + rank] = id;
+    }
+    fence();
+    from = to;
   }
 }
 
@@ -124,113 +194,26 @@ __device__ void plan_sub(int count, double e0, double e1, double e2, int& m0, in
   }
 }
 
-// One block per dense cell: order its points by (sub-cell, original index)
-// and write its sub-grid record (see device_common.h).  The sub-grid spans,
-// per axis, the central 90% of the cell's points (from a histogram of
-// kSubBins bins over their bounding box); points beyond fall in the edge
-// sub-cells.
+// Without sub-grids: one block per dense cell orders its points by original
+// index.
 template <typename T>
 __global__ __launch_bounds__(256) void k_order_big(const typename Rec<T>::type* __restrict__ tmp,
                                                    const int* __restrict__ cell_start, const int* __restrict__ big,
-                                                   const int* __restrict__ nbig, GridDev G,
+                                                   const int* __restrict__ nbig,
                                                    typename Rec<T>::type* __restrict__ out, int* __restrict__ perm,
-                                                   unsigned long long* __restrict__ gkey, unsigned* __restrict__ gval,
-                                                   int2* __restrict__ subinfo, int* __restrict__ sub_start,
-                                                   int* __restrict__ sub_total) {
+                                                   unsigned long long* __restrict__ gkey,
+                                                   unsigned* __restrict__ gval) {
   __shared__ unsigned long long skey[kLdsSortMax];
   __shared__ unsigned sval[kLdsSortMax];
-  __shared__ double sbox[4][6];
-  __shared__ int shist[3][kSubBins];
-  __shared__ int soff, sm[3];
-  __shared__ double slo[3], sih[3];
   const int nb = *nbig;
-  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int q = blockIdx.x; q < nb; q += gridDim.x) {
     const int c = big[q];
     const int b = cell_start[c], len = cell_start[c + 1] - b;
     const bool lds = len <= kLdsSortMax;
     unsigned long long* key = lds ? skey : gkey + b;
     unsigned* val = lds ? sval : gval + b;
-    if (subinfo) {
-      // bounding box of the cell's points
-      double mn0 = 1e300, mn1 = 1e300, mn2 = 1e300, mx0 = -1e300, mx1 = -1e300, mx2 = -1e300;
-      for (int t = threadIdx.x; t < len; t += blockDim.x) {
-        const auto r = tmp[b + t];
-        mn0 = fmin(mn0, (double)r.x); mx0 = fmax(mx0, (double)r.x);
-        mn1 = fmin(mn1, (double)r.y); mx1 = fmax(mx1, (double)r.y);
-        mn2 = fmin(mn2, (double)r.z); mx2 = fmax(mx2, (double)r.z);
-      }
-      for (int o = 32; o >= 1; o >>= 1) {
-        mn0 = fmin(mn0, __shfl_xor(mn0, o, 64)); mx0 = fmax(mx0, __shfl_xor(mx0, o, 64));
-        mn1 = fmin(mn1, __shfl_xor(mn1, o, 64)); mx1 = fmax(mx1, __shfl_xor(mx1, o, 64));
-        mn2 = fmin(mn2, __shfl_xor(mn2, o, 64)); mx2 = fmax(mx2, __shfl_xor(mx2, o, 64));
-      }
-      if (lane == 0) {
-        sbox[wid][0] = mn0; sbox[wid][1] = mn1; sbox[wid][2] = mn2;
-        sbox[wid][3] = mx0; sbox[wid][4] = mx1; sbox[wid][5] = mx2;
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        const int nw = (int)(blockDim.x + 63) >> 6;
-        for (int w = 1; w < nw; ++w) {
-          mn0 = fmin(mn0, sbox[w][0]); mn1 = fmin(mn1, sbox[w][1]); mn2 = fmin(mn2, sbox[w][2]);
-          mx0 = fmax(mx0, sbox[w][3]); mx1 = fmax(mx1, sbox[w][4]); mx2 = fmax(mx2, sbox[w][5]);
-        }
-        sbox[0][0] = mn0; sbox[0][1] = mn1; sbox[0][2] = mn2;
-        sbox[0][3] = mx0; sbox[0][4] = mx1; sbox[0][5] = mx2;
-      }
-      for (int t = threadIdx.x; t < 3 * kSubBins; t += blockDim.x) (&shist[0][0])[t] = 0;
-      __syncthreads();
-      // per-axis histograms over the bounding box
-      for (int t = threadIdx.x; t < len; t += blockDim.x) {
-        const auto r = tmp[b + t];
-        const double x[3] = {(double)r.x, (double)r.y, (double)r.z};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          const double lo = sbox[0][a], w = sbox[0][3 + a] - lo;
-          const int bin = w > 0.0 ? (int)fmin((x[a] - lo) / w * kSubBins, (double)(kSubBins - 1)) : 0;
-          atomicAdd(&shist[a][bin], 1);
-        }
-      }
-      __syncthreads();
-      if (threadIdx.x < 3) {
-        // the box of the central 90% of the points along this axis
-        const int a = threadIdx.x;
-        const double lo = sbox[0][a], w = sbox[0][3 + a] - lo;
-        const int cut_lo = len / 20, cut_hi = len - len / 20;
-        int acc = 0, blo = 0, bhi = kSubBins - 1;
-        bool got_lo = false;
-        for (int i = 0; i < kSubBins; ++i) {
-          const int next = acc + shist[a][i];
-          if (!got_lo && next > cut_lo) { blo = i; got_lo = true; }
-          if (next >= cut_hi) { bhi = i; break; }
-          acc = next;
-        }
-        slo[a] = lo + w * ((double)blo / kSubBins);
-        sih[a] = fmax(w * ((double)(bhi + 1 - blo) / kSubBins), (a == 0 ? G.h0 : a == 1 ? G.h1 : G.h2) * 0x1p-30);
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        // sih holds the extents here
-        const double e0 = sih[0], e1 = sih[1], e2 = sih[2];
-        int m0, m1, m2;
-        plan_sub(len, e0, e1, e2, m0, m1, m2);
-        sm[0] = m0; sm[1] = m1; sm[2] = m2;
-        sih[0] = m0 / e0; sih[1] = m1 / e1; sih[2] = m2 / e2;
-        const int words = (kSubHead + m0 * m1 * m2 + 1 + 3) & ~3;
-        soff = atomicAdd(sub_total, words);
-      }
-      __syncthreads();
-    }
-    const int m0 = subinfo ? sm[0] : 1, m1 = subinfo ? sm[1] : 1, m2 = subinfo ? sm[2] : 1;
-    const double lo0 = subinfo ? slo[0] : 0.0, lo1 = subinfo ? slo[1] : 0.0, lo2 = subinfo ? slo[2] : 0.0;
-    const double ih0 = subinfo ? sih[0] : 0.0, ih1 = subinfo ? sih[1] : 0.0, ih2 = subinfo ? sih[2] : 0.0;
     for (int t = threadIdx.x; t < len; t += blockDim.x) {
-      const auto r = tmp[b + t];
-      unsigned sid = 0;
-      if (subinfo)
-        sid = (unsigned)(sub_axis(r.x, lo0, ih0, m0) + m0 * (sub_axis(r.y, lo1, ih1, m1) + m1 * sub_axis(r.z, lo2, ih2, m2)));
-      key[t] = ((unsigned long long)sid << 32) | (unsigned)Rec<T>::id(r);
+      key[t] = (unsigned)Rec<T>::id(tmp[b + t]);
       val[t] = (unsigned)t;
     }
     __syncthreads();
@@ -238,29 +221,6 @@ __global__ __launch_bounds__(256) void k_order_big(const typename Rec<T>::type* 
     for (int t = threadIdx.x; t < len; t += blockDim.x) {
       out[b + t] = tmp[b + (int)val[t]];
       perm[b + t] = (int)(unsigned)(key[t] & 0xffffffffu);
-    }
-    if (subinfo) {
-      const int off = soff;
-      const int ns = m0 * m1 * m2;
-      int* rec = sub_start + off;
-      if (threadIdx.x == 0) {
-        *(int4*)rec = make_int4(m0, m1, m2, 0);
-        *(double2*)(rec + 4) = make_double2(lo0, lo1);
-        *(double2*)(rec + 8) = make_double2(lo2, ih0);
-        *(double2*)(rec + 12) = make_double2(ih1, ih2);
-        subinfo[c] = make_int2(off, ns);
-      }
-      for (int sc = threadIdx.x; sc <= ns; sc += blockDim.x) {
-        // first position whose sub-cell id is >= sc
-        int lo = 0, hi = len;
-        const unsigned long long want = (unsigned long long)sc << 32;
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          if (key[mid] < want) lo = mid + 1;
-          else hi = mid;
-        }
-        rec[kSubHead + sc] = lo;
-      }
     }
     __syncthreads();
   }
@@ -365,8 +325,10 @@ constexpr int kCntLds = 4096;
 // by the bitonic network instead of the per-sub-cell rank count below.
 constexpr int kCrowd = 256;
 
-// One block per dense cell (grid-stride over the dense-cell list): plan the
-// cell's sub-grid (as k_order_big), then a counting sort by sub-cell -- LDS
+// One block per dense cell of more than kWavePoints points (grid-stride over
+// their list): plan the cell's sub-grid (it spans, per axis, the central 90% of
+// the points, from a histogram of kSubBins bins over their bounding box; points
+// beyond fall in the edge sub-cells), then a counting sort by sub-cell -- LDS
 // atomic counts give each point its sub-cell and a provisional slot, a block
 // scan turns counts into the sub-cell starts (written to the record as they
 // are) -- and within a sub-cell each point's final rank is the number of its
@@ -380,12 +342,11 @@ __global__ __launch_bounds__(256) void k_order_dense(const typename Rec<T>::type
                                                      unsigned* __restrict__ g_sid, unsigned* __restrict__ g_rank,
                                                      unsigned* __restrict__ g_slot, int* __restrict__ g_cnt,
                                                      unsigned long long* __restrict__ gkey, unsigned* __restrict__ gval,
-                                                     int2* __restrict__ subinfo, int* __restrict__ sub_start,
-                                                     int* __restrict__ sub_total) {
+                                                     int2* __restrict__ subinfo, int* __restrict__ sub_start) {
   __shared__ int s_cnt[kCntLds];
   __shared__ double sbox[4][6];
   __shared__ int shist[3][kSubBins];
-  __shared__ int soff, sm[3], s_crowd, s_bin[3][2];
+  __shared__ int sm[3], s_crowd, s_bin[3][2];
   __shared__ double slo[3], sih[3];
   const int nb = *nbig;
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -472,8 +433,6 @@ __global__ __launch_bounds__(256) void k_order_dense(const typename Rec<T>::type
       plan_sub(len, e0, e1, e2, m0, m1, m2);
       sm[0] = m0; sm[1] = m1; sm[2] = m2;
       sih[0] = m0 / e0; sih[1] = m1 / e1; sih[2] = m2 / e2;
-      const int words = (kSubHead + m0 * m1 * m2 + 1 + 3) & ~3;
-      soff = atomicAdd(sub_total, words);
     }
     __syncthreads();
     const int m0 = sm[0], m1 = sm[1], m2 = sm[2];
@@ -495,6 +454,7 @@ __global__ __launch_bounds__(256) void k_order_dense(const typename Rec<T>::type
     for (int sc = threadIdx.x; sc < ns; sc += blockDim.x) crowd |= cnt[sc] > kCrowd;
     if (crowd) s_crowd = 1;
     block_scan_inplace(cnt, ns + 1);  // cnt[sc] = first point of sub-cell sc, cnt[ns] = len
+    const int soff = sub_offset(b);
     int* rec = sub_start + soff;
     if (threadIdx.x == 0) {
       *(int4*)rec = make_int4(m0, m1, m2, 0);
@@ -535,6 +495,144 @@ __global__ __launch_bounds__(256) void k_order_dense(const typename Rec<T>::type
       }
     }
     __syncthreads();
+  }
+}
+
+// A wave per dense cell of up to 64 R points, R to a lane, all in registers: the
+// same sub-grid and order as k_order_dense, without its barriers.  The bins that
+// bound the central 90% are order statistics of the points' bins, found bit by
+// bit with ballots rather than from a histogram.  Bound by vector instructions
+// (divisions and roots in double): 12M filament points with 166,000 dense cells
+// take 0.24 ms, where k_order_dense took 2.1.
+template <typename T, int R>
+__device__ __forceinline__ void order_mid(const typename Rec<T>::type* __restrict__ tmp, int c, int b, int len,
+                                          const GridDev& G, typename Rec<T>::type* __restrict__ out,
+                                          int* __restrict__ perm, int2* __restrict__ subinfo,
+                                          int* __restrict__ sub_start, int* cnt, unsigned* slot) {
+  const int lane = threadIdx.x;
+  typename Rec<T>::type r[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) r[i] = tmp[b + min(lane + 64 * i, len - 1)];  // past the end: the last point again
+  T mn[3] = {r[0].x, r[0].y, r[0].z}, mx[3] = {r[0].x, r[0].y, r[0].z};
+#pragma unroll
+  for (int i = 1; i < R; ++i) {
+    const T x[3] = {r[i].x, r[i].y, r[i].z};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      mn[a] = x[a] < mn[a] || mn[a] != mn[a] ? x[a] : mn[a];
+      mx[a] = x[a] > mx[a] || mx[a] != mx[a] ? x[a] : mx[a];
+    }
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const T lo = __shfl_xor(mn[a], o, 64), hi = __shfl_xor(mx[a], o, 64);
+      mn[a] = lo < mn[a] || mn[a] != mn[a] ? lo : mn[a];
+      mx[a] = hi > mx[a] || mx[a] != mx[a] ? hi : mx[a];
+    }
+  // smallest bins that hold, with the bins below, more than len / 20 points and
+  // all but len / 20
+  const int need[2] = {len / 20 + 1, len - len / 20};
+  double lo_[3], ext[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const double lo = fmin((double)mn[a], 1e300), w = fmax((double)mx[a], -1e300) - lo;
+    int bin[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const double x = a == 0 ? r[i].x : a == 1 ? r[i].y : r[i].z;
+      bin[i] = w > 0.0 ? (int)fmin((x - lo) / w * kSubBins, (double)(kSubBins - 1)) : 0;
+      if (lane + 64 * i >= len) bin[i] = kSubBins;
+    }
+    int v[2] = {0, 0};
+#pragma unroll
+    for (int bit = kSubBins / 2; bit >= 1; bit >>= 1)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        int have = 0;
+#pragma unroll
+        for (int i = 0; i < R; ++i) have += __popcll(__ballot(bin[i] < v[s] + bit));
+        if (have < need[s]) v[s] += bit;
+      }
+    lo_[a] = lo + w * ((double)v[0] / kSubBins);
+    ext[a] = fmax(w * ((double)(v[1] + 1 - v[0]) / kSubBins), (a == 0 ? G.h0 : a == 1 ? G.h1 : G.h2) * 0x1p-30);
+  }
+  int m0, m1, m2;
+  plan_sub(len, ext[0], ext[1], ext[2], m0, m1, m2);
+  const double ih0 = m0 / ext[0], ih1 = m1 / ext[1], ih2 = m2 / ext[2];
+  const int ns = m0 * m1 * m2;  // <= len / 2
+  for (int sc = lane; sc <= ns; sc += 64) cnt[sc] = 0;
+  __syncthreads();
+  int sid[R], at[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    sid[i] = sub_axis(r[i].x, lo_[0], ih0, m0) +
+             m0 * (sub_axis(r[i].y, lo_[1], ih1, m1) + m1 * sub_axis(r[i].z, lo_[2], ih2, m2));
+    at[i] = lane + 64 * i < len ? atomicAdd(&cnt[sid[i]], 1) : 0;
+  }
+  __syncthreads();
+  const int soff = sub_offset(b);
+  int* rec = sub_start + soff;
+  if (lane == 0) {
+    *(int4*)rec = make_int4(m0, m1, m2, 0);
+    *(double2*)(rec + 4) = make_double2(lo_[0], lo_[1]);
+    *(double2*)(rec + 8) = make_double2(lo_[2], ih0);
+    *(double2*)(rec + 12) = make_double2(ih1, ih2);
+    subinfo[c] = make_int2(soff, ns);
+  }
+  int carry = 0;  // starts of the sub-cells
+  for (int s0 = 0; s0 <= ns; s0 += 64) {
+    const int v = s0 + lane <= ns ? cnt[s0 + lane] : 0;
+    int x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (s0 + lane <= ns) {
+      cnt[s0 + lane] = carry + x - v;
+      rec[kSubHead + s0 + lane] = carry + x - v;
+    }
+    carry += __shfl(x, 63, 64);
+  }
+  __syncthreads();
+  // provisional slots, then each point's rank among its sub-cell's indices
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+    if (lane + 64 * i < len) slot[cnt[sid[i]] + at[i]] = (unsigned)Rec<T>::id(r[i]);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if (lane + 64 * i >= len) continue;
+    const unsigned id = (unsigned)Rec<T>::id(r[i]);
+    const int s0 = cnt[sid[i]], s1 = cnt[sid[i] + 1];
+    int rank = 0;
+    for (int u = s0; u < s1; ++u) rank += slot[u] < id;
+    out[b + s0 + rank] = r[i];
+    perm[b + s0 + rank] = (int)id;
+  }
+  __syncthreads();
+}
+
+// One-wave blocks, grid-stride over the list of dense cells of up to
+// kWavePoints points.
+template <typename T>
+__global__ __launch_bounds__(64) void k_order_mid(const typename Rec<T>::type* __restrict__ tmp,
+                                                  const int* __restrict__ cell_start, const int* __restrict__ list,
+                                                  const int* __restrict__ nlist, int ncells, GridDev G,
+                                                  typename Rec<T>::type* __restrict__ out, int* __restrict__ perm,
+                                                  int2* __restrict__ subinfo, int* __restrict__ sub_start) {
+  __shared__ int cnt[kWavePoints / 2 + 1];
+  __shared__ unsigned slot[kWavePoints];
+  const int n = nlist[1];
+  for (int q = blockIdx.x; q < n; q += gridDim.x) {
+    const int c = list[ncells - 1 - q];
+    const int b = cell_start[c], len = cell_start[c + 1] - b;
+    if (len <= 64)
+      order_mid<T, 1>(tmp, c, b, len, G, out, perm, subinfo, sub_start, cnt, slot);
+    else
+      order_mid<T, kWavePoints / 64>(tmp, c, b, len, G, out, perm, subinfo, sub_start, cnt, slot);
   }
 }
 
@@ -598,14 +696,13 @@ votess_status launch_grid_sort(votess_ctx* ctx, const void* pts, votess_dtype dt
   int* count = ws.take<int>(ncells + 1);
   void* tmp = ws.take<char>((size_t)(n > 0 ? n : 1) * (dt == VOTESS_F32 ? 16 : 32));
   int* big = ws.take<int>(ncells + 16);
-  int* nbig = ctx->d_counter;
+  int* nbig = ctx->d_counter;  // and of the cells listed from the end
   unsigned long long* gkey = ws.take<unsigned long long>(n > 0 ? n : 1);
   unsigned* gval = ws.take<unsigned>(n > 0 ? n : 1);
   unsigned* g_sid = ws.take<unsigned>(n + 1);
   unsigned* g_rank = ws.take<unsigned>(n + 1);
   unsigned* g_slot = ws.take<unsigned>(n + 1);
   int* g_cnt = ws.take<int>(n + 1);
-  int* sub_total = ctx->d_counter + 1;
   VT_HIP(hipMemsetAsync(count, 0, (ncells + 1) * sizeof(int), st));
   VT_HIP(hipMemsetAsync(nbig, 0, 2 * sizeof(int), st));
   const int TB = 256;
@@ -619,30 +716,30 @@ votess_status launch_grid_sort(votess_ctx* ctx, const void* pts, votess_dtype dt
   }
   VT_TRY(scan_i32(count, ncells, cell_start, ws, st));
   if (n > 0) {
-    const unsigned cblk = (unsigned)((ncells + TB - 1) / TB);
-    if (dt == VOTESS_F32) {
-      k_scatter<float><<<nblk, TB, 0, st>>>((const float*)pts, n, cr, cell_start, (float4*)tmp);
-      k_order_small<float><<<cblk, TB, 0, st>>>((const float4*)tmp, cell_start, (int)ncells, (float4*)sorted, perm,
-                                                big, nbig, (int2*)subinfo);
-      if (subinfo)
-        k_order_dense<float><<<kDenseBlocks, 256, 0, st>>>((const float4*)tmp, cell_start, big, nbig, G,
-                                                           (float4*)sorted, perm, g_sid, g_rank, g_slot, g_cnt, gkey,
-                                                           gval, (int2*)subinfo, sub_start, sub_total);
-      else
-        k_order_big<float><<<512, 256, 0, st>>>((const float4*)tmp, cell_start, big, nbig, G, (float4*)sorted, perm,
-                                                gkey, gval, (int2*)subinfo, sub_start, sub_total);
-    } else {
-      k_scatter<double><<<nblk, TB, 0, st>>>((const double*)pts, n, cr, cell_start, (double4*)tmp);
-      k_order_small<double><<<cblk, TB, 0, st>>>((const double4*)tmp, cell_start, (int)ncells, (double4*)sorted,
-                                                 perm, big, nbig, (int2*)subinfo);
-      if (subinfo)
-        k_order_dense<double><<<kDenseBlocks, 256, 0, st>>>((const double4*)tmp, cell_start, big, nbig, G,
-                                                            (double4*)sorted, perm, g_sid, g_rank, g_slot, g_cnt,
-                                                            gkey, gval, (int2*)subinfo, sub_start, sub_total);
-      else
-        k_order_big<double><<<512, 256, 0, st>>>((const double4*)tmp, cell_start, big, nbig, G, (double4*)sorted,
-                                                 perm, gkey, gval, (int2*)subinfo, sub_start, sub_total);
-    }
+    const unsigned cblk = (unsigned)((ncells + kSmallCells - 1) / kSmallCells);
+    const int split = subinfo ? kWavePoints : 0;
+    auto order = [&](auto zero, auto* rec, auto* dst) {
+      using T = decltype(zero);
+      k_scatter<T><<<nblk, TB, 0, st>>>((const T*)pts, n, cr, cell_start, rec);
+      k_order_small<T><<<cblk, kSmallCells, 0, st>>>(rec, cell_start, (int)ncells, dst, perm, big, nbig, split,
+                                                     (int2*)subinfo);
+      if (subinfo) {
+        // as many blocks as there can be such cells, and no launch where there are none
+        const int nmid = std::min(kWaveBlocks, n / (kSubMin + 1)), ndense = std::min(kDenseBlocks, n / (kWavePoints + 1));
+        if (nmid)
+          k_order_mid<T><<<nmid, 64, 0, st>>>(rec, cell_start, big, nbig, (int)ncells, G, dst, perm, (int2*)subinfo,
+                                              sub_start);
+        if (ndense)
+          k_order_dense<T><<<ndense, 256, 0, st>>>(rec, cell_start, big, nbig, G, dst, perm, g_sid, g_rank, g_slot, g_cnt,
+                                                   gkey, gval, (int2*)subinfo, sub_start);
+      } else {
+        k_order_big<T><<<512, 256, 0, st>>>(rec, cell_start, big, nbig, dst, perm, gkey, gval);
+      }
+    };
+    if (dt == VOTESS_F32)
+      order(0.0f, (float4*)tmp, (float4*)sorted);
+    else
+      order(0.0, (double4*)tmp, (double4*)sorted);
     VT_HIP(hipGetLastError());
   }
   ws.used = mark;
