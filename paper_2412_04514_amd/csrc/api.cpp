@@ -105,29 +105,45 @@ bool valid_k(int k) {
   return k == 8 || k == 12 || k == 16 || k == 24 || k == 32 || k == 48 || k == 64 || k == 128 || k == kMaxK;
 }
 
+// Times of stretches of a stream, added up when the list ends, so that no
+// stretch has the host wait for it.
+struct Timers {
+  struct Span {
+    hipEvent_t a = nullptr, b = nullptr;
+    double* acc;
+  };
+  std::vector<Span> spans;
+  ~Timers() { settle(); }
+  void settle() {
+    for (Span& s : spans) {
+      float ms = 0;
+      if (s.b && hipEventSynchronize(s.b) == hipSuccess && hipEventElapsedTime(&ms, s.a, s.b) == hipSuccess)
+        *s.acc += ms;
+      if (s.a) (void)hipEventDestroy(s.a);
+      if (s.b) (void)hipEventDestroy(s.b);
+    }
+    spans.clear();
+  }
+};
 struct Timer {
-  hipEvent_t a = nullptr, b = nullptr;
+  Timers& list;
+  Timers::Span span;
   hipStream_t st;
-  double* acc;
-  bool ok = false;
-  Timer(hipStream_t s, double* out) : st(s), acc(out) {
-    ok = hipEventCreate(&a) == hipSuccess && hipEventCreate(&b) == hipSuccess;
-    if (ok) (void)hipEventRecord(a, st);
+  bool open = false;
+  Timer(Timers& l, hipStream_t s, double* out) : list(l), st(s) {
+    span.acc = out;
+    open = hipEventCreate(&span.a) == hipSuccess && hipEventRecord(span.a, st) == hipSuccess;
   }
   void stop() {
-    if (!ok) return;
-    (void)hipEventRecord(b, st);
-    (void)hipEventSynchronize(b);
-    float ms = 0;
-    (void)hipEventElapsedTime(&ms, a, b);
-    *acc += ms;
-    ok = false;
+    if (open && (hipEventCreate(&span.b) != hipSuccess || hipEventRecord(span.b, st) != hipSuccess)) {
+      if (span.b) (void)hipEventDestroy(span.b);
+      span.b = nullptr;
+    }
+    open = false;
+    if (span.a) list.spans.push_back(span);
+    span.a = nullptr;
   }
-  ~Timer() {
-    stop();
-    if (a) (void)hipEventDestroy(a);
-    if (b) (void)hipEventDestroy(b);
-  }
+  ~Timer() { stop(); }
 };
 
 }  // namespace
@@ -158,7 +174,8 @@ votess_ctx* votess_create(int device) {
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess) ctx->num_cu = prop.multiProcessorCount;
   if (hipMalloc(&ctx->d_err, 256) != hipSuccess || hipMalloc(&ctx->d_counter, 256) != hipSuccess ||
-      hipMemset(ctx->d_err, 0, 256) != hipSuccess || hipMemset(ctx->d_counter, 0, 256) != hipSuccess) {
+      hipMemset(ctx->d_err, 0, 256) != hipSuccess || hipMemset(ctx->d_counter, 0, 256) != hipSuccess ||
+      hipHostMalloc(&ctx->h_report, sizeof(Report)) != hipSuccess) {
     fail(VOTESS_ENOMEM, "context scratch");
     votess_destroy(ctx);
     return nullptr;
@@ -176,6 +193,7 @@ void votess_destroy(votess_ctx* ctx) {
   if (ctx->ws.base) dev_free(ctx, ctx->ws.base);
   if (ctx->d_err) (void)hipFree(ctx->d_err);
   if (ctx->d_counter) (void)hipFree(ctx->d_counter);
+  if (ctx->h_report) (void)hipHostFree(ctx->h_report);
   delete ctx;
 }
 
@@ -468,6 +486,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
   hipStream_t st = (hipStream_t)stream;
   VT_HIP(hipSetDevice(ctx->device));
   votess_stats& S = out->stats;
+  Timers timers;
   auto t_start = std::chrono::steady_clock::now();
   if (P.periodic) {
     if (P.kmodel || P.want_vertices || P.index_space != 0 || P.force_fail_every)
@@ -515,13 +534,16 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
 
   // ---- a1-a3 grid sort
   {
-    Timer T(st, &S.ms_sort);
+    Timer T(timers, st, &S.ms_sort);
     VT_TRY(votess_grid_sort(ctx, pts, dtype, n, box, &grid, cell_start.get<int32_t>(), perm.get<int32_t>(),
                             sorted.p, subinfo.get<int32_t>(), sub_start.get<int32_t>(), stream));
   }
-  uint32_t errs = 0;
-  VT_TRY(votess_ctx_errors(ctx, stream, &errs));
-  if (errs & ERR_OUT_OF_BOX) return fail(VOTESS_EOUTOFBOX, "a point lies outside the box (or is NaN)");
+  Report rep;  // as of the last report()
+  auto report = [&](bool errors = false) -> votess_status {
+    return read_report(ctx, errors, counters.get<unsigned long long>(), nullptr, st, rep);
+  };
+  VT_TRY(report(true));
+  if (rep.errors & ERR_OUT_OF_BOX) return fail(VOTESS_EOUTOFBOX, "a point lies outside the box (or is NaN)");
 
   ClipLaunch base;
   base.sorted = sorted.p;
@@ -582,10 +604,8 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
   int32_t* cur = cells.get<int32_t>();
   int32_t* nxt = cells2.get<int32_t>();
   // entry of a pass in the statistics, after its clip (and the passes that it took in)
-  auto record_pass = [&](int64_t cells_in, int taken) -> votess_status {
-    unsigned long long cnt[kClipCounters];
-    VT_HIP(hipMemcpyAsync(cnt, counters.p, sizeof(cnt), hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
+  auto record_pass = [&](int64_t cells_in, int taken) {
+    const unsigned long long* cnt = rep.clip;
     for (int i = 0; i <= taken && S.npasses < VOTESS_MAX_PASSES; ++i, ++S.npasses) {
       const bool last = i == taken;
       const int64_t left = last ? nfail : (int64_t)cnt[kLevelCounter + i];
@@ -596,25 +616,23 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
       cells_in = left;
     }
     entered = (int64_t)cnt[5];
-    return VOTESS_OK;
   };
   // cells that overflowed the fast kernel rerun in the large-capacity kernel
   auto capacity_pass = [&](const int32_t* ids, int cnt, int kk, bool strm) -> votess_status {
-    int ncap = 0;
     VT_TRY(launch_compact_failed(status.get<uint8_t>(), ids, cnt, nxt, ctx->d_counter, 1u << VOTESS_CELL_CAPACITY,
                                  ctx->ws, st));
-    VT_HIP(hipMemcpyAsync(&ncap, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
+    VT_TRY(report());
+    const int ncap = rep.count;
     if (ncap == 0) return VOTESS_OK;
     S.capacity_cells += ncap;
     Buf knn2;
     if (kk > 0 && !all_listed) {  // (no list in the fused form: the large kernel streams from ring 0 too)
       VT_TRY(alloc_buf(ctx, knn2, (size_t)ncap * kk * 4));
-      Timer T(st, &S.ms_knn);
+      Timer T(timers, st, &S.ms_knn);
       VT_TRY(launch_knn(ctx, sorted.p, dtype, n, GD, cell_start.get<int32_t>(), SG, nxt, ncap, kk, dist,
                         knn2.get<int32_t>(), st));
     }
-    Timer T(st, &S.ms_clip);
+    Timer T(timers, st, &S.ms_clip);
     ClipLaunch c2 = base;
     c2.cells = nxt;
     c2.nc = ncap;
@@ -634,13 +652,13 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
     } else {
       if (!fused) {
         VT_TRY(alloc_buf(ctx, knn, nn * (size_t)k * 4));
-        Timer T(st, &S.ms_knn);
+        Timer T(timers, st, &S.ms_knn);
         VT_TRY(launch_knn(ctx, sorted.p, dtype, n, GD, cell_start.get<int32_t>(), SG, nullptr, n, k, dist,
                           knn.get<int32_t>(), st));
         all_listed = true;
       }
       {
-        Timer T(st, &S.ms_clip);
+        Timer T(timers, st, &S.ms_clip);
         ClipLaunch c = base;
         c.cells = nullptr;
         c.nc = n;
@@ -651,26 +669,25 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
         VT_TRY(launch_clip(c, st));
       }
     }
-    VT_TRY(votess_ctx_errors(ctx, stream, &errs));
-    if (errs & ERR_DUPLICATE) return fail(VOTESS_EDUPLICATE, "two points coincide exactly");
+    VT_TRY(report(true));
+    if (rep.errors & ERR_DUPLICATE) return fail(VOTESS_EDUPLICATE, "two points coincide exactly");
     if (P.force_fail_every > 0) {
       k_force_fail<<<(n + 255) / 256, 256, 0, st>>>(status.get<uint8_t>(), n, P.force_fail_every);
       VT_HIP(hipGetLastError());
     }
-    if (merged > 0) VT_TRY(capacity_pass(nullptr, n, k, stream_last && nretry == merged));
-    // radius failures retry at 2k; capacity overflows go to the large kernel
-    VT_TRY(launch_compact_failed(status.get<uint8_t>(), nullptr, n, cur, ctx->d_counter,
-                                 (1u << VOTESS_CELL_RADIUS) | (1u << VOTESS_CELL_CAPACITY), ctx->ws, st));
-    VT_HIP(hipMemcpyAsync(&nfail, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
-    if (P.kmodel) {
-      unsigned long long v = 0;
-      VT_HIP(hipMemcpyAsync(&v, counters.get<unsigned long long>() + 5, 8, hipMemcpyDeviceToHost, st));
-      VT_HIP(hipStreamSynchronize(st));
-      entered = (int64_t)v;
-    } else {
-      VT_TRY(record_pass(n, merged));
+    // radius failures retry at 2k; capacity overflows go to the large kernel.
+    // The clip counts both: where it counted none, the statuses need no look.
+    if (P.force_fail_every > 0 || rep.clip[kCapacityCounter] + rep.clip[kRadiusCounter] > 0) {
+      if (merged > 0) VT_TRY(capacity_pass(nullptr, n, k, stream_last && nretry == merged));
+      VT_TRY(launch_compact_failed(status.get<uint8_t>(), nullptr, n, cur, ctx->d_counter,
+                                   (1u << VOTESS_CELL_RADIUS) | (1u << VOTESS_CELL_CAPACITY), ctx->ws, st));
+      VT_TRY(report());
+      nfail = rep.count;
     }
+    if (P.kmodel)
+      entered = (int64_t)rep.clip[5];
+    else
+      record_pass(n, merged);
   }
   // ---- GPU retry ladder: cells whose radius test failed retry at doubled k
   for (int r = merged; r < nretry && nfail > 0 && P.force_fail_every == 0 && k < kMaxK; ++r) {
@@ -678,12 +695,12 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
     all_listed = false;
     VT_TRY(alloc_buf(ctx, knn, (size_t)nfail * k * 4));
     {
-      Timer T(st, &S.ms_knn);
+      Timer T(timers, st, &S.ms_knn);
       VT_TRY(launch_knn(ctx, sorted.p, dtype, n, GD, cell_start.get<int32_t>(), SG, cur, nfail, k, dist,
                         knn.get<int32_t>(), st));
     }
     {
-      Timer T(st, &S.ms_clip);
+      Timer T(timers, st, &S.ms_clip);
       ClipLaunch c = base;
       c.cells = cur;
       c.nc = nfail;
@@ -696,29 +713,27 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
     const int cells_in = nfail;
     VT_TRY(launch_compact_failed(status.get<uint8_t>(), cur, nfail, nxt, ctx->d_counter,
                                  (1u << VOTESS_CELL_RADIUS) | (1u << VOTESS_CELL_CAPACITY), ctx->ws, st));
-    VT_HIP(hipMemcpyAsync(&nfail, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
-    VT_TRY(record_pass(cells_in, 0));
+    VT_TRY(report());
+    nfail = rep.count;
+    record_pass(cells_in, 0);
     std::swap(cur, nxt);
   }
   // capacity overflows that no retry revisited (no retries left, or k at its maximum)
   if (nfail > 0 && P.force_fail_every == 0) VT_TRY(capacity_pass(cur, nfail, k, stream_last));
   // ---- everything not certified goes to the host
   int nhost = 0;
-  if (n > 0) {
+  if (nfail > 0 || rep.clip[1] > 0) {  // (rep is from after the last clip, unless cells are left)
     VT_TRY(launch_compact_failed(status.get<uint8_t>(), nullptr, n, nxt, ctx->d_counter,
                                  (1u << VOTESS_CELL_RADIUS) | (1u << VOTESS_CELL_CAPACITY) |
                                      (1u << VOTESS_CELL_UNRESOLVED), ctx->ws,
                                  st));
-    VT_HIP(hipMemcpyAsync(&nhost, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
-    unsigned long long cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    VT_HIP(hipMemcpyAsync(cnt, counters.p, sizeof(cnt), hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
-    S.unresolved_cells = (int64_t)cnt[1];
-    S.rechecks = (int64_t)cnt[0];
-    S.refined_cells = (int64_t)cnt[3];
-    S.streamed_cells = (int64_t)cnt[4];
+    VT_TRY(report());
+    nhost = rep.count;
   }
+  S.unresolved_cells = (int64_t)rep.clip[1];
+  S.rechecks = (int64_t)rep.clip[0];
+  S.refined_cells = (int64_t)rep.clip[3];
+  S.streamed_cells = (int64_t)rep.clip[4];
   // host-fallback cells whose rows exceed the per-cell staging (indices into
   // long_cells / long_ids)
   std::vector<int> long_rows;
@@ -809,7 +824,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
 
   // ---- a9 assembly
   {
-    Timer T(st, &S.ms_assemble);
+    Timer T(timers, st, &S.ms_assemble);
     Buf row_ptr, col, volume, area, centroid;
     VT_TRY(alloc_buf(ctx, row_ptr, (nn + 1) * 8));
     VT_TRY(alloc_buf(ctx, volume, nn * 8));
@@ -851,6 +866,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
       out->vxyz = (double*)vxyz.release();
       out->vplanes = (int32_t*)vpl.release();
     }
+    T.stop();
     VT_HIP(hipStreamSynchronize(st));
     out->row_ptr = (int64_t*)row_ptr.release();
     out->col = (int32_t*)col.release();
@@ -860,6 +876,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
       out->centroid = (double*)centroid.release();
     }
   }
+  timers.settle();
   S.ms_total = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
   return VOTESS_OK;
 }

@@ -78,6 +78,19 @@ __global__ __launch_bounds__(kCompactBlock) void k_compact_write(const uint8_t* 
   if (take) out[base + __popcll(b & ((1ull << lane) - 1ull))] = id;
 }
 
+__global__ void k_report(uint32_t* __restrict__ err, const int* __restrict__ count,
+                         const unsigned long long* __restrict__ counters, const int64_t* __restrict__ total,
+                         Report* __restrict__ out) {
+  const int t = threadIdx.x;
+  if (t == 0) {
+    out->errors = err ? *err : 0;
+    if (err) *err = 0;
+    out->count = *count;
+    out->total = total ? *total : 0;
+  }
+  if (t < kClipCounters) out->clip[t] = counters ? counters[t] : 0;
+}
+
 __global__ void k_rows_count(const int* __restrict__ nbr_count, const int* __restrict__ perm, int n, int sorted_space,
                              int* __restrict__ counts) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -174,6 +187,15 @@ __global__ void k_vrows_fill(const int* __restrict__ vcount, const double* __res
 
 }  // namespace
 
+votess_status read_report(votess_ctx* ctx, bool errors, const unsigned long long* counters, const int64_t* total,
+                          hipStream_t st, Report& r) {
+  k_report<<<1, 64, 0, st>>>(errors ? ctx->d_err : nullptr, ctx->d_counter, counters, total, (Report*)ctx->h_report);
+  VT_HIP(hipGetLastError());
+  VT_HIP(hipStreamSynchronize(st));
+  r = *(const Report*)ctx->h_report;
+  return VOTESS_OK;
+}
+
 votess_status launch_compact_failed(const uint8_t* status, const int32_t* cells, int nc, int32_t* out_cells,
                                     int32_t* d_count, uint8_t want_status_mask, Workspace& ws, hipStream_t st) {
   if (nc <= 0) {
@@ -208,8 +230,9 @@ votess_status launch_assemble(const int32_t* nbr_count, const int32_t* nbr, int 
       VT_HIP(hipGetLastError());
     }
     VT_TRY(scan_i32_to_i64(counts, n, row_ptr, ws, st));
-    VT_HIP(hipMemcpyAsync(nnz_h, row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
+    Report r;
+    VT_TRY(read_report(ws.ctx, false, nullptr, row_ptr + n, st, r));
+    *nnz_h = r.total;
     ws.used = mark;
     return VOTESS_OK;
   }
@@ -238,8 +261,9 @@ votess_status launch_assemble_vertices(const int32_t* vcount, const double* vert
       VT_HIP(hipGetLastError());
     }
     VT_TRY(scan_i32_to_i64(counts, n, vrow_ptr, ws, st));
-    VT_HIP(hipMemcpyAsync(nv_h, vrow_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
+    Report r;
+    VT_TRY(read_report(ws.ctx, false, nullptr, vrow_ptr + n, st, r));
+    *nv_h = r.total;
     ws.used = mark;
     return VOTESS_OK;
   }

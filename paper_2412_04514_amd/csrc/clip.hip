@@ -1779,7 +1779,9 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       if (lane == 0 && b) atomicAdd(&a.counters[c], (unsigned long long)__popcll(b));
     };
     add(1, fin == VOTESS_CELL_UNRESOLVED);
-    add(2, fin == VOTESS_CELL_CAPACITY);
+    const bool word = !((a.mark >> fin) & 1);  // of this launch, on the cell's status
+    add(kCapacityCounter, word && fin == VOTESS_CELL_CAPACITY);
+    add(kRadiusCounter, word && fin == VOTESS_CELL_RADIUS);
     add(5, streamed);
     add(4, streamed && st == VOTESS_CELL_CERTIFIED);
     if constexpr (RECHECK) {

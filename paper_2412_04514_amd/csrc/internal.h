@@ -70,6 +70,7 @@ struct votess_ctx {
   void* user = nullptr;
   uint32_t* d_err = nullptr;   // device error word
   int* d_counter = nullptr;    // small device scratch counters [16]
+  void* h_report = nullptr;    // pinned host memory that read_report's kernel writes
   votess::Workspace ws;
   int num_cu = 0;
   void* noalloc_scratch = nullptr;  // device address of the static scratch (votess_features_noalloc)
@@ -112,7 +113,8 @@ votess_status launch_knn(votess_ctx* ctx, const void* sorted, votess_dtype dt, i
 // clipping (clip.hip)
 constexpr int kLevels = 3;        // shorter lists whose outcome a clip counts
 constexpr int kLevelCounter = 6;  // their first counter
-constexpr int kClipCounters = kLevelCounter + kLevels;
+constexpr int kCapacityCounter = 2, kRadiusCounter = kLevelCounter + kLevels;
+constexpr int kClipCounters = kRadiusCounter + 1;
 struct ClipLaunch {
   const void* sorted;
   votess_dtype dtype;
@@ -141,7 +143,8 @@ struct ClipLaunch {
   double* r2out = nullptr;       // [rows] R^2 of each certified cell (nullable; an upper bound on the float path)
   unsigned long long* counters;  // [kClipCounters]: rechecks, unresolved, capacity, refined, streamed (certified
                                  // by the stream phase), stream entries, cells not certified by the first
-                                 // level[i] entries of their list -- nullable
+                                 // level[i] entries of their list, radius; statuses as the launch leaves
+                                 // them -- nullable
   int level[kLevels] = {0, 0, 0};  // (0: not counted)
   int own_rows = 1;              // 0: `cells` may name a cell twice with out_by_id
   int stream = 0;                // 1: uncertified cells continue by grid rings
@@ -155,6 +158,19 @@ votess_status launch_clip(const ClipLaunch& a, hipStream_t st);
 // order-preserving; takes nc/256 ints of `ws` for the duration of its kernels
 votess_status launch_compact_failed(const uint8_t* status, const int32_t* cells, int nc, int32_t* out_cells,
                                     int32_t* d_count, uint8_t want_status_mask, Workspace& ws, hipStream_t st);
+
+// What the host needs to know before it goes on (assemble.hip): one kernel
+// writes it to pinned memory and the host waits once, where every value used
+// to take a copy and a wait (a tessellation of 2k points in double: 0.67 ms with
+// those, 0.49 ms).
+struct Report {
+  uint32_t errors;  // the device error word, if asked for; cleared as it is read
+  int count;      // *d_counter (of the last compaction)
+  int64_t total;  // *total, if given
+  unsigned long long clip[kClipCounters];  // counters, if given
+};
+votess_status read_report(votess_ctx* ctx, bool errors, const unsigned long long* counters, const int64_t* total,
+                          hipStream_t st, Report& r);
 
 // CSR assembly (assemble.hip)
 // area_sorted / cen_sorted (nullable) travel with their rows into area / centroid.

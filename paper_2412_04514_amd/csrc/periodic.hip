@@ -239,9 +239,9 @@ votess_status tessellate_periodic(votess_ctx* ctx, const void* pts, votess_dtype
     VT_HIP(hipGetLastError());
     VT_TRY(launch_compact_failed(flags.get<uint8_t>(), nullptr, n_ext, cells.get<int>(), ctx->d_counter, 1u << 1,
                                  ctx->ws, st));
-    int nc = 0;
-    VT_HIP(hipMemcpyAsync(&nc, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
+    Report rep;
+    VT_TRY(read_report(ctx, false, nullptr, nullptr, st, rep));
+    const int nc = rep.count;
     if (nc == 0) break;
     // ---- k-NN + clip with the stream phase, large kernel, host fallback
     const int k = 64;
@@ -303,11 +303,15 @@ votess_status tessellate_periodic(votess_ctx* ctx, const void* pts, votess_dtype
     // the cells' statuses are by row t: compact rows, not ids
     DBuf rows, ids2, knn2;
     VT_TRY(rows.alloc(ctx, (size_t)nc * 4));
-    VT_TRY(launch_compact_failed(status.get<uint8_t>(), nullptr, nc, rows.get<int>(), ctx->d_counter,
-                                 1u << VOTESS_CELL_CAPACITY, ctx->ws, st));
+    // (the clip counts the cells that it leaves: none, and no status needs a look)
+    VT_TRY(read_report(ctx, false, counters.get<unsigned long long>(), nullptr, st, rep));
     int ncap = 0;
-    VT_HIP(hipMemcpyAsync(&ncap, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
+    if (rep.clip[kCapacityCounter] > 0) {
+      VT_TRY(launch_compact_failed(status.get<uint8_t>(), nullptr, nc, rows.get<int>(), ctx->d_counter,
+                                   1u << VOTESS_CELL_CAPACITY, ctx->ws, st));
+      VT_TRY(read_report(ctx, false, counters.get<unsigned long long>(), nullptr, st, rep));
+      ncap = rep.count;
+    }
     S.capacity_cells += ncap;
     std::vector<int> rows_h;
     if (ncap > 0) {
@@ -380,15 +384,16 @@ votess_status tessellate_periodic(votess_ctx* ctx, const void* pts, votess_dtype
       VT_HIP(hipStreamSynchronize(st));
     }
     // ---- the rest (still uncertified) on the host
-    VT_TRY(launch_compact_failed(status.get<uint8_t>(), nullptr, nc, rows.get<int>(), ctx->d_counter,
-                                 (1u << VOTESS_CELL_RADIUS) | (1u << VOTESS_CELL_CAPACITY) |
-                                     (1u << VOTESS_CELL_UNRESOLVED),
-                                 ctx->ws, st));
     int nhost = 0;
-    unsigned long long cntr[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    VT_HIP(hipMemcpyAsync(&nhost, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
-    VT_HIP(hipMemcpyAsync(cntr, counters.p, sizeof(cntr), hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
+    if (rep.clip[kCapacityCounter] + rep.clip[kRadiusCounter] + rep.clip[1] > 0) {
+      VT_TRY(launch_compact_failed(status.get<uint8_t>(), nullptr, nc, rows.get<int>(), ctx->d_counter,
+                                   (1u << VOTESS_CELL_RADIUS) | (1u << VOTESS_CELL_CAPACITY) |
+                                       (1u << VOTESS_CELL_UNRESOLVED),
+                                   ctx->ws, st));
+      VT_TRY(read_report(ctx, false, counters.get<unsigned long long>(), nullptr, st, rep));
+      nhost = rep.count;
+    }
+    const unsigned long long* cntr = rep.clip;
     S.rechecks += (int64_t)cntr[0];
     S.refined_cells += (int64_t)cntr[3];
     S.streamed_cells += (int64_t)cntr[4];
@@ -474,8 +479,8 @@ votess_status tessellate_periodic(votess_ctx* ctx, const void* pts, votess_dtype
     VT_HIP(hipGetLastError());
     VT_TRY(launch_compact_failed(done.get<uint8_t>(), nullptr, n, cells.get<int>(), ctx->d_counter, 1u << 0, ctx->ws,
                                  st));
-    VT_HIP(hipMemcpyAsync(&pending, ctx->d_counter, 4, hipMemcpyDeviceToHost, st));
-    VT_HIP(hipStreamSynchronize(st));
+    VT_TRY(read_report(ctx, false, nullptr, nullptr, st, rep));
+    pending = rep.count;
     if (pending > 0 && w >= kMaxPeriods * lmin)
       return fail(VOTESS_EUNRESOLVED, "periodic: %d cells reach farther than %d periods", pending, kMaxPeriods);
     w *= 2.0;
