@@ -753,7 +753,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
     std::vector<HostCellOut> res;
     host_fallback_cells(rec.data(), dtype, n, grid, cs.data(), ids.data(), nhost, wantv, wantf, P.host_threads,
                         res);
-    // write back per cell (small transfers, batched through host staging)
+    // write back: one upload, one kernel
     std::vector<int32_t> h_cnt(nhost), h_nbr((size_t)nhost * kMaxNbr, -1), h_vc;
     std::vector<double> h_vol(nhost), h_v, h_area, h_cen;
     if (wantf) {
@@ -793,31 +793,28 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
     }
     long_cells.swap(res);
     long_ids = ids;
-    for (int i = 0; i < nhost; ++i) {  // contiguous id runs go in one copy each
-      int e = i;
-      while (e + 1 < nhost && ids[e + 1] == ids[e] + 1) ++e;
-      const int s0 = ids[i], len = e - i + 1;
-      VT_HIP(hipMemcpyAsync(nbr_count.get<int32_t>() + s0, &h_cnt[i], len * 4, hipMemcpyHostToDevice, st));
-      VT_HIP(hipMemcpyAsync(nbr.get<int32_t>() + (size_t)s0 * kMaxNbr, &h_nbr[(size_t)i * kMaxNbr],
-                            (size_t)len * kMaxNbr * 4, hipMemcpyHostToDevice, st));
-      VT_HIP(hipMemcpyAsync(vol.get<double>() + s0, &h_vol[i], len * 8, hipMemcpyHostToDevice, st));
-      VT_HIP(hipMemcpyAsync(status.get<uint8_t>() + s0, &h_st[i], len, hipMemcpyHostToDevice, st));
-      if (wantf) {
-        VT_HIP(hipMemcpyAsync(farea.get<double>() + (size_t)s0 * kMaxNbr, &h_area[(size_t)i * kMaxNbr],
-                              (size_t)len * kMaxNbr * 8, hipMemcpyHostToDevice, st));
-        VT_HIP(hipMemcpyAsync(fcen.get<double>() + (size_t)s0 * 3, &h_cen[(size_t)i * 3], (size_t)len * 3 * 8,
-                              hipMemcpyHostToDevice, st));
-      }
-      if (wantv) {
-        VT_HIP(hipMemcpyAsync(vcount.get<int32_t>() + s0, &h_vc[i], len * 4, hipMemcpyHostToDevice, st));
-        VT_HIP(hipMemcpyAsync(verts.get<double>() + (size_t)s0 * kMaxVert * 3, &h_v[(size_t)i * kMaxVert * 3],
-                              (size_t)len * kMaxVert * 3 * 8, hipMemcpyHostToDevice, st));
-        VT_HIP(hipMemcpyAsync(vplanes.get<int32_t>() + (size_t)s0 * kMaxVert * 3, &h_vp[(size_t)i * kMaxVert * 3],
-                              (size_t)len * kMaxVert * 3 * 4, hipMemcpyHostToDevice, st));
-      }
-      i = e;
+    RowsIn hr;
+    hr.at = ids.data();
+    hr.status = h_st.data();
+    hr.count = h_cnt.data();
+    hr.nbr = h_nbr.data();
+    hr.volume = h_vol.data();
+    RowsOut ro{status.get<uint8_t>(), nbr_count.get<int32_t>(), nbr.get<int32_t>(), vol.get<double>()};
+    if (wantf) {
+      hr.area = h_area.data();
+      hr.centroid = h_cen.data();
+      ro.area = farea.get<double>();
+      ro.centroid = fcen.get<double>();
     }
-    VT_HIP(hipStreamSynchronize(st));
+    if (wantv) {
+      hr.vcount = h_vc.data();
+      hr.verts = h_v.data();
+      hr.vplanes = h_vp.data();
+      ro.vcount = vcount.get<int32_t>();
+      ro.verts = verts.get<double>();
+      ro.vplanes = vplanes.get<int32_t>();
+    }
+    VT_TRY(put_host_rows(ctx, hr, nhost, kMaxNbr, kMaxVert, ro, st));
     S.fallback_cells = nhost;
     S.ms_fallback = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   }

@@ -5,6 +5,9 @@
 // vertices follow.
 #include "internal.h"
 
+#include <cstring>
+#include <vector>
+
 namespace votess {
 namespace {
 
@@ -76,6 +79,29 @@ __global__ __launch_bounds__(kCompactBlock) void k_compact_write(const uint8_t* 
   int base = boff[blockIdx.x];
   for (int v = 0; v < w; ++v) base += wsum[v];
   if (take) out[base + __popcll(b & ((1ull << lane) - 1ull))] = id;
+}
+
+// One wave per row.
+__global__ __launch_bounds__(64) void k_put_rows(RowsIn h, int max_nbr, int max_vert, RowsOut out) {
+  const size_t t = blockIdx.x, r = h.at[t];
+  const int l = threadIdx.x;
+  if (l == 0) {
+    out.status[r] = h.status[t];
+    out.count[r] = h.count[t];
+    out.volume[r] = h.volume[t];
+    if (h.r2) out.r2[r] = h.r2[t];
+    if (h.vcount) out.vcount[r] = h.vcount[t];
+  }
+  if (h.centroid && l < 3) out.centroid[r * 3 + l] = h.centroid[t * 3 + l];
+  for (int e = l; e < max_nbr; e += 64) {
+    out.nbr[r * max_nbr + e] = h.nbr[t * max_nbr + e];
+    if (h.area) out.area[r * max_nbr + e] = h.area[t * max_nbr + e];
+  }
+  if (h.verts)
+    for (int e = l; e < 3 * max_vert; e += 64) {
+      out.verts[r * 3 * max_vert + e] = h.verts[t * 3 * max_vert + e];
+      out.vplanes[r * 3 * max_vert + e] = h.vplanes[t * 3 * max_vert + e];
+    }
 }
 
 __global__ void k_report(uint32_t* __restrict__ err, const int* __restrict__ count,
@@ -186,6 +212,59 @@ __global__ void k_vrows_fill(const int* __restrict__ vcount, const double* __res
 }
 
 }  // namespace
+
+votess_status put_rows(const RowsIn& in, int rows, int max_nbr, int max_vert, const RowsOut& out, hipStream_t st) {
+  if (rows <= 0) return VOTESS_OK;
+  k_put_rows<<<(unsigned)rows, 64, 0, st>>>(in, max_nbr, max_vert, out);
+  VT_HIP(hipGetLastError());
+  return VOTESS_OK;
+}
+
+votess_status put_host_rows(votess_ctx* ctx, const RowsIn& h, int rows, int max_nbr, int max_vert, const RowsOut& out,
+                            hipStream_t st) {
+  if (rows <= 0) return VOTESS_OK;
+  // one upload of all arrays, each at a multiple of 16 bytes
+  size_t bytes = 0;
+  auto place = [&](const void* p, size_t len) {
+    const size_t at = bytes;
+    if (p) bytes += (len + 15) / 16 * 16;
+    return at;
+  };
+  const size_t R = rows, N = R * max_nbr, V = R * max_vert * 3;
+  const size_t len[11] = {R * 4, R, R * 4, N * 4, R * 8, R * 8, N * 8, R * 24, R * 4, V * 8, V * 4};
+  const void* src[11] = {h.at,   h.status,   h.count,  h.nbr,   h.volume, h.r2,
+                         h.area, h.centroid, h.vcount, h.verts, h.vplanes};
+  size_t off[11];
+  for (int i = 0; i < 11; ++i) off[i] = place(src[i], len[i]);
+  std::vector<char> host(bytes);
+  for (int i = 0; i < 11; ++i)
+    if (src[i]) std::memcpy(host.data() + off[i], src[i], len[i]);
+  char* dev = (char*)dev_alloc(ctx, bytes);
+  if (!dev) return fail(VOTESS_ENOMEM, "rows from the host: %zu bytes", bytes);
+  RowsIn d;
+  auto at = [&](int i) { return src[i] ? (const void*)(dev + off[i]) : nullptr; };
+  d.at = (const int32_t*)at(0);
+  d.status = (const uint8_t*)at(1);
+  d.count = (const int32_t*)at(2);
+  d.nbr = (const int32_t*)at(3);
+  d.volume = (const double*)at(4);
+  d.r2 = (const double*)at(5);
+  d.area = (const double*)at(6);
+  d.centroid = (const double*)at(7);
+  d.vcount = (const int32_t*)at(8);
+  d.verts = (const double*)at(9);
+  d.vplanes = (const int32_t*)at(10);
+  hipError_t e = hipMemcpyAsync(dev, host.data(), bytes, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) {
+    k_put_rows<<<(unsigned)rows, 64, 0, st>>>(d, max_nbr, max_vert, out);
+    e = hipGetLastError();
+  }
+  const hipError_t w = hipStreamSynchronize(st);  // before the staging goes
+  dev_free(ctx, dev);
+  if (e == hipSuccess) e = w;
+  if (e != hipSuccess) return fail(VOTESS_EHIP, "rows from the host: %s", hipGetErrorString(e));
+  return VOTESS_OK;
+}
 
 votess_status read_report(votess_ctx* ctx, bool errors, const unsigned long long* counters, const int64_t* total,
                           hipStream_t st, Report& r) {

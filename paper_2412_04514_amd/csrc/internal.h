@@ -172,6 +172,39 @@ struct Report {
 votess_status read_report(votess_ctx* ctx, bool errors, const unsigned long long* counters, const int64_t* total,
                           hipStream_t st, Report& r);
 
+// Rows of cells that were built apart (on the host, or by the large kernel),
+// put in their places by one kernel: row t of each array goes to row at[t]
+// (assemble.hip).  Null arrays are left out.
+struct RowsIn {
+  const int32_t* at;
+  const uint8_t* status;
+  const int32_t* count;
+  const int32_t* nbr;  // [rows, max_nbr], and the areas
+  const double* volume;
+  const double* r2 = nullptr;
+  const double* area = nullptr;
+  const double* centroid = nullptr;  // [rows, 3]
+  const int32_t* vcount = nullptr;
+  const double* verts = nullptr;  // [rows, max_vert, 3], and the planes
+  const int32_t* vplanes = nullptr;
+};
+struct RowsOut {
+  uint8_t* status;
+  int32_t* count;
+  int32_t* nbr;
+  double* volume;
+  double* r2 = nullptr;
+  double* area = nullptr;
+  double* centroid = nullptr;
+  int32_t* vcount = nullptr;
+  double* verts = nullptr;
+  int32_t* vplanes = nullptr;
+};
+votess_status put_rows(const RowsIn& in, int rows, int max_nbr, int max_vert, const RowsOut& out, hipStream_t st);
+// the same from host memory: one upload; waits for the stream before it returns
+votess_status put_host_rows(votess_ctx* ctx, const RowsIn& h, int rows, int max_nbr, int max_vert, const RowsOut& out,
+                            hipStream_t st);
+
 // CSR assembly (assemble.hip)
 // area_sorted / cen_sorted (nullable) travel with their rows into area / centroid.
 votess_status launch_assemble(const int32_t* nbr_count, const int32_t* nbr, int max_nbr, const double* vol_sorted,
