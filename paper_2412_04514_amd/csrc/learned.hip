@@ -4,10 +4,10 @@
 //
 //  * k_features   12 features per query from its 16-NN list and the grid.
 //  * k_mlp        BF16 MFMA (v_mfma_f32_16x16x16bf16_1k, FP32 accumulate)
-//                 forward pass for 16-sample tiles; in training mode also
-//                 softmax cross-entropy and the backward pass, accumulating
-//                 per-block weight gradients with MFMA (sum over samples
-//                 as the K dimension).  Inference writes the chosen bucket.
+//                 forward pass for 16-sample tiles; writes the chosen bucket.
+//  * k_mlp_grad   the same, with softmax cross-entropy and the backward pass,
+//                 accumulating per-block weight gradients with MFMA (sum over
+//                 samples as the K dimension).
 //  * k_reduce     deterministic fixed-order sum of the per-block partials.
 //  * k_adam       Adam on FP32 master weights.
 //
@@ -30,7 +30,7 @@ constexpr int NF = VOTESS_NFEAT, NH = VOTESS_NHID, NO = VOTESS_NBUCKET;
 constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + NH * NF, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_W2 + NH * NH,
               OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NO * NH, NPARAM = OFF_B3 + NO;
 static_assert(NPARAM == VOTESS_NPARAM, "parameter layout");
-constexpr int kSamplesPerBlock = 64;  // four 16-sample tiles per wave
+constexpr int kSamplesPerBlock = 64;  // four tiles of 16 samples
 __device__ constexpr int kBuckets[VOTESS_NBUCKET] = {8, 12, 16, 24, 32, 48, 64};
 }  // namespace votess
 
@@ -182,269 +182,289 @@ struct MlpArgs {
   float* logits;    // forward: [nb][NO] (nullable)
 };
 
-// mode 0: forward (logits and / or bucket), 1: forward + backward partials
-template <int MODE>
-__global__ __launch_bounds__(64) void k_mlp(MlpArgs a) {
-  const int l = threadIdx.x;
-  const int r = l & 15, g4 = l >> 4;  // A/B: row / column r, k-group g4; D: row 4 g4 + i, column r
-  __shared__ unsigned short hs[16 * NH];  // activations / signals in [sample][unit] (bf16 bits)
-  __shared__ float ps[16 * 16];           // logits -> probabilities [sample][output]
-  const float* th = a.theta;
-  // weights as bf16 operands
-  bf16x4 W1B[4], W2B[4][4], W3B[4], W3T[4], W2T[4][4];
-  for (int nt = 0; nt < 4; ++nt) {  // layer 1: B[k=f][n=u] = W1[u][f]
-    float w[4];
-    for (int i = 0; i < 4; ++i) {
-      const int f = 4 * g4 + i;
-      w[i] = f < NF ? th[OFF_W1 + (16 * nt + r) * NF + f] : 0.0f;
-    }
-    W1B[nt] = pack4(w[0], w[1], w[2], w[3]);
-  }
-  for (int kt = 0; kt < 4; ++kt)
-    for (int nt = 0; nt < 4; ++nt) {  // layer 2: B[k=u1][n=u2] = W2[u2][u1]
-      float w[4], wt[4];
-      for (int i = 0; i < 4; ++i) {
-        w[i] = th[OFF_W2 + (16 * nt + r) * NH + 16 * kt + 4 * g4 + i];
-        wt[i] = th[OFF_W2 + (16 * kt + 4 * g4 + i) * NH + 16 * nt + r];  // backward: B[k=u2][n=u1] = W2[u2][u1]
-      }
-      W2B[kt][nt] = pack4(w[0], w[1], w[2], w[3]);
-      W2T[kt][nt] = pack4(wt[0], wt[1], wt[2], wt[3]);
-    }
-  for (int kt = 0; kt < 4; ++kt) {  // layer 3: B[k=u][n=o] = W3[o][u]
-    float w[4];
+// Orders the LDS accesses of one wave.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Weight fragments (bf16 operands of a wave's lane): layer 1 B[k=f][n=u] =
+// W1[u][f], layer 2 B[k=u1][n=u2] = W2[u2][u1], layer 3 B[k=u][n=o] = W3[o][u];
+// backward B[k=o][n=u] = W3[o][u] and B[k=u2][n=u1] = W2[u2][u1].
+constexpr int kFragW1 = 0, kFragW2 = 4, kFragW3 = 20, kFragForward = 24, kFragW3T = 24, kFragW2T = 28, kFrags = 44;
+__device__ __forceinline__ bf16x4 weight_frag(const float* __restrict__ th, int f, int r, int g4) {
+  float w[4];
+  if (f < kFragW2) {
+    const int nt = f - kFragW1;
+    for (int i = 0; i < 4; ++i) w[i] = 4 * g4 + i < NF ? th[OFF_W1 + (16 * nt + r) * NF + 4 * g4 + i] : 0.0f;
+  } else if (f < kFragW3) {
+    const int kt = (f - kFragW2) >> 2, nt = (f - kFragW2) & 3;
+    for (int i = 0; i < 4; ++i) w[i] = th[OFF_W2 + (16 * nt + r) * NH + 16 * kt + 4 * g4 + i];
+  } else if (f < kFragW3T) {
+    const int kt = f - kFragW3;
     for (int i = 0; i < 4; ++i) w[i] = r < NO ? th[OFF_W3 + r * NH + 16 * kt + 4 * g4 + i] : 0.0f;
-    W3B[kt] = pack4(w[0], w[1], w[2], w[3]);
+  } else if (f < kFragW2T) {
+    const int nt = f - kFragW3T;
+    for (int i = 0; i < 4; ++i) w[i] = 4 * g4 + i < NO ? th[OFF_W3 + (4 * g4 + i) * NH + 16 * nt + r] : 0.0f;
+  } else {
+    const int kt = (f - kFragW2T) >> 2, nt = (f - kFragW2T) & 3;
+    for (int i = 0; i < 4; ++i) w[i] = th[OFF_W2 + (16 * kt + 4 * g4 + i) * NH + 16 * nt + r];
   }
-  for (int nt = 0; nt < 4; ++nt) {  // backward: B[k=o][n=u] = W3[o][u]
-    float w[4];
-    for (int i = 0; i < 4; ++i) {
-      const int o = 4 * g4 + i;
-      w[i] = o < NO ? th[OFF_W3 + o * NH + 16 * nt + r] : 0.0f;
-    }
-    W3T[nt] = pack4(w[0], w[1], w[2], w[3]);
-  }
-  float b1[4], b2[4];
+  return pack4(w[0], w[1], w[2], w[3]);
+}
+
+// A row of four bf16 from [sample][unit], as an A operand
+__device__ __forceinline__ bf16x4 row4(const unsigned short* hs, int r, int kt, int g4) {
+  bf16x4 v;
+  for (int i = 0; i < 4; ++i) v[i] = (short)hs[r * NH + 16 * kt + 4 * g4 + i];
+  return v;
+}
+// and four of a column, as the lane's rows of a D operand
+__device__ __forceinline__ bf16x4 col4(const unsigned short* hs, int r, int nt, int g4) {
+  bf16x4 v;
+  for (int i = 0; i < 4; ++i) v[i] = (short)hs[(4 * g4 + i) * NH + 16 * nt + r];
+  return v;
+}
+
+// Biases and standardisation of a lane.
+struct MlpLane {
+  float b1[4], b2[4], b3, mean[4], sdv[4];
+};
+__device__ __forceinline__ MlpLane mlp_lane(const MlpArgs& a, int r, int g4) {
+  MlpLane p;
   for (int nt = 0; nt < 4; ++nt) {
-    b1[nt] = th[OFF_B1 + 16 * nt + r];
-    b2[nt] = th[OFF_B2 + 16 * nt + r];
+    p.b1[nt] = a.theta[OFF_B1 + 16 * nt + r];
+    p.b2[nt] = a.theta[OFF_B2 + 16 * nt + r];
   }
-  const float b3 = r < NO ? th[OFF_B3 + r] : 0.0f;
-  float mean[4], sdv[4];
+  p.b3 = r < NO ? a.theta[OFF_B3 + r] : 0.0f;
   for (int i = 0; i < 4; ++i) {
     const int f = 4 * g4 + i;
-    mean[i] = f < NF ? a.norm[f] : 0.0f;
-    sdv[i] = f < NF ? a.norm[NF + f] : 1.0f;
+    p.mean[i] = f < NF ? a.norm[f] : 0.0f;
+    p.sdv[i] = f < NF ? a.norm[NF + f] : 1.0f;
   }
+  return p;
+}
 
-  // backward accumulators (D layout)
-  floatx4 gW1[4], gW2[4][4], gW3[4];
+// One wave: the 16 samples from `base` on.  Hidden activations go to hs1 and
+// hs2 in [sample][unit] (bf16 bits; the two may be one buffer), their
+// arguments to z1 and z2, the logits to ps in [sample][output].
+__device__ __forceinline__ void mlp_forward(const MlpArgs& a, int base, const bf16x4* W, const MlpLane& p,
+                                            unsigned short* hs1, unsigned short* hs2, float* ps, floatx4* z1,
+                                            floatx4* z2) {
+  const int l = threadIdx.x & 63;
+  const int r = l & 15, g4 = l >> 4;  // A/B: row / column r, k-group g4; D: row 4 g4 + i, column r
   const floatx4 z4 = {0.f, 0.f, 0.f, 0.f};
-  for (int t = 0; t < 4; ++t) {
-    gW1[t] = z4;
-    gW3[t] = z4;
-    for (int u = 0; u < 4; ++u) gW2[t][u] = z4;
+  // ---- inputs: A layout X[s=r][f=4 g4 + i]
+  float xa[4];
+  const int sa = base + r;
+  for (int i = 0; i < 4; ++i) {
+    const int f = 4 * g4 + i;
+    const float v = (sa < a.nb && f < NF) ? a.feats[(size_t)sa * NF + f] : 0.0f;
+    xa[i] = (f < NF && sa < a.nb) ? bf16_round((v - p.mean[i]) / p.sdv[i]) : 0.0f;
   }
-  float gb1[4] = {0, 0, 0, 0}, gb2[4] = {0, 0, 0, 0}, gb3 = 0.0f, loss = 0.0f;
+  const bf16x4 XA = pack4(xa[0], xa[1], xa[2], xa[3]);
+  // ---- layer 1
+  for (int nt = 0; nt < 4; ++nt) {
+    z1[nt] = mfma(XA, W[kFragW1 + nt], z4);
+    for (int i = 0; i < 4; ++i) {
+      z1[nt][i] += p.b1[nt];
+      hs1[(4 * g4 + i) * NH + 16 * nt + r] = bf16_bits(bf16_round(fmaxf(z1[nt][i], 0.0f)));
+    }
+  }
+  wave_sync();
+  bf16x4 H[4];
+  for (int kt = 0; kt < 4; ++kt) H[kt] = row4(hs1, r, kt, g4);
+  wave_sync();
+  // ---- layer 2
+  for (int nt = 0; nt < 4; ++nt) {
+    floatx4 acc = z4;
+    for (int kt = 0; kt < 4; ++kt) acc = mfma(H[kt], W[kFragW2 + 4 * kt + nt], acc);
+    for (int i = 0; i < 4; ++i) {
+      acc[i] += p.b2[nt];
+      hs2[(4 * g4 + i) * NH + 16 * nt + r] = bf16_bits(bf16_round(fmaxf(acc[i], 0.0f)));
+    }
+    z2[nt] = acc;
+  }
+  wave_sync();
+  for (int kt = 0; kt < 4; ++kt) H[kt] = row4(hs2, r, kt, g4);
+  // ---- layer 3: logits D[s = 4 g4 + i][o = r]
+  floatx4 z3 = z4;
+  for (int kt = 0; kt < 4; ++kt) z3 = mfma(H[kt], W[kFragW3 + kt], z3);
+  for (int i = 0; i < 4; ++i) ps[(4 * g4 + i) * 16 + r] = z3[i] + p.b3;
+  wave_sync();
+}
 
+// Forward (logits and / or bucket): one wave per block, grid-stride over tiles
+// of 16 samples.
+__global__ __launch_bounds__(64) void k_mlp(MlpArgs a) {
+  const int l = threadIdx.x;
+  const int r = l & 15, g4 = l >> 4;
+  __shared__ unsigned short hs[16 * NH];
+  __shared__ float ps[16 * 16];
+  bf16x4 W[kFragForward];
+#pragma unroll
+  for (int f = 0; f < kFragForward; ++f) W[f] = weight_frag(a.theta, f, r, g4);
+  const MlpLane p = mlp_lane(a, r, g4);
   const int tiles_total = (a.nb + 15) / 16;
-  // training: block b owns tiles 4b..4b+3 (its partial sums are per block);
-  // inference: grid-stride over tiles
-  const int t_begin = MODE == 1 ? blockIdx.x * 4 : blockIdx.x;
-  const int t_end = MODE == 1 ? min(tiles_total, blockIdx.x * 4 + 4) : tiles_total;
-  const int t_step = MODE == 1 ? 1 : gridDim.x;
-  for (int tile = t_begin; tile < t_end; tile += t_step) {
-    {
-      const int base = tile * 16;
-      // ---- inputs: A layout X[s=r][f=4 g4 + i]
-      float xa[4];
-      const int sa = base + r;
-      for (int i = 0; i < 4; ++i) {
-        const int f = 4 * g4 + i;
-        const float v = (sa < a.nb && f < NF) ? a.feats[(size_t)sa * NF + f] : 0.0f;
-        xa[i] = (f < NF && sa < a.nb) ? bf16_round((v - mean[i]) / sdv[i]) : 0.0f;
+  for (int tile = blockIdx.x; tile < tiles_total; tile += gridDim.x) {
+    floatx4 z1[4], z2[4];
+    mlp_forward(a, tile * 16, W, p, hs, hs, ps, z1, z2);
+    // ---- softmax per sample (lanes 0..15, one sample each)
+    const int s = tile * 16 + l;
+    if (l < 16 && s < a.nb) {
+      float mx = -FLT_MAX;
+      for (int o = 0; o < NO; ++o) mx = fmaxf(mx, ps[l * 16 + o]);
+      float e[NO], sum = 0.0f;
+      for (int o = 0; o < NO; ++o) {
+        e[o] = expf(ps[l * 16 + o] - mx);
+        sum += e[o];
       }
-      const bf16x4 XA = pack4(xa[0], xa[1], xa[2], xa[3]);
-      // ---- layer 1
-      floatx4 z1[4];
-      bf16x4 H1D[4];
-      for (int nt = 0; nt < 4; ++nt) {
-        z1[nt] = mfma(XA, W1B[nt], z4);
-        float h[4];
-        for (int i = 0; i < 4; ++i) {
-          z1[nt][i] += b1[nt];
-          h[i] = bf16_round(fmaxf(z1[nt][i], 0.0f));
-          hs[(4 * g4 + i) * NH + 16 * nt + r] = bf16_bits(h[i]);
-        }
-        H1D[nt] = pack4(h[0], h[1], h[2], h[3]);
-      }
-      __syncthreads();
-      bf16x4 H1A[4];
-      for (int kt = 0; kt < 4; ++kt) {
-        bf16x4 v;
-        for (int i = 0; i < 4; ++i) v[i] = (short)hs[r * NH + 16 * kt + 4 * g4 + i];
-        H1A[kt] = v;
-      }
-      __syncthreads();
-      // ---- layer 2
-      floatx4 z2[4];
-      bf16x4 H2D[4];
-      for (int nt = 0; nt < 4; ++nt) {
-        floatx4 acc = z4;
-        for (int kt = 0; kt < 4; ++kt) acc = mfma(H1A[kt], W2B[kt][nt], acc);
-        float h[4];
-        for (int i = 0; i < 4; ++i) {
-          acc[i] += b2[nt];
-          h[i] = bf16_round(fmaxf(acc[i], 0.0f));
-          hs[(4 * g4 + i) * NH + 16 * nt + r] = bf16_bits(h[i]);
-        }
-        z2[nt] = acc;
-        H2D[nt] = pack4(h[0], h[1], h[2], h[3]);
-      }
-      __syncthreads();
-      bf16x4 H2A[4];
-      for (int kt = 0; kt < 4; ++kt) {
-        bf16x4 v;
-        for (int i = 0; i < 4; ++i) v[i] = (short)hs[r * NH + 16 * kt + 4 * g4 + i];
-        H2A[kt] = v;
-      }
-      // ---- layer 3: logits D[s = 4 g4 + i][o = r]
-      floatx4 z3 = z4;
-      for (int kt = 0; kt < 4; ++kt) z3 = mfma(H2A[kt], W3B[kt], z3);
-      for (int i = 0; i < 4; ++i) ps[(4 * g4 + i) * 16 + r] = z3[i] + b3;
-      __syncthreads();
-      // ---- softmax per sample (lanes 0..15, one sample each)
-      if (l < 16) {
-        const int s = base + l;
-        float mx = -FLT_MAX;
-        for (int o = 0; o < NO; ++o) mx = fmaxf(mx, ps[l * 16 + o]);
-        float e[NO], sum = 0.0f;
-        for (int o = 0; o < NO; ++o) {
-          e[o] = expf(ps[l * 16 + o] - mx);
-          sum += e[o];
-        }
-        if (MODE == 0 && s < a.nb) {
-          if (a.logits)
-            for (int o = 0; o < NO; ++o) a.logits[(size_t)s * NO + o] = ps[l * 16 + o];
-          if (a.bucket) {
-            float c = 0.0f;
-            int b = NO - 1;
-            for (int o = 0; o < NO - 1; ++o) {
-              c += e[o];
-              if (c >= a.tau * sum) {
-                b = o;
-                break;
-              }
-            }
-            a.bucket[s] = (uint8_t)b;
+      if (a.logits)
+        for (int o = 0; o < NO; ++o) a.logits[(size_t)s * NO + o] = ps[l * 16 + o];
+      if (a.bucket) {
+        float c = 0.0f;
+        int b = NO - 1;
+        for (int o = 0; o < NO - 1; ++o) {
+          c += e[o];
+          if (c >= a.tau * sum) {
+            b = o;
+            break;
           }
         }
-        if (MODE == 1) {
-          const int y = s < a.nb ? a.labels[s] : 0;
-          if (s < a.nb) loss += ((mx + logf(sum)) - ps[l * 16 + y]) * a.inv_batch;
-          for (int o = 0; o < 16; ++o) {
-            float g = 0.0f;
-            if (o < NO && s < a.nb) g = (e[o] / sum - (o == y ? 1.0f : 0.0f)) * a.inv_batch;
-            ps[l * 16 + o] = g;
-          }
-        }
-      }
-      __syncthreads();
-      if (MODE == 1) {
-        // ---- G3 in D layout [s = 4 g4 + i][o = r]; db3; dW3 += G3^T H2
-        float g3[4];
-        for (int i = 0; i < 4; ++i) g3[i] = ps[(4 * g4 + i) * 16 + r];
-        gb3 += g3[0] + g3[1] + g3[2] + g3[3];
-        const bf16x4 G3D = pack4(g3[0], g3[1], g3[2], g3[3]);
-        for (int nt = 0; nt < 4; ++nt) gW3[nt] = mfma(G3D, H2D[nt], gW3[nt]);
-        // G3 in A layout [s = r][o = 4 g4 + i] (rounded)
-        bf16x4 G3A;
-        for (int i = 0; i < 4; ++i) G3A[i] = (short)bf16_bits(ps[r * 16 + 4 * g4 + i]);
-        // ---- dH2 = G3 W3, G2 = dH2 * (z2 > 0)
-        float g2[4][4];
-        for (int nt = 0; nt < 4; ++nt) {
-          const floatx4 dh = mfma(G3A, W3T[nt], z4);
-          for (int i = 0; i < 4; ++i) {
-            g2[nt][i] = z2[nt][i] > 0.0f ? dh[i] : 0.0f;
-            gb2[nt] += g2[nt][i];
-          }
-        }
-        __syncthreads();
-        bf16x4 G2D[4];
-        for (int nt = 0; nt < 4; ++nt) {
-          G2D[nt] = pack4(g2[nt][0], g2[nt][1], g2[nt][2], g2[nt][3]);
-          for (int i = 0; i < 4; ++i) hs[(4 * g4 + i) * NH + 16 * nt + r] = bf16_bits(g2[nt][i]);
-        }
-        // dW2[u2][u1] += G2^T H1
-        for (int mt = 0; mt < 4; ++mt)
-          for (int nt = 0; nt < 4; ++nt) gW2[mt][nt] = mfma(G2D[mt], H1D[nt], gW2[mt][nt]);
-        __syncthreads();
-        bf16x4 G2A[4];
-        for (int kt = 0; kt < 4; ++kt) {
-          bf16x4 v;
-          for (int i = 0; i < 4; ++i) v[i] = (short)hs[r * NH + 16 * kt + 4 * g4 + i];
-          G2A[kt] = v;
-        }
-        // ---- dH1 = G2 W2, G1 = dH1 * (z1 > 0); dW1 += G1^T X
-        bf16x4 XB;  // B layout X[s = 4 g4 + i][f = r]
-        {
-          float xb[4];
-          for (int i = 0; i < 4; ++i) {
-            const int s = base + 4 * g4 + i;
-            const float v = (s < a.nb && r < NF) ? a.feats[(size_t)s * NF + r] : 0.0f;
-            xb[i] = (s < a.nb && r < NF) ? bf16_round((v - a.norm[r]) / a.norm[NF + r]) : 0.0f;
-          }
-          XB = pack4(xb[0], xb[1], xb[2], xb[3]);
-        }
-        for (int nt = 0; nt < 4; ++nt) {
-          floatx4 dh = z4;
-          for (int kt = 0; kt < 4; ++kt) dh = mfma(G2A[kt], W2T[kt][nt], dh);
-          float g1[4];
-          for (int i = 0; i < 4; ++i) {
-            g1[i] = z1[nt][i] > 0.0f ? dh[i] : 0.0f;
-            gb1[nt] += g1[i];
-          }
-          gW1[nt] = mfma(pack4(g1[0], g1[1], g1[2], g1[3]), XB, gW1[nt]);
-        }
-        __syncthreads();
+        a.bucket[s] = (uint8_t)b;
       }
     }
-  }
-  if (MODE == 1) {
-    float* out = a.partial + (size_t)blockIdx.x * (NPARAM + 1);
-    // weights: D layout rows 4 g4 + i, column r
-    for (int mt = 0; mt < 4; ++mt)
-      for (int i = 0; i < 4; ++i) {
-        const int u = 16 * mt + 4 * g4 + i;
-        if (r < NF) out[OFF_W1 + u * NF + r] = gW1[mt][i];
-        for (int nt = 0; nt < 4; ++nt) out[OFF_W2 + u * NH + 16 * nt + r] = gW2[mt][nt][i];
-      }
-    for (int nt = 0; nt < 4; ++nt)
-      for (int i = 0; i < 4; ++i) {
-        const int o = 4 * g4 + i;
-        if (o < NO) out[OFF_W3 + o * NH + 16 * nt + r] = gW3[nt][i];
-      }
-    // biases: reduce over the four row groups
-    for (int nt = 0; nt < 4; ++nt) {
-      float v1 = gb1[nt], v2 = gb2[nt];
-      v1 += __shfl_xor(v1, 16, 64);
-      v1 += __shfl_xor(v1, 32, 64);
-      v2 += __shfl_xor(v2, 16, 64);
-      v2 += __shfl_xor(v2, 32, 64);
-      if (g4 == 0) {
-        out[OFF_B1 + 16 * nt + r] = v1;
-        out[OFF_B2 + 16 * nt + r] = v2;
-      }
-    }
-    float v3 = gb3;
-    v3 += __shfl_xor(v3, 16, 64);
-    v3 += __shfl_xor(v3, 32, 64);
-    if (g4 == 0 && r < NO) out[OFF_B3 + r] = v3;
-    float ls = loss;
-    for (int o = 1; o < 64; o <<= 1) ls += __shfl_xor(ls, o, 64);
-    if (l == 0) out[NPARAM] = ls;
+    wave_sync();
   }
 }
 
+// Forward and backward of 64 samples per block, with the block's partial sums
+// of gradient and loss.  Bound by latency: a batch of 8192 makes 128 blocks, one
+// for every second CU.  So four waves take a tile of 16 samples each, share the
+// making of the weight fragments through LDS, and then each sums a quarter of
+// the gradient over the four tiles in their order.  8192 samples: 13 us (one wave
+// alone over the four tiles: 21 us).
+__global__ __launch_bounds__(256) void k_mlp_grad(MlpArgs a) {
+  constexpr int T = 4;  // tiles and waves
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int r = l & 15, g4 = l >> 4;
+  __shared__ unsigned short hs1[T][16 * NH], hs2[T][16 * NH], hsg[T][16 * NH];  // [sample][unit] (bf16 bits)
+  __shared__ float ps[T][16 * 16];  // logits -> signals [sample][output]
+  // signals of the hidden layers, by layer, tile, fragment, row and lane; the
+  // weight fragments before that
+  __shared__ float sig[2][T][4][4][64];
+  __shared__ bf16x4 xb_[T][64];
+  __shared__ float ent[T][16];  // cross entropy per sample
+  static_assert(sizeof(sig) >= kFrags * 64 * sizeof(bf16x4), "the weight fragments fit where the signals go");
+  bf16x4* frag = (bf16x4*)&sig[0][0][0][0][0];
+#pragma unroll
+  for (int f = w; f < kFrags; f += T) frag[f * 64 + l] = weight_frag(a.theta, f, r, g4);
+  const MlpLane p = mlp_lane(a, r, g4);
+  __syncthreads();
+  bf16x4 W[kFrags];
+#pragma unroll
+  for (int f = 0; f < kFrags; ++f) W[f] = frag[f * 64 + l];
+  __syncthreads();
+  const floatx4 z4 = {0.f, 0.f, 0.f, 0.f};
+  const int tiles = min(T, (a.nb + 15) / 16 - (int)blockIdx.x * T);
+  if (w < tiles) {
+    const int base = ((int)blockIdx.x * T + w) * 16;
+    float* q = ps[w];
+    floatx4 z1[4], z2[4];
+    mlp_forward(a, base, W, p, hs1[w], hs2[w], q, z1, z2);
+    // ---- softmax per sample (lanes 0..15, one sample each)
+    if (l < 16) {
+      const int s = base + l;
+      float mx = -FLT_MAX;
+      for (int o = 0; o < NO; ++o) mx = fmaxf(mx, q[l * 16 + o]);
+      float e[NO], sum = 0.0f;
+      for (int o = 0; o < NO; ++o) {
+        e[o] = expf(q[l * 16 + o] - mx);
+        sum += e[o];
+      }
+      const int y = s < a.nb ? a.labels[s] : 0;
+      if (s < a.nb) ent[w][l] = (mx + logf(sum)) - q[l * 16 + y];
+      for (int o = 0; o < 16; ++o) {
+        float g = 0.0f;
+        if (o < NO && s < a.nb) g = (e[o] / sum - (o == y ? 1.0f : 0.0f)) * a.inv_batch;
+        q[l * 16 + o] = g;
+      }
+    }
+    wave_sync();
+    // ---- G3 in A layout [s = r][o = 4 g4 + i] (rounded)
+    bf16x4 G3A;
+    for (int i = 0; i < 4; ++i) G3A[i] = (short)bf16_bits(q[r * 16 + 4 * g4 + i]);
+    // ---- dH2 = G3 W3, G2 = dH2 * (z2 > 0)
+    for (int nt = 0; nt < 4; ++nt) {
+      const floatx4 dh = mfma(G3A, W[kFragW3T + nt], z4);
+      for (int i = 0; i < 4; ++i) {
+        const float g = z2[nt][i] > 0.0f ? dh[i] : 0.0f;
+        sig[1][w][nt][i][l] = g;
+        hsg[w][(4 * g4 + i) * NH + 16 * nt + r] = bf16_bits(g);
+      }
+    }
+    wave_sync();
+    bf16x4 G2A[4];
+    for (int kt = 0; kt < 4; ++kt) G2A[kt] = row4(hsg[w], r, kt, g4);
+    // ---- dH1 = G2 W2, G1 = dH1 * (z1 > 0)
+    for (int nt = 0; nt < 4; ++nt) {
+      floatx4 dh = z4;
+      for (int kt = 0; kt < 4; ++kt) dh = mfma(G2A[kt], W[kFragW2T + 4 * kt + nt], dh);
+      for (int i = 0; i < 4; ++i) sig[0][w][nt][i][l] = z1[nt][i] > 0.0f ? dh[i] : 0.0f;
+    }
+    float xb[4];  // B layout X[s = 4 g4 + i][f = r]
+    for (int i = 0; i < 4; ++i) {
+      const int s = base + 4 * g4 + i;
+      const float v = (s < a.nb && r < NF) ? a.feats[(size_t)s * NF + r] : 0.0f;
+      xb[i] = (s < a.nb && r < NF) ? bf16_round((v - a.norm[r]) / a.norm[NF + r]) : 0.0f;
+    }
+    xb_[w][l] = pack4(xb[0], xb[1], xb[2], xb[3]);
+  }
+  __syncthreads();
+  // ---- gradients, in D layout: wave w sums rows 16 w ... of W1 and W2, columns
+  // 16 w ... of W3, and (wave 0) the output biases and the loss
+  floatx4 gW1 = z4, gW2[4] = {z4, z4, z4, z4}, gW3 = z4;
+  float gb1 = 0.0f, gb2 = 0.0f, gb3 = 0.0f, loss = 0.0f;
+  for (int t = 0; t < tiles; ++t) {
+    float g1[4], g2[4], g3[4];
+    for (int i = 0; i < 4; ++i) {
+      g1[i] = sig[0][t][w][i][l];
+      g2[i] = sig[1][t][w][i][l];
+      g3[i] = ps[t][(4 * g4 + i) * 16 + r];
+      gb1 += g1[i];
+      gb2 += g2[i];
+    }
+    gb3 += g3[0] + g3[1] + g3[2] + g3[3];
+    gW3 = mfma(pack4(g3[0], g3[1], g3[2], g3[3]), col4(hs2[t], r, w, g4), gW3);
+    const bf16x4 G2D = pack4(g2[0], g2[1], g2[2], g2[3]);
+    for (int nt = 0; nt < 4; ++nt) gW2[nt] = mfma(G2D, col4(hs1[t], r, nt, g4), gW2[nt]);
+    gW1 = mfma(pack4(g1[0], g1[1], g1[2], g1[3]), xb_[t][l], gW1);
+    const int s = ((int)blockIdx.x * T + t) * 16 + l;
+    if (l < 16 && s < a.nb) loss += ent[t][l] * a.inv_batch;
+  }
+  float* out = a.partial + (size_t)blockIdx.x * (NPARAM + 1);
+  for (int i = 0; i < 4; ++i) {
+    const int u = 16 * w + 4 * g4 + i, o = 4 * g4 + i;
+    if (r < NF) out[OFF_W1 + u * NF + r] = gW1[i];
+    for (int nt = 0; nt < 4; ++nt) out[OFF_W2 + u * NH + 16 * nt + r] = gW2[nt][i];
+    if (o < NO) out[OFF_W3 + o * NH + 16 * w + r] = gW3[i];
+  }
+  // biases: reduce over the four row groups
+  auto rows = [](float v) {
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
+  };
+  gb1 = rows(gb1);
+  gb2 = rows(gb2);
+  gb3 = rows(gb3);
+  if (g4 == 0) {
+    out[OFF_B1 + 16 * w + r] = gb1;
+    out[OFF_B2 + 16 * w + r] = gb2;
+    if (w == 0 && r < NO) out[OFF_B3 + r] = gb3;
+  }
+  for (int o = 1; o < 64; o <<= 1) loss += __shfl_xor(loss, o, 64);
+  if (threadIdx.x == 0) out[NPARAM] = loss;
+}
 
 // Fixed-order sum of per-block partials: out[p] = sum_b partial[b][p], and the
 // same to the caller's buffers (nullable): the gradient and, last, the loss.
@@ -566,7 +586,7 @@ votess_status run_choose(votess_kmodel* km, const float* feats, int nq, float ta
   a.logits = logits;
   const int tiles = (nq + 15) / 16;
   const int blocks = std::max(1, std::min(tiles, 256 * 16));
-  k_mlp<0><<<blocks, 64, 0, st>>>(a);
+  k_mlp<<<blocks, 64, 0, st>>>(a);
   VT_HIP(hipGetLastError());
   return VOTESS_OK;
 }
@@ -588,7 +608,7 @@ static votess_status run_grad(votess_kmodel* km, const float* feats, const uint8
   a.nb = nb;
   a.inv_batch = 1.0f / (float)nb;
   a.partial = km->partial;
-  k_mlp<1><<<blocks, 64, 0, st>>>(a);
+  k_mlp_grad<<<blocks, 256, 0, st>>>(a);
   VT_HIP(hipGetLastError());
   k_reduce<<<(NPARAM + 1 + 63) / 64, 64, 0, st>>>(km->partial, blocks, km->grads, grads, loss);
   VT_HIP(hipGetLastError());
