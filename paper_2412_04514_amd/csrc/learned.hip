@@ -8,8 +8,8 @@
 //  * k_mlp_grad   the same, with softmax cross-entropy and the backward pass,
 //                 accumulating per-block weight gradients with MFMA (sum over
 //                 samples as the K dimension).
-//  * k_reduce     deterministic fixed-order sum of the per-block partials.
-//  * k_adam       Adam on FP32 master weights.
+//  * k_reduce     deterministic fixed-order sum of the per-block partials, and
+//                 Adam on FP32 master weights.
 //
 // MFMA operand layout (16x16x16, wave64, lane l, element i = 0..3):
 //   A[m][k]: m = l % 16, k = 4 (l / 16) + i;   B[k][n]: k = 4 (l / 16) + i, n = l % 16
@@ -40,7 +40,6 @@ struct votess_kmodel {
   float* m = nullptr;      // Adam moments
   float* v = nullptr;
   float* norm = nullptr;   // [24]: mean[12], std[12]
-  float* grads = nullptr;  // [NPARAM]
   float* partial = nullptr;
   int partial_blocks = 0;
   int step = 0;
@@ -466,41 +465,42 @@ __global__ __launch_bounds__(256) void k_mlp_grad(MlpArgs a) {
   if (threadIdx.x == 0) out[NPARAM] = loss;
 }
 
-// Fixed-order sum of per-block partials: out[p] = sum_b partial[b][p], and the
-// same to the caller's buffers (nullable): the gradient and, last, the loss.
+// Fixed-order sum of per-block partials, g[p] = sum_b partial[b][p], to the
+// caller's buffers (nullable): the gradient and, last, the loss; with theta, the
+// Adam step of parameter p (bias corrections c1, c2).
 // Waits on loads, one partial after the other if they are added as they come
 // (30 us for 128 blocks): 16 are loaded at a time, then added in order, and
-// one-wave blocks spread the 5448 sums over the chip.
+// one-wave blocks spread the 5448 sums over the chip (6 us).  Adam in a launch of
+// its own: a step of 8192 samples 21.6 us, here 20.0.
 constexpr int kReduceAhead = 16;
-__global__ __launch_bounds__(64) void k_reduce(const float* __restrict__ partial, int blocks, float* __restrict__ out,
-                                               float* __restrict__ grads, float* __restrict__ loss) {
+__global__ __launch_bounds__(64) void k_reduce(const float* __restrict__ partial, int blocks,
+                                               float* __restrict__ grads, float* __restrict__ loss,
+                                               float* __restrict__ theta, float* __restrict__ m,
+                                               float* __restrict__ v, float lr, float c1, float c2) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p > NPARAM) return;
   float acc = 0.0f;
   int b = 0;
   for (; b + kReduceAhead <= blocks; b += kReduceAhead) {
-    float v[kReduceAhead];
+    float w[kReduceAhead];
 #pragma unroll
-    for (int i = 0; i < kReduceAhead; ++i) v[i] = partial[(size_t)(b + i) * (NPARAM + 1) + p];
+    for (int i = 0; i < kReduceAhead; ++i) w[i] = partial[(size_t)(b + i) * (NPARAM + 1) + p];
 #pragma unroll
-    for (int i = 0; i < kReduceAhead; ++i) acc += v[i];
+    for (int i = 0; i < kReduceAhead; ++i) acc += w[i];
   }
   for (; b < blocks; ++b) acc += partial[(size_t)b * (NPARAM + 1) + p];
-  out[p] = acc;
-  if (p < NPARAM && grads) grads[p] = acc;
-  if (p == NPARAM && loss) *loss = acc;
-}
-
-__global__ void k_adam(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
-                       const float* __restrict__ g, float lr, float c1, float c2) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= NPARAM) return;
-  const float gi = g[p];
-  const float mi = 0.9f * m[p] + 0.1f * gi;
-  const float vi = 0.999f * v[p] + 0.001f * gi * gi;
-  m[p] = mi;
-  v[p] = vi;
-  theta[p] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+  if (p == NPARAM) {
+    if (loss) *loss = acc;
+    return;
+  }
+  if (grads) grads[p] = acc;
+  if (theta) {
+    const float mi = 0.9f * m[p] + 0.1f * acc;
+    const float vi = 0.999f * v[p] + 0.001f * acc * acc;
+    m[p] = mi;
+    v[p] = vi;
+    theta[p] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+  }
 }
 
 // Training label of a cell from the method's own run (status and k_needed of
@@ -591,8 +591,9 @@ votess_status run_choose(votess_kmodel* km, const float* feats, int nq, float ta
   return VOTESS_OK;
 }
 
+// (lr > 0: with an Adam step, bias corrections c1 and c2)
 static votess_status run_grad(votess_kmodel* km, const float* feats, const uint8_t* labels, int nb, float* grads,
-                              float* loss, hipStream_t st) {
+                              float* loss, float lr, float c1, float c2, hipStream_t st) {
   const int blocks = (nb + kSamplesPerBlock - 1) / kSamplesPerBlock;
   if (blocks > km->partial_blocks) {
     dev_free(km->ctx, km->partial);
@@ -610,7 +611,8 @@ static votess_status run_grad(votess_kmodel* km, const float* feats, const uint8
   a.partial = km->partial;
   k_mlp_grad<<<blocks, 256, 0, st>>>(a);
   VT_HIP(hipGetLastError());
-  k_reduce<<<(NPARAM + 1 + 63) / 64, 64, 0, st>>>(km->partial, blocks, km->grads, grads, loss);
+  k_reduce<<<(NPARAM + 1 + 63) / 64, 64, 0, st>>>(km->partial, blocks, grads, loss, lr > 0 ? km->theta : nullptr, km->m,
+                                                  km->v, lr, c1, c2);
   VT_HIP(hipGetLastError());
   return VOTESS_OK;
 }
@@ -795,8 +797,7 @@ votess_kmodel* votess_kmodel_create(votess_ctx* ctx, uint64_t seed) {
   km->m = (float*)dev_alloc(ctx, NPARAM * 4);
   km->v = (float*)dev_alloc(ctx, NPARAM * 4);
   km->norm = (float*)dev_alloc(ctx, 2 * NF * 4);
-  km->grads = (float*)dev_alloc(ctx, (NPARAM + 1) * 4);
-  if (!km->theta || !km->m || !km->v || !km->norm || !km->grads) {
+  if (!km->theta || !km->m || !km->v || !km->norm) {
     votess_kmodel_destroy(km);
     fail(VOTESS_ENOMEM, "kmodel_create");
     return nullptr;
@@ -826,7 +827,6 @@ void votess_kmodel_destroy(votess_kmodel* km) {
   dev_free(ctx, km->m);
   dev_free(ctx, km->v);
   dev_free(ctx, km->norm);
-  dev_free(ctx, km->grads);
   dev_free(ctx, km->partial);
   delete km;
 }
@@ -926,7 +926,7 @@ votess_status votess_kmodel_grad(votess_kmodel* km, const float* feats, const ui
   if (nb < 1 || nb >= (1LL << 31) - 1) return fail(VOTESS_EINVAL, "kmodel_grad: bad batch");
   VT_HIP(hipSetDevice(km->ctx->device));
   hipStream_t st = (hipStream_t)stream;
-  return run_grad(km, feats, labels, (int)nb, grads, loss, st);
+  return run_grad(km, feats, labels, (int)nb, grads, loss, 0.0f, 1.0f, 1.0f, st);
 }
 
 votess_status votess_kmodel_train_step(votess_kmodel* km, const float* feats, const uint8_t* labels, int64_t nb,
@@ -935,11 +935,9 @@ votess_status votess_kmodel_train_step(votess_kmodel* km, const float* feats, co
   if (nb < 1 || nb >= (1LL << 31) - 1 || !(lr > 0.0f)) return fail(VOTESS_EINVAL, "kmodel_train_step: bad batch/lr");
   VT_HIP(hipSetDevice(km->ctx->device));
   hipStream_t st = (hipStream_t)stream;
-  VT_TRY(run_grad(km, feats, labels, (int)nb, nullptr, loss, st));
+  const float t = (float)(km->step + 1);
+  VT_TRY(run_grad(km, feats, labels, (int)nb, nullptr, loss, lr, 1.0f - std::pow(0.9f, t), 1.0f - std::pow(0.999f, t), st));
   km->step += 1;
-  const float c1 = 1.0f - std::pow(0.9f, (float)km->step), c2 = 1.0f - std::pow(0.999f, (float)km->step);
-  k_adam<<<(NPARAM + 255) / 256, 256, 0, st>>>(km->theta, km->m, km->v, km->grads, lr, c1, c2);
-  VT_HIP(hipGetLastError());
   return VOTESS_OK;
 }
 
