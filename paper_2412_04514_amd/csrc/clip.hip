@@ -1817,14 +1817,14 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
 // XCDs): launched block b takes logical block (b mod 8) per + b / 8, so each
 // XCD clips a contiguous stretch of grid-sorted cells, whose neighbours its L2
 // then holds.
-// The fast kernels are held to 3 waves per SIMD, as many as their LDS lets a
-// CU hold: with triangles in 16 bits and planes without their offsets a list
+// The kernels are held to 3 waves per SIMD, as many as their LDS lets a CU
+// hold: with triangles in 16 bits and planes without their offsets a list
 // wave takes 13.1 KB (double clip of float points 16.2, of double ones 19.3)
 // and a CU holds 12 (10, 8); with 32-bit triangles and offsets 14.9 (22.1) KB
 // and 10 (7).  Clip times with those and now: 3M clustered points in double
 // 58.9 and 51.1 ms, 16M in float 215.9 and 202.6 ms, 1M uniform 6.99 and 6.39.
 template <typename P, typename R, int L, int TMAX, int PMAX, bool RECHECK, bool STREAM>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TMAX <= 64 ? 3 : 1))) void k_clip(ClipArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_clip(ClipArgs a) {
   constexpr int G = 64 / L;
   const int waves = 64 / a.per;  // that share 64 cells
   const int nblk = clip_blocks(a.nc, a.per, a.rest), per8 = (nblk + 7) / 8;
@@ -1914,9 +1914,14 @@ votess_status run_fast(ClipArgs ca, bool split, hipStream_t st) {
   return VOTESS_OK;
 }
 
+// The large-capacity kernel.  64 planes make 2 * 64 - 4 = 124 vertices at most
+// (a simple polyhedron), so 128 slots hold every cell that the planes let it
+// hold; with 256 a wave takes 24 KB and a SIMD holds 1.5 of them.  Clip of 1.2M
+// filament points with faces, 33,000 of them here: 45.6 ms with 256 slots, 43.3
+// with 128; with 16 lanes per cell 46.6.
 template <typename P, typename R, bool RECHECK>
 votess_status run_large(const ClipArgs& ca, hipStream_t st) {
-  launch_all<P, R, 32, 256, 64, RECHECK>(ca, false, st);
+  launch_all<P, R, 32, 128, 64, RECHECK>(ca, false, st);
   VT_HIP(hipGetLastError());
   return VOTESS_OK;
 }
@@ -1977,8 +1982,6 @@ votess_status launch_clip(const ClipLaunch& a, hipStream_t st) {
     if (a.dtype == VOTESS_F32) return run_fast<float, double, false>(c, split, st);
     return run_fast<double, double, false>(c, split, st);
   }
-  // the large-capacity kernel: 32 lanes per cell (two cells per wave keep its
-  // LDS per workgroup low enough for more than one wave per SIMD)
   if (f32) return run_large<float, float, true>(c, st);
   if (a.dtype == VOTESS_F32) return run_large<float, double, false>(c, st);
   return run_large<double, double, false>(c, st);
