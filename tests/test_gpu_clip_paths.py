@@ -1,0 +1,139 @@
+"""The routes through the clip: list kernel with its state handed to the stream
+kernel or one kernel in place, waves of one cell up to full ones, passes with
+short lists taken as one, the large-capacity kernel up to its 64 planes; and
+k-NN lists of every length against the longest."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import compare_rows, note, volume_errors
+from paper_2412_04514_amd import gen
+
+pytestmark = pytest.mark.gpu
+
+vt = pytest.importorskip("paper_2412_04514_amd")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _sorted(kind, n, dt, seed=31):
+    P = getattr(gen, kind)(n, seed=seed, dtype=dt)
+    cs, perm, srt, grid = vt.grid_sort(torch.from_numpy(P).cuda())
+    return srt, cs, grid
+
+
+def _same_cells(a, b, rows, exact):
+    """Cells certified in both: the same neighbours, and the same volume (exact:
+    bit for bit)."""
+    ok = (a["status"][:rows] == 0) & (b["status"][:rows] == 0)
+    for key in ("nbr_count", "kneeded"):
+        assert torch.equal(a[key][:rows][ok], b[key][:rows][ok]), key
+    na, nb = a["nbr"][:rows][ok].cpu().numpy(), b["nbr"][:rows][ok].cpu().numpy()
+    cnt = a["nbr_count"][:rows][ok].cpu().numpy()
+    for x, y, c in zip(na, nb, cnt):
+        assert np.array_equal(np.sort(x[:c]), np.sort(y[:c]))
+    va, vb = a["volume"][:rows][ok], b["volume"][:rows][ok]
+    if exact:
+        assert torch.equal(va, vb)
+    else:
+        # the same vertices, their corner terms (at most 120, which cancel by up
+        # to R^3 / V, some 1e4 here) summed in another order
+        assert torch.all((va - vb).abs() <= 1e-9 * vb)
+    return ok
+
+
+@pytest.mark.parametrize("kind", ["uniform", "cluster", "filament"])
+@pytest.mark.parametrize("dt,prec", [(np.float32, "f32"), (np.float32, "f64"), (np.float64, "f64")])
+def test_handed_over_and_in_place(kind, dt, prec):
+    # rows of 58 entries hold the state of a cell between the two kernels; with
+    # 57 one kernel does both
+    srt, cs, grid = _sorted(kind, 4000, dt)
+    for k in (8, 48):
+        lists = vt.knn(srt, grid, cs, k, dist=prec)
+        r = {m: vt.clip_cells(srt, lists, k, precision=prec, stream=True, grid=grid, cell_start=cs, max_nbr=m)
+             for m in (57, 58, 64)}
+        ok = _same_cells(r[57], r[58], 4000, exact=False)
+        note(f"  {kind} {prec} k={k}: {int(ok.sum())} cells by both routes")
+        assert int(ok.sum()) > 3900
+        _same_cells(r[58], r[64], 4000, exact=True)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("stream", [False, True])
+def test_waves_of_any_fill(prec, stream):
+    # cells one to a wave, up to eight, and windows of 64 that end anywhere
+    n = 40_000
+    srt, cs, grid = _sorted("cluster", n, np.float32)
+    lists = vt.knn(srt, grid, cs, 16, dist=prec)
+    kw = dict(precision=prec, stream=stream, grid=grid, cell_start=cs)
+    whole = vt.clip_cells(srt, lists, 16, **kw)
+    for nc in (1, 2, 63, 64, 65, 127, 2048, 4097, 16_383, 16_384):
+        cells = torch.arange(n - nc, n, dtype=torch.int32, device="cuda")
+        part = vt.clip_cells(srt, lists[n - nc:].contiguous(), 16, cells=cells, **kw)
+        tail = {key: whole[key][n - nc:n] for key in ("status", "nbr_count", "nbr", "volume", "kneeded")}
+        assert torch.equal(part["status"][:nc], tail["status"]), nc
+        _same_cells(part, tail, nc, exact=True)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("k0,retries", [(8, 1), (8, 3), (16, 2), (24, 1), (32, 1), (32, 2)])
+def test_passes_taken_as_one(k0, retries, prec):
+    P = torch.from_numpy(gen.cluster(30_000, seed=32, dtype=np.float32)).cuda()
+    a = vt.tessellate(P, k0=k0, max_gpu_retries=retries, precision=prec)
+    b = vt.tessellate(P, k0=64, max_gpu_retries=0, precision=prec)
+    assert torch.equal(a.row_ptr, b.row_ptr) and torch.equal(a.col, b.col)
+    # (longer lists than 64 change which phase cuts first, so the rounding)
+    tol = 1e-5 if prec == "f32" else 1e-12
+    assert torch.all((a.volume - b.volume).abs() <= 2 * tol * b.volume)
+    p = a.stats["passes"]
+    ks = [k0 * 2 ** i for i in range(len(p))]
+    assert [x["k"] for x in p] == ks and p[0]["cells"] == len(P)
+    for x, y in zip(p, p[1:]):
+        assert y["cells"] == x["failed"] <= x["cells"]
+
+
+@pytest.mark.parametrize("m", [26, 27, 31, 32, 33, 48, 58, 59, 63, 64])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_cells_of_many_faces(m, prec):
+    # a generator in a shell of m others has m faces and 2 m - 4 vertices
+    rng = np.random.default_rng(m)
+    k = np.arange(m) + 0.5
+    phi, theta = np.arccos(1 - 2 * k / m), np.pi * (1 + 5 ** 0.5) * k
+    shell = 0.5 + 0.1 * np.stack([np.cos(theta) * np.sin(phi), np.sin(theta) * np.sin(phi), np.cos(phi)], 1)
+    shell += 1e-4 * rng.standard_normal(shell.shape)
+    bg = rng.random((2000, 3))
+    P = np.concatenate([[[0.5, 0.5, 0.5]], shell, bg[np.linalg.norm(bg - 0.5, axis=1) > 0.25]]).astype(np.float32)
+    res = vt.tessellate(torch.from_numpy(P).cuda(), k0=64, max_gpu_retries=0, precision=prec)
+    orc = oracle.tessellate(P.astype(np.float64), volume_ld=True)
+    st = res.stats
+    note(f"  shell of {m} {prec}: capacity cells {st['capacity_cells']}, host cells {st['fallback_cells']}")
+    rp, col = res.row_ptr.cpu().numpy(), res.col.cpu().numpy()
+    assert rp[1] - rp[0] == m
+    assert not compare_rows(rp, col, orc)
+    assert not volume_errors(res.volume.cpu().numpy(), orc, prec).viol.any()
+    if m > 32:
+        assert st["capacity_cells"] >= 1  # more planes than the fast kernels hold
+    if m <= 58:
+        assert st["fallback_cells"] == 0  # m planes and, for a while, the six walls
+
+
+@pytest.mark.parametrize("kind", ["uniform", "cluster"])
+@pytest.mark.parametrize("dt,dist", [(np.float32, "f32"), (np.float32, "f64"), (np.float64, "f64")])
+def test_lists_are_prefixes(kind, dt, dist):
+    # (against exact lists elsewhere): each length has lists and lanes of its own
+    n = 5000
+    srt, cs, grid = _sorted(kind, n, dt)
+    long_ = vt.knn(srt, grid, cs, 256, dist=dist)
+    for k in (8, 12, 16, 24, 32, 48, 64, 128):
+        assert torch.equal(vt.knn(srt, grid, cs, k, dist=dist), long_[:, :k].contiguous()), k
+    few = torch.tensor([0, 1, n // 2, n - 1], dtype=torch.int32, device="cuda")
+    assert torch.equal(vt.knn(srt, grid, cs, 24, queries=few, dist=dist), long_[few.long(), :24])
+    # fewer points than the list: the rest is -1
+    srt, cs, grid = _sorted(kind, 20, dt)
+    got = vt.knn(srt, grid, cs, 32, dist=dist)
+    assert torch.all(got[:, 19:] == -1) and torch.all(got[:, :19] >= 0)
