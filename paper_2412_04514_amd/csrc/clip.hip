@@ -1855,7 +1855,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
   clip_group<P, R, L, TMAX, PMAX, RECHECK, STREAM>(a, have ? t_idx : 0, have, resume);
 }
 
-constexpr int kFillWaves = 2048;
+constexpr int kFillWaves = 2048, kRestWaves = 8192;
 
 // takes the marks off again
 __global__ void k_unmark(uint8_t* status, const int* cells, int nc) {
@@ -1875,8 +1875,12 @@ void launch(ClipArgs ca, bool rest, hipStream_t st) {
   // time with full waves, from 2048 and from 4096: 10k clustered points, float
   // 2.87, 2.53 and 2.59 ms; 100k 6.69, 6.08 and 6.21 ms; 8k filament points,
   // double 1.24, 1.14 and 1.28 ms; 8k uniform ones, float 0.26, 0.32 and 0.34.
+  // A launch over the cells that are left finds a tenth to two thirds of them,
+  // so that its waves are filled from four times as many on (10k clustered
+  // points from 2048, 8192 and 16384: 2.57, 2.46 and 2.46 ms; 30k filament
+  // points with faces 0.465, 0.466 and 0.496).
   ca.per = 64 / L;
-  while (ca.per > 1 && ca.nc / ca.per < kFillWaves) ca.per /= 2;
+  while (ca.per > 1 && ca.nc / ca.per < (rest ? kRestWaves : kFillWaves)) ca.per /= 2;
   const int n = clip_blocks(ca.nc, ca.per, rest);
   k_clip<P, R, L, TMAX, PMAX, RECHECK, STREAM><<<(unsigned)(8 * ((n + 7) / 8)), 64, 0, st>>>(ca);
 }
