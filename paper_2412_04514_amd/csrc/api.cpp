@@ -338,6 +338,7 @@ votess_status votess_clip_cells(votess_ctx* ctx, const void* sorted, votess_dtyp
   a.centroid = centroid;
   a.counters = nullptr;
   a.own_rows = !(cells && opts->out_by_id);
+  a.spare_rows = 0;
   a.stream = opts->stream;
   if (opts->stream) {
     if (!opts->grid || !opts->cell_start) return fail(VOTESS_EINVAL, "clip: stream needs grid and cell_start");

@@ -147,6 +147,7 @@ struct ClipLaunch {
                                  // them -- nullable
   int level[kLevels] = {0, 0, 0};  // (0: not counted)
   int own_rows = 1;              // 0: `cells` may name a cell twice with out_by_id
+  int spare_rows = 1;            // 0: rows of nbr of uncertified cells stay as they are
   int stream = 0;                // 1: uncertified cells continue by grid rings
   const int32_t* cell_start = nullptr;
   GridDev grid{};
