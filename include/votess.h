@@ -153,8 +153,8 @@ VOTESS_API int64_t votess_sub_capacity(int64_t n);
 /* ------------------------------------------------------------- k-NN (a4) */
 
 /* The k nearest other points of each query (paper, Summary section: the
- * neighbour search after the grid sort), by a shell-expanding search over the
- * grid.
+ * neighbour search after the grid sort): a seed block of grid cells around the
+ * query, then every row of cells that meets the ball of the k-th distance.
  *   sorted, cell_start, subinfo, sub_start  from votess_grid_sort (the last
  *              two nullable: dense cells are then scanned whole)
  *   queries    [nq] sorted indices, or NULL for all n points (nq = n)
@@ -267,7 +267,8 @@ typedef struct {
   int64_t bucket_cells[8];  /* learned-k: cells per bucket */
   double ms_sort, ms_knn, ms_clip, ms_features, ms_mlp, ms_assemble, ms_fallback, ms_total;
   /* per pass: cells its list left uncertified that went on into the stream
-   * phase (pass_failed counts the cells still uncertified after it) */
+   * phase (pass_failed counts the cells still uncertified after it).  Passes
+   * whose lists hold at most 64 entries run as one; each has its entry here */
   int64_t pass_streamed[VOTESS_MAX_PASSES];
 } votess_stats;
 
