@@ -502,7 +502,7 @@ __global__ __launch_bounds__(256) void k_order_dense(const typename Rec<T>::type
 // same sub-grid and order as k_order_dense, without its barriers.  The bins that
 // bound the central 90% are order statistics of the points' bins, found bit by
 // bit with ballots rather than from a histogram.  Bound by vector instructions
-// (divisions and roots in double): 12M filament points with 166,000 dense cells
+// (divisions and roots in double): 12M filament points with 148,000 dense cells
 // take 0.24 ms, where k_order_dense took 2.1.
 template <typename T, int R>
 __device__ __forceinline__ void order_mid(const typename Rec<T>::type* __restrict__ tmp, int c, int b, int len,
