@@ -41,9 +41,7 @@
 #include "internal.h"
 #include "device_common.h"
 
-#include <algorithm>
 #include <cfloat>
-#include <cmath>
 
 namespace votess {
 namespace {
@@ -74,7 +72,6 @@ struct ClipArgs {
   int kstride;    // entries per list row
   int knn_by_id;  // list row of a cell: its sorted id (else its position in cells)
   double eps;
-  double fscale;   // a power of two that brings the box's extent near 1
   double dmargin;  // applied to d^2 in certificate tests (k-lists built in float)
   int max_nbr, max_vert, out_by_id;
   uint8_t* status;
@@ -391,7 +388,15 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   // whose ball meets the dense cell being scanned (see below)
   constexpr int kReach = TMAX <= 64 ? 48 : TMAX;
   constexpr int RVN = STREAM ? G * kReach : 1;
-  __shared__ float4 reachv[RVN];
+  // (float: centre and radius, one 16-byte read; double: the vertex slot and the
+  // radius, half the LDS of a copy: 3M clustered points 64.2 and 70.4 ms)
+  struct alignas(16) Ball {
+    R x, y, z, r;
+  };
+  constexpr int RVF = STREAM && RECHECK ? G * kReach : 1, RVD = STREAM && !RECHECK ? G * kReach : 1;
+  __shared__ Ball reachv[RVF];
+  __shared__ R reachr[RVD];
+  __shared__ unsigned char reachs[RVD];
   __shared__ unsigned char relD[RVN];
   // stream phase: sub-cell widths of the dense cell being scanned, per group
   constexpr int DG = STREAM ? G * 3 : 1;
@@ -1094,23 +1099,27 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     // the flower box and the reach list leave it out.
     const double dk2in = (double)dk2 * (1.0 - 1e-6);
     const R rlim = dk2in > 0.0 ? (R)(0.5 * sqrt(dk2in) * (1.0 - 1e-6)) : R(-1);
-    // Boxes of candidates are tested in float, relative to the seed, their
-    // bounds widened by gmarg and rounded outward.  The double clip scales what
-    // it turns to float by a power of two that brings the box's extent near 1,
-    // so that no square over- or underflows.
-    const R fsc = RECHECK ? R(1) : (R)a.fscale;
+    // Boxes of candidates, and candidates, are tested in the clip's precision,
+    // relative to the seed; the bounds of boxes are widened by gmarg and, in
+    // float, rounded outward.  (Float tests would lose the double clip points
+    // that cut by less than a float can tell: a cell a thousand times as long as
+    // wide and smaller than 1e-8 of the box lost a fifth of those that cut its
+    // tip by 1e-10 of the cell.)
     struct Box {
-      float x0, x1, y0, y1, z0, z1;
+      R x0, x1, y0, y1, z0, z1;
     };
     auto round_out = [&](double x0, double x1, double y0, double y1, double z0, double z1) -> Box {
-      auto next = [](float f, int up) -> float {  // the next float below (up = -1) or above (+1) f
-        const int b = __float_as_int(f);
-        return f == 0.0f ? up * FLT_MIN : __int_as_float(b + (b < 0 ? -up : up));
-      };
-      auto lo = [&](double v) -> float { const float f = (float)v; return (double)f > v ? next(f, -1) : f; };
-      auto hi = [&](double v) -> float { const float f = (float)v; return (double)f < v ? next(f, 1) : f; };
-      const double f = RECHECK ? 1.0 : (double)fsc;
-      return {lo(x0 * f), hi(x1 * f), lo(y0 * f), hi(y1 * f), lo(z0 * f), hi(z1 * f)};
+      if constexpr (RECHECK) {
+        auto next = [](float f, int up) -> float {  // the next float below (up = -1) or above (+1) f
+          const int b = __float_as_int(f);
+          return f == 0.0f ? up * FLT_MIN : __int_as_float(b + (b < 0 ? -up : up));
+        };
+        auto lo = [&](double v) -> float { const float f = (float)v; return (double)f > v ? next(f, -1) : f; };
+        auto hi = [&](double v) -> float { const float f = (float)v; return (double)f < v ? next(f, 1) : f; };
+        return {lo(x0), hi(x1), lo(y0), hi(y1), lo(z0), hi(z1)};
+      } else {
+        return {x0, x1, y0, y1, z0, z1};
+      }
     };
     // A box that lies inside the list's ball holds list members only: every
     // point in it is closer than the list's last one even after the rounding
@@ -1124,11 +1133,21 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     // meets none of these balls holds no cutting point, and a candidate is
     // tested against these vertices alone.  Rebuilt after a cut; should it not
     // fit, every test passes (reach_all), which costs time only.
-    float4* rv = reachv + (STREAM ? g * kReach : 0);
+    const int rvb = STREAM ? g * kReach : 0;
+    auto ball = [&](int i) -> Ball {
+      if constexpr (RECHECK) {
+        return reachv[rvb + i];
+      } else {
+        const int t = vb + reachs[rvb + i];
+        return {vx[t], vy[t], vz[t], reachr[rvb + i]};
+      }
+    };
     int nrv = 0;
+    R rmax = R(0);  // double clip: the largest |v|
     bool reach_ok = false, reach_all = false;
     auto reach = [&]() {
       int n = 0;
+      if constexpr (!RECHECK) rmax = sqrt(R2);
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         if (L * s >= H) continue;
@@ -1139,10 +1158,14 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         const bool on = tri[vb + t] != kEmpty && r >= rlim;
         const unsigned gbits = gballot(on);
         const int w = n + __popc(gbits & below);
-        // (double positions and radii are rounded to float: 4e-6 covers that)
-        if (on && w < kReach)
-          rv[w] = make_float4((float)(v.x * fsc), (float)(v.y * fsc), (float)(v.z * fsc),
-                              RECHECK ? (float)r : (float)(r * fsc) * (1.0f + 4e-6f));
+        if (on && w < kReach) {
+          if constexpr (RECHECK) {
+            reachv[rvb + w] = {v.x, v.y, v.z, r};
+          } else {
+            reachr[rvb + w] = r;
+            reachs[rvb + w] = (unsigned char)t;
+          }
+        }
         n += __popc(gbits);
       }
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -1150,10 +1173,10 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       nrv = min(n, kReach);
       reach_ok = true;
     };
-    auto meets = [](const Box& b, const float4& v) -> bool {
-      const float gx = fmaxf(0.0f, fmaxf(b.x0 - v.x, v.x - b.x1)), gy = fmaxf(0.0f, fmaxf(b.y0 - v.y, v.y - b.y1)),
-                  gz = fmaxf(0.0f, fmaxf(b.z0 - v.z, v.z - b.z1));
-      return gx * gx + gy * gy + gz * gz <= v.w * v.w;
+    auto meets = [](const Box& b, const Ball& v) -> bool {
+      const R gx = fmax(R(0), fmax(b.x0 - v.x, v.x - b.x1)), gy = fmax(R(0), fmax(b.y0 - v.y, v.y - b.y1)),
+              gz = fmax(R(0), fmax(b.z0 - v.z, v.z - b.z1));
+      return gx * gx + gy * gy + gz * gz <= v.r * v.r;
     };
     // The flower box (of the union of those balls), in coordinates and in grid
     // cells.  Candidates are enumerated inside it, ring by ring of grid cells.
@@ -1236,7 +1259,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       if (in_list_ball(ax - m, bx + m, ay - m, by + m, az - m, bz + m)) return false;
       const Box b = round_out(ax - m, bx + m, ay - m, by + m, az - m, bz + m);
       bool any = reach_all;
-      for (int i = 0; i < nrv; ++i) any = any || meets(b, rv[i]);
+      for (int i = 0; i < nrv; ++i) any = any || meets(b, ball(i));
       return any;
     };
     int jcur = 0, jend = 0;
@@ -1278,7 +1301,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       if (in_list_ball(ax, bx, ay, by, az, bz)) return false;
       const Box b = round_out(ax, bx, ay, by, az, bz);
       bool any = !okD || reach_all;
-      for (int i = 0; i < nD; ++i) any = any || meets(b, rv[rd[i]]);
+      for (int i = 0; i < nD; ++i) any = any || meets(b, ball(rd[i]));
       return any;
     };
     bool rdense = false;  // the current range lies in a dense cell
@@ -1401,7 +1424,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
             if (!in_list_ball(ax, bx, ay, by, az, bz)) {
               const Box b = round_out(ax, bx, ay, by, az, bz);
               for (int i0 = 0; i0 < nrv; i0 += L) {
-                const bool on = i0 + j < nrv && meets(b, rv[i0 + j]);
+                const bool on = i0 + j < nrv && meets(b, ball(i0 + j));
                 const unsigned gbits = gballot(on);
                 if (on) rd[nD + __popc(gbits & below)] = (unsigned char)(i0 + j);
                 nD += __popc(gbits);
@@ -1496,26 +1519,26 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     const R skip_scale = RECHECK ? R(1) - R(2e-6) : R(1) - R(1e-12);
     // can this lane's candidate cut: within twice the radius, and some vertex
     // in reach on the far side of the bisector, up to a bound on the plane
-    // test's own uncertainty (and on the float arithmetic here)?
+    // test's own uncertainty (and on the arithmetic here)?
     auto may_cut = [&]() -> bool {
       if (!(myd2 * skip_scale <= R(4) * (RECHECK ? (R)R2up : R2))) return false;
       if (reach_all) return true;
-      const float ex = (float)(myx * fsc), ey = (float)(myy * fsc), ez = (float)(myz * fsc);
-      const float c = 0.5f * (float)(myd2 * fsc * fsc);
-      float far = -c;
+      const R c = R(0.5) * myd2;
+      R far = -c;
       if (rdense && okD) {
         for (int i = 0; i < nD; ++i) {
-          const float4 v = rv[rd[i]];
-          far = fmaxf(far, ex * v.x + ey * v.y + ez * v.z);
+          const Ball v = ball(rd[i]);
+          far = fmax(far, myx * v.x + myy * v.y + myz * v.z);
         }
       } else {
         for (int i = 0; i < nrv; ++i) {
-          const float4 v = rv[i];
-          far = fmaxf(far, ex * v.x + ey * v.y + ez * v.z);
+          const Ball v = ball(i);
+          far = fmax(far, myx * v.x + myy * v.y + myz * v.z);
         }
       }
-      const float r2 = RECHECK ? R2up : (float)(R2 * fsc * fsc);
-      const float w = (wv + 2e-6f) * (c + __builtin_amdgcn_sqrtf(2.0f * c * r2));
+      R w;
+      if constexpr (RECHECK) w = (wv + 2e-6f) * (c + __builtin_amdgcn_sqrtf(2.0f * c * R2up));
+      else w = R(1e-12) * (c + (fabs(myx) + fabs(myy) + fabs(myz)) * rmax);
       return !(far < c - w);
     };
     while (__any(strm && st == ST_RUN)) {
@@ -1967,9 +1990,6 @@ votess_status launch_clip(const ClipLaunch& a, hipStream_t st) {
   c.kstride = a.knn_stride > 0 ? a.knn_stride : a.k;
   c.knn_by_id = a.knn_by_id;
   c.eps = a.eps;
-  double ext = 0.0;
-  for (int i = 0; i < 3; ++i) ext = std::max(ext, a.hi[i] - a.lo[i]);
-  c.fscale = std::ldexp(1.0, -std::ilogb(ext));
   // k-lists ordered by float distances may misplace near-ties by a few ulp:
   // certify only with that much slack
   c.dmargin = a.knn_dist == VOTESS_F32 ? (1.0 - 8.0 * (double)FLT_EPSILON) : 1.0;
