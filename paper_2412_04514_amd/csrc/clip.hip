@@ -585,11 +585,12 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   // between (rarely) are the bounds worked out.
   const float verrel = fmaxf(16.0f * (float)a.eps, FLT_EPSILON);
   const float kap = (3.5f + verrel) * verrel + 2.0f * (float)a.eps + 4e-6f;
-  float R2up = 0.0f, rlo = 0.0f, rhi = 0.0f;
+  float R2up = 0.0f, Rup = 0.0f, rlo = 0.0f, rhi = 0.0f;
   auto set_radius = [&](R r2) {
     R2 = r2;
     if constexpr (RECHECK) {
       R2up = r2 * (1.0f + kap);
+      Rup = __builtin_amdgcn_sqrtf(R2up);
       rlo = 4.0f * r2 * (1.0f - kap);
       rhi = 4.0f * R2up;
     }
@@ -720,17 +721,21 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   // by how vertices are made err <= max(16 eps, FLT_EPSILON) r.  A test outside
   // the bound is certain; one inside it works its own window out.
   // window(): for every vertex, window0(): less the |n|_1 err of the vertex.
+  // (5e-7, in the candidates' test of the stream phase 2e-6, covers the roundings
+  // of the float tests themselves: with an eps below 1e-6 they reach past the
+  // rest.  |n| and |v| are rooted apart: the product of their squares leaves the
+  // range of floats where the lengths are still in it.)
   const float wv = (float)a.eps + 1.7321f * verrel;
   auto window = [&](R d2, R c) -> R {
     if constexpr (RECHECK) {
-      return ((float)a.eps * c + wv * __builtin_amdgcn_sqrtf(d2 * R2up)) * (1.0f + 1e-4f);
+      return (((float)a.eps + 5e-7f) * c + (wv + 5e-7f) * (__builtin_amdgcn_sqrtf(d2) * Rup)) * (1.0f + 1e-4f);
     } else {
       return R(0);
     }
   };
   auto window0 = [&](R d2, R c) -> R {
     if constexpr (RECHECK) {
-      return (float)a.eps * (c + __builtin_amdgcn_sqrtf(d2 * R2up)) * (1.0f + 1e-4f);
+      return (float)a.eps * (c + __builtin_amdgcn_sqrtf(d2) * Rup) * (1.0f + 1e-4f);
     } else {
       return R(0);
     }
@@ -1537,7 +1542,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         }
       }
       R w;
-      if constexpr (RECHECK) w = (wv + 2e-6f) * (c + __builtin_amdgcn_sqrtf(2.0f * c * R2up));
+      if constexpr (RECHECK) w = (wv + 2e-6f) * (c + __builtin_amdgcn_sqrtf(2.0f * c) * Rup);
       else w = R(1e-12) * (c + (fabs(myx) + fabs(myy) + fabs(myz)) * rmax);
       return !(far < c - w);
     };
