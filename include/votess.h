@@ -134,7 +134,7 @@ VOTESS_API votess_status votess_grid_plan(int64_t n, const votess_box* box, doub
  *              point's sub-cell is s_a = clamp(floor((x_a - lo_a) ih_a), 0,
  *              m_a - 1), ih_a = m_a / e_a, id s0 + m0 (s1 + m1 s2).
  *              subinfo[2c] = offset of the cell's record in sub_start (-1
- *              for other cells), subinfo[2c+1] = m0 m1 m2
+ *              for other cells), subinfo[2c+1] = m0 m1 m2 (0 for other cells)
  *   sub_start  [votess_sub_capacity(n)] int32 out (nullable with subinfo),
  *              16-byte aligned: per dense cell a record at its offset (a
  *              multiple of 4): m0, m1, m2, 0, then lo[3] and ih[3] as doubles,

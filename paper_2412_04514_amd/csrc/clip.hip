@@ -417,7 +417,8 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     int fb0, fb1, fb2, fb3, fb4, fb5;
     int rr, pq, np, zlo, ylo, nyr, rln, rlp;
     int rx, rx1, rrow, yy, zz;
-    int dm, dm0, dm1, dm2, dbase, dsx0, dsx1, dsy0, dsy1, dsz0, dsz1, dsto;
+    int dm, dm0, dm1, dm2, dbase, dsx0, dsx1, dsy0, dsy1, dsz0, dsz1;
+    unsigned dsto;
     int dq1, dq2, kyn, kzn, dq, dqn, srn, srp;
   };
   __shared__ Enum senum[STREAM ? G : 1];
@@ -1281,7 +1282,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     // next sub-row ordinal, their count; listed ranges, next one
     int &dq = E_.dq, &dqn = E_.dqn, &srn = E_.srn, &srp = E_.srp;
     dq = 0; dqn = 0; srn = 0; srp = 0;
-    int& dsto = E_.dsto;  // the dense cell's sub-grid record: a.sub.start + dsto
+    unsigned& dsto = E_.dsto;  // the dense cell's sub-grid record: a.sub.start + dsto
     dsto = 0;
     // entries of the reach list whose ball meets the dense cell's sub-block
     // (valid for the vertices they were listed for)
@@ -1382,7 +1383,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
             xe = rx;
             for (;;) {
               const int xc = xe + j;
-              const bool dn = xc <= rx1 && a.sub.info[rrow + xc].x >= 0;
+              const bool dn = xc <= rx1 && is_dense(a.sub.info[rrow + xc]);
               const unsigned dmask = gballot(dn);
               if (dmask) {
                 xe += __ffs(dmask) - 1;
@@ -1404,7 +1405,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
           }
           // dense cell rx: its sub-cells inside the flower box
           const int2 info = a.sub.info[rrow + rx];
-          const SubCell sc = sub_cell(a.sub.start + info.x);
+          const SubCell sc = sub_cell(sub_record(a.sub, info));
           dsx0 = sub_axis(fwb[0], sc.lo0, sc.ih0, sc.m0);
           dsx1 = sub_axis(fwb[1], sc.lo0, sc.ih0, sc.m0);
           dsy0 = sub_axis(fwb[2], sc.lo1, sc.ih1, sc.m1);
@@ -1444,7 +1445,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
             dm = hit ? 1 : 0;
           }
           if (dm) {
-            dsto = info.x;
+            dsto = (unsigned)info.x;
             dbase = a.cell_start[rrow + rx];
             dm0 = sc.m0;
             dm1 = sc.m1;

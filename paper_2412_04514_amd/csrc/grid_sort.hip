@@ -55,13 +55,6 @@ __global__ void k_scatter(const T* __restrict__ pts, int n, const int2* __restri
   tmp[cell_start[c.x] + c.y] = Rec<T>::make(pts[3 * (size_t)i], pts[3 * (size_t)i + 1], pts[3 * (size_t)i + 2], i);
 }
 
-// Position of a dense cell's record in sub_start: a function of the cell's
-// first point b, so that the cells need not agree on it.  A cell of len > 16
-// points spans 4 floor(7 len / 17) words or more from its position to the next
-// one's, and its record takes (kSubHead + len / 2 + 1, rounded up to 4) <= that;
-// all of them end before 28 n / 17 < sub_capacity(n).
-__device__ __forceinline__ int sub_offset(int b) { return 4 * (int)((long long)b * 7 / 17); }
-
 // Orders small cells (up to kSubMin points) and lists the dense ones: those of
 // up to `split` points from the end of the list backwards, for k_order_mid,
 // the others from its front.  A wave takes 64 consecutive cells and goes over
@@ -454,14 +447,14 @@ __global__ __launch_bounds__(256) void k_order_dense(const typename Rec<T>::type
     for (int sc = threadIdx.x; sc < ns; sc += blockDim.x) crowd |= cnt[sc] > kCrowd;
     if (crowd) s_crowd = 1;
     block_scan_inplace(cnt, ns + 1);  // cnt[sc] = first point of sub-cell sc, cnt[ns] = len
-    const int soff = sub_offset(b);
+    const unsigned soff = sub_offset(b);
     int* rec = sub_start + soff;
     if (threadIdx.x == 0) {
       *(int4*)rec = make_int4(m0, m1, m2, 0);
       *(double2*)(rec + 4) = make_double2(lo0, lo1);
       *(double2*)(rec + 8) = make_double2(lo2, ih0);
       *(double2*)(rec + 12) = make_double2(ih1, ih2);
-      subinfo[c] = make_int2(soff, ns);
+      subinfo[c] = make_int2((int)soff, ns);
     }
     for (int sc = threadIdx.x; sc <= ns; sc += blockDim.x) rec[kSubHead + sc] = cnt[sc];
     if (!s_crowd) {
@@ -572,14 +565,14 @@ __device__ __forceinline__ void order_mid(const typename Rec<T>::type* __restric
     at[i] = lane + 64 * i < len ? atomicAdd(&cnt[sid[i]], 1) : 0;
   }
   __syncthreads();
-  const int soff = sub_offset(b);
+  const unsigned soff = sub_offset(b);
   int* rec = sub_start + soff;
   if (lane == 0) {
     *(int4*)rec = make_int4(m0, m1, m2, 0);
     *(double2*)(rec + 4) = make_double2(lo_[0], lo_[1]);
     *(double2*)(rec + 8) = make_double2(lo_[2], ih0);
     *(double2*)(rec + 12) = make_double2(ih1, ih2);
-    subinfo[c] = make_int2(soff, ns);
+    subinfo[c] = make_int2((int)soff, ns);
   }
   int carry = 0;  // starts of the sub-cells
   for (int s0 = 0; s0 <= ns; s0 += 64) {

@@ -282,11 +282,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(D) =
   // fills the list, and its k-th distance bounds the search
   const int c0 = cx + G.g0 * (cy + G.g1 * cz);
   const int2 info0 = sub.info ? sub.info[c0] : make_int2(-1, 0);
-  const bool seed_sub = info0.x >= 0 && cell_start[c0 + 1] - cell_start[c0] >= K + 1;
+  const bool seed_sub = is_dense(info0) && cell_start[c0 + 1] - cell_start[c0] >= K + 1;
   int qx = cx, qy = cy, qz = cz, m0 = G.g0, m1 = G.g1, m2 = G.g2, base0 = 0;
   const int* srec = cell_start;  // row starts: grid cells, or the own cell's sub-cells
   if (seed_sub) {
-    const SubCell sc = sub_cell(sub.start + info0.x);
+    const SubCell sc = sub_cell(sub_record(sub, info0));
     srec = sc.start;
     base0 = cell_start[c0];
     m0 = sc.m0;
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(D) =
       int xe = x;
       for (;;) {
         const int xc = xe + l;
-        const bool dense = xc <= x1 && sub.info && sub.info[row + xc].x >= 0;
+        const bool dense = xc <= x1 && sub.info && is_dense(sub.info[row + xc]);
         const unsigned long long dm = gballot(dense);
         if (dm) {
           xe += __ffsll((long long)dm) - 1;
@@ -500,7 +500,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(D) =
         continue;
       }
       // dense cell: the square of its sub-rows that meets the ball
-      const SubCell sc = sub_cell(sub.start + sub.info[row + x].x);
+      const SubCell sc = sub_cell(sub_record(sub, sub.info[row + x]));
       const double r0 = sqrt(rad2()) + margin;
       const int sz0 = sub_axis(p2 - r0, sc.lo2, sc.ih2, sc.m2), sz1 = sub_axis(p2 + r0, sc.lo2, sc.ih2, sc.m2);
       const int sy0 = sub_axis(p1 - r0, sc.lo1, sc.ih1, sc.m1), sy1 = sub_axis(p1 + r0, sc.lo1, sc.ih1, sc.m1);
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(D) =
       // the next sub-rows: each lane cuts its own to the ball, leaves out the
       // seed block's sub-cells and reads what is left
       const int c = E_.dcell;
-      const SubCell sc = sub_cell(sub.start + sub.info[c].x);
+      const SubCell sc = sub_cell(sub_record(sub, sub.info[c]));
       const int base = cell_start[c];
       const double w1 = 1.0 / sc.ih1, w2 = 1.0 / sc.ih2;
       const double ylo = G.lo1 + E_.y * G.h1, yhi = ylo + G.h1, zlo = G.lo2 + E_.z * G.h2, zhi = zlo + G.h2;
