@@ -7,6 +7,13 @@
 namespace votess {
 namespace {
 
+// What a thread of a launch over `count` things takes; `count` (none) for the
+// threads past the end, whose index may be past 2^31 in the last block.
+__host__ __device__ __forceinline__ int thread_item(unsigned block, unsigned threads, unsigned thread, int count) {
+  const unsigned i = block * threads + thread;
+  return i < (unsigned)count ? (int)i : count;
+}
+
 __device__ __forceinline__ int axis_cell(double x, double lo, double ih, int g) {
   double c = floor((x - lo) * ih);
   c = fmin(fmax(c, 0.0), (double)(g - 1));  // NaN -> 0

@@ -72,7 +72,8 @@ __global__ __launch_bounds__(kSmallCells) void k_order_small(const typename Rec<
                                                              int* __restrict__ nlist, int split,
                                                              int2* __restrict__ subinfo) {
   __shared__ int heads_of[kSmallCells], ids_of[kSmallCells], ndense[2][kSmallCells / 64], at_[2];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = blockIdx.x * kSmallCells + threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c = thread_item(blockIdx.x, kSmallCells, threadIdx.x, ncells);
   int b = 0, len = 0;
   if (c < ncells) {
     b = cell_start[c];
