@@ -93,6 +93,17 @@ votess_status alloc_buf(votess_ctx* ctx, Buf& b, size_t bytes) {
   return VOTESS_OK;
 }
 
+// Waits for a stream when its scope ends before the scope's buffers do: what
+// the caller's allocator gets back, on an early return too, no kernel uses.
+struct Drain {
+  hipStream_t st;
+  bool on = true;
+  explicit Drain(hipStream_t s) : st(s) {}
+  ~Drain() {
+    if (on) (void)hipStreamSynchronize(st);
+  }
+};
+
 votess_status check_box(const votess_box* box) {
   if (!box) return fail(VOTESS_EINVAL, "box is null");
   for (int a = 0; a < 3; ++a)
@@ -505,8 +516,9 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
   const bool wantf = P.want_faces != 0;
   const votess_dtype dist = P.precision == VOTESS_CLIP_F32_RECHECK ? VOTESS_F32 : VOTESS_F64;
 
-  Buf cell_start, perm, sorted, status, nbr_count, nbr, vol, vcount, verts, vplanes, knn, cells, cells2, counters;
+  Buf cell_start, perm, sorted, status, nbr_count, nbr, vol, vcount, verts, vplanes, knn, knn2, cells, cells2, counters;
   Buf subinfo, sub_start, farea, fcen;
+  Drain drain(st);
   const size_t nn = (size_t)std::max(n, 1);
   VT_TRY(alloc_buf(ctx, cell_start, (grid.ncells + 1) * 4));
   VT_TRY(alloc_buf(ctx, subinfo, grid.ncells * 8));
@@ -626,7 +638,6 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
     const int ncap = rep.count;
     if (ncap == 0) return VOTESS_OK;
     S.capacity_cells += ncap;
-    Buf knn2;
     if (kk > 0 && !all_listed) {  // (no list in the fused form: the large kernel streams from ring 0 too)
       VT_TRY(alloc_buf(ctx, knn2, (size_t)ncap * kk * 4));
       Timer T(timers, st, &S.ms_knn);
@@ -866,6 +877,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
     }
     T.stop();
     VT_HIP(hipStreamSynchronize(st));
+    drain.on = false;
     out->row_ptr = (int64_t*)row_ptr.release();
     out->col = (int32_t*)col.release();
     out->volume = (double*)volume.release();

@@ -1,0 +1,64 @@
+"""Device memory goes back to the caller's allocator only when nothing on the
+stream uses it any more: an allocator need not know about streams."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+vt = pytest.importorskip("paper_2412_04514_amd")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+class Watched(vt.Context):
+    """Notes for each release whether the stream had work left."""
+
+    def __init__(self):
+        super().__init__()
+        self.busy = []
+
+        def release(p, _user):
+            self.busy.append(not torch.cuda.current_stream().query())
+            self._live.pop(int(p or 0), None)
+
+        self._release_cb = vt._lib.RELEASE_FN(release)
+        self.lib.votess_set_allocator(self.handle, self._alloc_cb, self._release_cb, None)
+
+
+def _shell(m, n, seed):
+    # a cell of m faces, more than the fast kernels hold, among n others
+    rng = np.random.default_rng(seed)
+    u = rng.standard_normal((m, 3))
+    shell = 0.5 + 0.1 * u / np.linalg.norm(u, axis=1, keepdims=True) + 1e-4 * rng.standard_normal(u.shape)
+    bg = rng.random((n, 3))
+    return np.concatenate([[[0.5, 0.5, 0.5]], shell, bg[np.linalg.norm(bg - 0.5, axis=1) > 0.25]])
+
+
+@pytest.mark.parametrize("kw", [dict(k0=64, max_gpu_retries=1), dict(k0=64, max_gpu_retries=0), dict(k0=32),
+                                dict(k0=0), dict(k0=32, faces=True, vertices=True),
+                                dict(k0=32, force_fail_every=50)], ids=str)
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+def test_nothing_is_released_in_use(kw, dt):
+    ctx = Watched()
+    P = torch.from_numpy(_shell(60, 20_000, 3).astype(dt)).cuda()
+    torch.cuda.synchronize()
+    r = vt.tessellate(P, ctx=ctx, precision="f32" if dt is np.float32 else "f64", **kw)
+    assert len(ctx.busy) > 5 and not any(ctx.busy)
+    if kw.get("max_gpu_retries") == 1:
+        assert r.stats["capacity_cells"] > 0  # with lists of its own
+
+
+def test_nothing_is_released_in_use_after_an_error():
+    ctx = Watched()
+    P = torch.rand(20_000, 3, device="cuda")
+    P[1] = P[0]
+    with pytest.raises(vt.VotessError):
+        vt.tessellate(P, ctx=ctx)
+    with pytest.raises(vt.VotessError):
+        vt.tessellate(torch.rand(20_000, 3, device="cuda") + 0.5, ctx=ctx)
+    assert len(ctx.busy) > 5 and not any(ctx.busy)
