@@ -765,7 +765,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
     std::vector<HostCellOut> res;
     host_fallback_cells(rec.data(), dtype, n, grid, cs.data(), ids.data(), nhost, wantv, wantf, P.host_threads,
                         res);
-    // write back: one upload, one kernel
+    // write back: an upload and a kernel per chunk of rows
     std::vector<int32_t> h_cnt(nhost), h_nbr((size_t)nhost * kMaxNbr, -1), h_vc;
     std::vector<double> h_vol(nhost), h_v, h_area, h_cen;
     if (wantf) {

@@ -5,6 +5,7 @@
 // vertices follow.
 #include "internal.h"
 
+#include <algorithm>
 #include <cstring>
 #include <vector>
 
@@ -220,25 +221,27 @@ votess_status put_rows(const RowsIn& in, int rows, int max_nbr, int max_vert, co
   return VOTESS_OK;
 }
 
+constexpr size_t kStagingBytes = 8 << 20;
 votess_status put_host_rows(votess_ctx* ctx, const RowsIn& h, int rows, int max_nbr, int max_vert, const RowsOut& out,
                             hipStream_t st) {
   if (rows <= 0) return VOTESS_OK;
-  // one upload of all arrays, each at a multiple of 16 bytes
-  size_t bytes = 0;
-  auto place = [&](const void* p, size_t len) {
-    const size_t at = bytes;
-    if (p) bytes += (len + 15) / 16 * 16;
-    return at;
-  };
-  const size_t R = rows, N = R * max_nbr, V = R * max_vert * 3;
-  const size_t len[11] = {R * 4, R, R * 4, N * 4, R * 8, R * 8, N * 8, R * 24, R * 4, V * 8, V * 4};
+  // All arrays of a chunk of rows in one upload, each at a multiple of 16
+  // bytes.  Chunks keep the staging small beside the call's own buffers: every
+  // cell may come this way, with vertices at 10 KB each.
+  const size_t N = max_nbr, V = (size_t)max_vert * 3;
+  const size_t row[11] = {4, 1, 4, N * 4, 8, 8, N * 8, 24, 4, V * 8, V * 4};  // bytes of a row
   const void* src[11] = {h.at,   h.status,   h.count,  h.nbr,   h.volume, h.r2,
                          h.area, h.centroid, h.vcount, h.verts, h.vplanes};
-  size_t off[11];
-  for (int i = 0; i < 11; ++i) off[i] = place(src[i], len[i]);
-  std::vector<char> host(bytes);
+  size_t per_row = 0;
   for (int i = 0; i < 11; ++i)
-    if (src[i]) std::memcpy(host.data() + off[i], src[i], len[i]);
+    if (src[i]) per_row += row[i];
+  const size_t chunk = std::min<size_t>(rows, std::max<size_t>(1, kStagingBytes / per_row));
+  size_t off[11], bytes = 0;
+  for (int i = 0; i < 11; ++i) {
+    off[i] = bytes;
+    if (src[i]) bytes += (chunk * row[i] + 15) / 16 * 16;
+  }
+  std::vector<char> host(bytes);
   char* dev = (char*)dev_alloc(ctx, bytes);
   if (!dev) return fail(VOTESS_ENOMEM, "rows from the host: %zu bytes", bytes);
   RowsIn d;
@@ -254,14 +257,20 @@ votess_status put_host_rows(votess_ctx* ctx, const RowsIn& h, int rows, int max_
   d.vcount = (const int32_t*)at(8);
   d.verts = (const double*)at(9);
   d.vplanes = (const int32_t*)at(10);
-  hipError_t e = hipMemcpyAsync(dev, host.data(), bytes, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) {
-    k_put_rows<<<(unsigned)rows, 64, 0, st>>>(d, max_nbr, max_vert, out);
-    e = hipGetLastError();
+  hipError_t e = hipSuccess;
+  for (size_t r0 = 0; r0 < (size_t)rows && e == hipSuccess; r0 += chunk) {
+    const size_t n = std::min(chunk, rows - r0);
+    for (int i = 0; i < 11; ++i)
+      if (src[i]) std::memcpy(host.data() + off[i], (const char*)src[i] + r0 * row[i], n * row[i]);
+    e = hipMemcpyAsync(dev, host.data(), bytes, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) {
+      k_put_rows<<<(unsigned)n, 64, 0, st>>>(d, max_nbr, max_vert, out);
+      e = hipGetLastError();
+    }
+    const hipError_t w = hipStreamSynchronize(st);  // before the staging is filled again, or goes
+    if (e == hipSuccess) e = w;
   }
-  const hipError_t w = hipStreamSynchronize(st);  // before the staging goes
   dev_free(ctx, dev);
-  if (e == hipSuccess) e = w;
   if (e != hipSuccess) return fail(VOTESS_EHIP, "rows from the host: %s", hipGetErrorString(e));
   return VOTESS_OK;
 }

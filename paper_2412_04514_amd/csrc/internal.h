@@ -202,7 +202,8 @@ struct RowsOut {
   int32_t* vplanes = nullptr;
 };
 votess_status put_rows(const RowsIn& in, int rows, int max_nbr, int max_vert, const RowsOut& out, hipStream_t st);
-// the same from host memory: one upload; waits for the stream before it returns
+// the same from host memory, a chunk of rows at a time; waits for the stream
+// before it returns
 votess_status put_host_rows(votess_ctx* ctx, const RowsIn& h, int rows, int max_nbr, int max_vert, const RowsOut& out,
                             hipStream_t st);
 

@@ -1,5 +1,6 @@
-"""Device memory goes back to the caller's allocator only when nothing on the
-stream uses it any more: an allocator need not know about streams."""
+"""What a tessellation asks of the caller's allocator: memory goes back only when
+nothing on the stream uses it any more (an allocator need not know about
+streams), and cells built on the host need little beside the call's buffers."""
 import numpy as np
 import pytest
 import torch
@@ -16,16 +17,25 @@ def _need_gpu():
 
 
 class Watched(vt.Context):
-    """Notes for each release whether the stream had work left."""
+    """Notes for each release whether the stream had work left, and the most
+    bytes that were out at a time."""
 
     def __init__(self):
         super().__init__()
-        self.busy = []
+        self.busy, self.peak = [], 0
+        alloc_ = self._alloc_cb
+
+        def alloc(nbytes, user):
+            p = alloc_(nbytes, user)
+            self.peak = max(self.peak, sum(t.numel() for t in self._live.values()))
+            return p
 
         def release(p, _user):
             self.busy.append(not torch.cuda.current_stream().query())
             self._live.pop(int(p or 0), None)
 
+        self._inner = alloc_
+        self._alloc_cb = vt._lib.ALLOC_FN(alloc)
         self._release_cb = vt._lib.RELEASE_FN(release)
         self.lib.votess_set_allocator(self.handle, self._alloc_cb, self._release_cb, None)
 
@@ -62,3 +72,22 @@ def test_nothing_is_released_in_use_after_an_error():
     with pytest.raises(vt.VotessError):
         vt.tessellate(torch.rand(20_000, 3, device="cuda") + 0.5, ctx=ctx)
     assert len(ctx.busy) > 5 and not any(ctx.busy)
+
+
+@pytest.mark.parametrize("every", [1, 7])
+@pytest.mark.parametrize("kw", [dict(), dict(vertices=True, faces=True)], ids=str)
+def test_cells_built_on_the_host_need_little_memory(kw, every):
+    P = torch.from_numpy(np.random.default_rng(4).random((20_000, 3))).cuda()
+    a, b = Watched(), Watched()
+    on_gpu = vt.tessellate(P, ctx=a, **kw)
+    on_host = vt.tessellate(P, ctx=b, force_fail_every=every, **kw)
+    assert on_host.stats["fallback_cells"] >= len(P) // every
+    assert b.peak <= a.peak + (16 << 20)
+    # every row in its place, whatever chunk it came in
+    assert torch.equal(on_gpu.row_ptr, on_host.row_ptr) and torch.equal(on_gpu.col, on_host.col)
+    assert torch.all((on_gpu.volume - on_host.volume).abs() <= 2e-12 * on_gpu.volume)
+    if kw:
+        assert torch.equal(on_gpu.vrow_ptr, on_host.vrow_ptr)
+        assert torch.all((on_gpu.centroid - on_host.centroid).abs() <= 1e-9)
+        # (areas of tiny faces: relative to the cell's largest)
+        assert torch.all((on_gpu.area - on_host.area).abs() <= 1e-9 * on_gpu.area.max())
