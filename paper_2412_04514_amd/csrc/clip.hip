@@ -1769,49 +1769,47 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   for (int f = j; f < PMAX; f += L) nnb += cert && ((alive >> f) & 1) && pid(f) >= 0;
   int ntot;
   int noff = gexcl(nnb, ntot);
-  if (cert) {
+  // vertices
+  int vtot = 0, voff = 0;
+  if (a.max_vert > 0) {
+    int nv = 0;
+    for (int t = j; t < H; t += L) nv += cert && tri[vb + t] != kEmpty;
+    voff = gexcl(nv, vtot);
+  }
+  // the cell's status: certified, unless its row is too short for it.  Rows of
+  // cells that are not certified stay as they are.
+  int fin = st;
+  if (cert && (ntot > a.max_nbr || (a.max_vert > 0 && vtot > a.max_vert))) fin = VOTESS_CELL_CAPACITY;
+  const bool put = cert && fin == VOTESS_CELL_CERTIFIED;
+  if (put) {
 #pragma unroll
     for (int q = 0; q < FO; ++q) {
       const int f = j + q * L;
       if (((alive >> f) & 1) && pid(f) >= 0) {
-        if (noff < a.max_nbr) {
-          a.nbr[(size_t)row * a.max_nbr + noff] = pid(f);
-          if (a.area) a.area[(size_t)row * a.max_nbr + noff] = farea[q];
-        }
+        a.nbr[(size_t)row * a.max_nbr + noff] = pid(f);
+        if (a.area) a.area[(size_t)row * a.max_nbr + noff] = farea[q];
         ++noff;
       }
     }
   }
-  // vertices
-  int vtot = 0;
-  if (a.max_vert > 0) {
-    int nv = 0;
-    for (int t = j; t < H; t += L) nv += cert && tri[vb + t] != kEmpty;
-    int voff = gexcl(nv, vtot);
-    if (cert) {
-      for (int t = j; t < H; t += L) {
-        const unsigned u = tri[vb + t];
-        if (u == kEmpty) continue;
-        if (voff < a.max_vert) {
-          const size_t o = ((size_t)row * a.max_vert + voff) * 3;
-          const V3<R> w = vget(t);
-          V3<double> v = {(double)w.x, (double)w.y, (double)w.z};
-          if (refine) v = vertex64(u);
-          a.verts[o + 0] = p64x + v.x;
-          a.verts[o + 1] = p64y + v.y;
-          a.verts[o + 2] = p64z + v.z;
-          a.vplanes[o + 0] = pid(TC::a(u));
-          a.vplanes[o + 1] = pid(TC::b(u));
-          a.vplanes[o + 2] = pid(TC::c(u));
-        }
-        ++voff;
-      }
+  if (put && a.max_vert > 0) {
+    for (int t = j; t < H; t += L) {
+      const unsigned u = tri[vb + t];
+      if (u == kEmpty) continue;
+      const size_t o = ((size_t)row * a.max_vert + voff) * 3;
+      const V3<R> w = vget(t);
+      V3<double> v = {(double)w.x, (double)w.y, (double)w.z};
+      if (refine) v = vertex64(u);
+      a.verts[o + 0] = p64x + v.x;
+      a.verts[o + 1] = p64y + v.y;
+      a.verts[o + 2] = p64z + v.z;
+      a.vplanes[o + 0] = pid(TC::a(u));
+      a.vplanes[o + 1] = pid(TC::b(u));
+      a.vplanes[o + 2] = pid(TC::c(u));
+      ++voff;
     }
   }
-  int fin = st;
   if (have && j == 0) {
-    if (fin == VOTESS_CELL_CERTIFIED && (ntot > a.max_nbr || (a.max_vert > 0 && vtot > a.max_vert)))
-      fin = VOTESS_CELL_CAPACITY;
     a.status[row] = (uint8_t)(fin | (a.rest || ((a.mark >> fin) & 1) ? kLeft : 0));
     a.nbr_count[row] = fin == VOTESS_CELL_CERTIFIED ? ntot : 0;
     a.volume[row] = fin == VOTESS_CELL_CERTIFIED ? vol : 0.0;
