@@ -268,7 +268,8 @@ typedef struct {
   double ms_sort, ms_knn, ms_clip, ms_features, ms_mlp, ms_assemble, ms_fallback, ms_total;
   /* per pass: cells its list left uncertified that went on into the stream
    * phase (pass_failed counts the cells still uncertified after it).  Passes
-   * whose lists hold at most 64 entries run as one; each has its entry here */
+   * whose lists hold at most 64 entries run as one; each that would have had
+   * cells to clip has the entry that it would have had by itself */
   int64_t pass_streamed[VOTESS_MAX_PASSES];
 } votess_stats;
 

@@ -620,6 +620,7 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
   auto record_pass = [&](int64_t cells_in, int taken) {
     const unsigned long long* cnt = rep.clip;
     for (int i = 0; i <= taken && S.npasses < VOTESS_MAX_PASSES; ++i, ++S.npasses) {
+      if (i > 0 && cells_in == 0) break;  // none was left for this pass
       const bool last = i == taken;
       const int64_t left = last ? nfail : (int64_t)cnt[kLevelCounter + i];
       S.pass_k[S.npasses] = last ? k : level[i];
@@ -653,6 +654,8 @@ extern "C" votess_status votess_tessellate(votess_ctx* ctx, const void* pts, vot
     c2.k = kk;
     c2.capacity = 1;
     c2.stream = strm ? 1 : 0;
+    if (all_listed)
+      for (int i = 1; i < merged; ++i) c2.level[i] = level[i];
     return launch_clip(c2, st);
   };
   // ---- first pass over all cells

@@ -610,7 +610,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     }
   };
   bool streamed = false;  // the cell has entered the stream phase
-  int kneed = 0;
+  int kneed = 0;  // unresolved at plane m of the list: -1 - m
   int nrecheck = 0;
   __syncthreads();
 
@@ -743,9 +743,10 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   };
 
   // Tests plane (n, c) of candidate nb against every vertex and, if it cuts,
-  // replaces the removed triangles; whether it did.  Called by every lane (wave-uniform).
+  // replaces the removed triangles; whether it did.  `m` is its place in the list
+  // (-1: not of the list).  Called by every lane (wave-uniform).
   // Always inlined: as a call, its captures live in scratch memory.
-  auto apply_plane = [&](bool run, R nx, R ny, R nz, R c, R d2, int nb) __attribute__((always_inline)) -> bool {
+  auto apply_plane = [&](bool run, R nx, R ny, R nz, R c, R d2, int nb, int m) __attribute__((always_inline)) -> bool {
     // ---- test the plane against every vertex
     unsigned out = 0;
     R least = R(3.0e38);  // the smallest margin of this lane's tests, less |n|_1 err
@@ -788,6 +789,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         }
         if (group_any(unresolved) && run) {
           st = VOTESS_CELL_UNRESOLVED;
+          kneed = -1 - m;
           run = false;
           out = 0;
         }
@@ -872,6 +874,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     for (int f = j; f < PMAX; f += L) omask[pb + f] = 0;
     if (doit && (btot < 3 || btot > PMAX)) {  // inconsistent topology (rounding): give up on the cell
       st = VOTESS_CELL_UNRESOLVED;
+      kneed = -1 - m;
       doit = false;
     }
     // new triangles (a, b, ps): into the freed slots, then past H
@@ -953,8 +956,10 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
               certb = gballot(on && p == 1);
               uncb = gballot(on && p == 2);
               // a plane that has cut is looked at again for the certificate
-              // alone, and for a recheck only at the end of the list
-              if (again && mb + cur < a.k - 1) uncb &= ~(1u << cur);
+              // alone, and for a recheck only at the end of a list
+              const int len = mb + cur + 1;
+              if (again && len != a.k && len != a.level[0] && len != a.level[1] && len != a.level[2])
+                uncb &= ~(1u << cur);
             }
           } else {
             certb = gballot(on && (R)(cd2 * (R)kDmargin) > R(4) * R2);
@@ -1018,6 +1023,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
             const double d64 = dot(n64, n64);
             if (fabs(d64 - 4.0 * r64) <= 1e-12 * d64) {
               st = VOTESS_CELL_UNRESOLVED;
+              kneed = -1 - m;
               run = false;
             } else if (d64 * kDmargin > 4.0 * r64) {
               st = VOTESS_CELL_CERTIFIED;
@@ -1031,7 +1037,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       const R nx = shfl_t(cx_, gb + i), ny = shfl_t(cy_, gb + i), nz = shfl_t(cz_, gb + i);
       const R d2 = dist2_nc(nx, ny, nz);
       const bool ap = run && ((pendb >> i) & 1u);
-      const bool did = apply_plane(ap, nx, ny, nz, R(0.5) * d2, d2, nb);
+      const bool did = apply_plane(ap, nx, ny, nz, R(0.5) * d2, d2, nb, m);
       // on past plane m; if it cut, its own distance may already certify the
       // cell that it left (with a list of m + 1)
       again = ap && did;
@@ -1598,7 +1604,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         // the radius may have shrunk since the batch was filtered
         if (d2 * skip_scale > R(4) * (RECHECK ? (R)R2up : R2)) run2 = false;
       }
-      if (apply_plane(run2, nx, ny, nz, c, d2, nb2)) reach_ok = okD = flower_ok = false;
+      if (apply_plane(run2, nx, ny, nz, c, d2, nb2, -1)) reach_ok = okD = flower_ok = false;
     }
   }
 
@@ -1819,16 +1825,17 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       a.centroid[(size_t)row * 3 + 1] = ok ? cmy : 0.0;
       a.centroid[(size_t)row * 3 + 2] = ok ? cmz : 0.0;
     }
-    if (a.kneeded) a.kneeded[row] = kneed;
+    if (a.kneeded) a.kneeded[row] = max(kneed, 0);
     if (a.r2out) a.r2out[row] = fin == VOTESS_CELL_CERTIFIED ? (RECHECK ? (double)R2up : (double)R2) : 0.0;
     if (a.vcount) a.vcount[row] = fin == VOTESS_CELL_CERTIFIED ? vtot : 0;
   }
   // counters: one addition per wave (all of them meet at one address)
   if (a.counters) {
     const bool lead = have && j == 0;
-    auto add = [&](int c, bool v) {
+    auto add = [&](int c, bool v, bool less = false) {
       const unsigned long long b = __ballot(lead && v);
-      if (lane == 0 && b) atomicAdd(&a.counters[c], (unsigned long long)__popcll(b));
+      const unsigned long long by = (unsigned long long)__popcll(b);
+      if (lane == 0 && b) atomicAdd(&a.counters[c], less ? 0ull - by : by);
     };
     add(1, fin == VOTESS_CELL_UNRESOLVED);
     const bool word = !((a.mark >> fin) & 1);  // of this launch, on the cell's status
@@ -1845,14 +1852,22 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       rc += __shfl_xor(rc, 32, 64);
       if (lane == 0 && rc) atomicAdd(&a.counters[0], (unsigned long long)rc);
     }
-    // cells that a list of level[i] does not certify, counted by the launch
-    // that has the last word on the cell's list
-    const bool mine = !resume && !(fin == VOTESS_CELL_CAPACITY && ((a.mark >> fin) & 1));
+    // cells that a pass with lists of level[i] would have left, counted by the
+    // launch that has the last word on the cell's list: the large kernel for
+    // cells that the fast ones cannot hold, except in the first pass, which has no
+    // large kernel (so that a cell that the stream phase, after the list, leaves to
+    // the large kernel is taken off again).  A cell that is unresolved at a plane
+    // of the list's first level[i] would not have been left, but unresolved.
+    const bool over = fin == VOTESS_CELL_CAPACITY && PMAX <= 32;
+    const bool mine = !resume && !(over && ((a.mark >> fin) & 1));
 #pragma unroll
     for (int i = 0; i < kLevels; ++i)
-      if (a.level[i])
-        add(kLevelCounter + i, mine && (fin == VOTESS_CELL_CERTIFIED ? kneed > a.level[i]
-                                                                     : fin != VOTESS_CELL_UNRESOLVED));
+      if (a.level[i]) {
+        add(kLevelCounter + i, mine && (fin == VOTESS_CELL_CERTIFIED    ? kneed > a.level[i]
+                                        : fin == VOTESS_CELL_UNRESOLVED ? kneed >= 0 || -1 - kneed >= a.level[i]
+                                                                        : !over || i == 0));
+        if (STREAM && i > 0) add(kLevelCounter + i, resume && over, true);
+      }
   }
 }
 

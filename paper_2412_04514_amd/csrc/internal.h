@@ -142,9 +142,9 @@ struct ClipLaunch {
   double* centroid = nullptr;    // [rows, 3] cell centroids (nullable)
   double* r2out = nullptr;       // [rows] R^2 of each certified cell (nullable; an upper bound on the float path)
   unsigned long long* counters;  // [kClipCounters]: rechecks, unresolved, capacity, refined, streamed (certified
-                                 // by the stream phase), stream entries, cells not certified by the first
-                                 // level[i] entries of their list, radius; statuses as the launch leaves
-                                 // them -- nullable
+                                 // by the stream phase), stream entries, cells that a pass with the first
+                                 // level[i] entries of their list would have left, radius; statuses as
+                                 // the launch leaves them -- nullable
   int level[kLevels] = {0, 0, 0};  // (0: not counted)
   int own_rows = 1;              // 0: `cells` may name a cell twice with out_by_id
   int spare_rows = 1;            // 0: rows of nbr of uncertified cells stay as they are
