@@ -586,12 +586,11 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   // between (rarely) are the bounds worked out.
   const float verrel = fmaxf(16.0f * (float)a.eps, FLT_EPSILON);
   const float kap = (3.5f + verrel) * verrel + 2.0f * (float)a.eps + 4e-6f;
-  float R2up = 0.0f, Rup = 0.0f, rlo = 0.0f, rhi = 0.0f;
+  float R2up = 0.0f, rlo = 0.0f, rhi = 0.0f;
   auto set_radius = [&](R r2) {
     R2 = r2;
     if constexpr (RECHECK) {
       R2up = r2 * (1.0f + kap);
-      Rup = __builtin_amdgcn_sqrtf(R2up);
       rlo = 4.0f * r2 * (1.0f - kap);
       rhi = 4.0f * R2up;
     }
@@ -729,14 +728,16 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   const float wv = (float)a.eps + 1.7321f * verrel;
   auto window = [&](R d2, R c) -> R {
     if constexpr (RECHECK) {
-      return (((float)a.eps + 5e-7f) * c + (wv + 5e-7f) * (__builtin_amdgcn_sqrtf(d2) * Rup)) * (1.0f + 1e-4f);
+      const float nv = __builtin_amdgcn_sqrtf(d2) * __builtin_amdgcn_sqrtf(R2up);
+      return (((float)a.eps + 5e-7f) * c + (wv + 5e-7f) * nv) * (1.0f + 1e-4f);
     } else {
       return R(0);
     }
   };
   auto window0 = [&](R d2, R c) -> R {
     if constexpr (RECHECK) {
-      return (float)a.eps * (c + __builtin_amdgcn_sqrtf(d2) * Rup) * (1.0f + 1e-4f);
+      const float nv = __builtin_amdgcn_sqrtf(d2) * __builtin_amdgcn_sqrtf(R2up);
+      return (float)a.eps * (c + nv) * (1.0f + 1e-4f);
     } else {
       return R(0);
     }
@@ -789,7 +790,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         }
         if (group_any(unresolved) && run) {
           st = VOTESS_CELL_UNRESOLVED;
-          kneed = -1 - m;
+          if (m >= 0) kneed = -1 - m;
           run = false;
           out = 0;
         }
@@ -874,7 +875,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     for (int f = j; f < PMAX; f += L) omask[pb + f] = 0;
     if (doit && (btot < 3 || btot > PMAX)) {  // inconsistent topology (rounding): give up on the cell
       st = VOTESS_CELL_UNRESOLVED;
-      kneed = -1 - m;
+      if (m >= 0) kneed = -1 - m;
       doit = false;
     }
     // new triangles (a, b, ps): into the freed slots, then past H
@@ -1549,7 +1550,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         }
       }
       R w;
-      if constexpr (RECHECK) w = (wv + 2e-6f) * (c + __builtin_amdgcn_sqrtf(2.0f * c) * Rup);
+      if constexpr (RECHECK) w = (wv + 2e-6f) * (c + __builtin_amdgcn_sqrtf(2.0f * c) * __builtin_amdgcn_sqrtf(R2up));
       else w = R(1e-12) * (c + (fabs(myx) + fabs(myy) + fabs(myz)) * rmax);
       return !(far < c - w);
     };

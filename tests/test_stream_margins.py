@@ -215,10 +215,10 @@ def test_radius_bounds_lie_within_kap(eps):
 
 def test_the_clip_uses_these_windows():
     src = (Path(__file__).resolve().parent.parent / "paper_2412_04514_amd" / "csrc" / "clip.hip").read_text()
-    for form in ("((float)a.eps + 5e-7f) * c + (wv + 5e-7f) * (__builtin_amdgcn_sqrtf(d2) * Rup)",
-                 "(float)a.eps * (c + __builtin_amdgcn_sqrtf(d2) * Rup) * (1.0f + 1e-4f)",
-                 "(wv + 2e-6f) * (c + __builtin_amdgcn_sqrtf(2.0f * c) * Rup)",
-                 "Rup = __builtin_amdgcn_sqrtf(R2up)",
+    src = src.replace("__builtin_amdgcn_sqrtf", "sqrt")
+    for form in ("nv = sqrt(d2) * sqrt(R2up)", "((float)a.eps + 5e-7f) * c + (wv + 5e-7f) * nv",
+                 "(float)a.eps * (c + nv) * (1.0f + 1e-4f)",
+                 "(wv + 2e-6f) * (c + sqrt(2.0f * c) * sqrt(R2up))",
                  "(3.5f + verrel) * verrel + 2.0f * (float)a.eps + 4e-6f",
                  "fmaxf(16.0f * (float)a.eps, FLT_EPSILON)", "(float)a.eps + 1.7321f * verrel"):
         assert form in src, form
