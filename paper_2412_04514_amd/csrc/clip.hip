@@ -113,14 +113,29 @@ __device__ __forceinline__ R dot(const V3<R>& a, const V3<R>& b) {
   return a.x * b.x + a.y * b.y + a.z * b.z;
 }
 
-// Vertex of planes a, b, c: solve [na; nb; nc] x = [ca, cb, cc].
-template <typename R>
-__device__ __forceinline__ V3<R> solve3(const V3<R>& na, R ca, const V3<R>& nb, R cb, const V3<R>& nc, R cc) {
-  const V3<R> bc = cross(nb, nc), ca_ = cross(nc, na), ab = cross(na, nb);
-  const R det = dot(na, bc);
-  const R inv = R(1) / det;
-  return {(ca * bc.x + cb * ca_.x + cc * ab.x) * inv, (ca * bc.y + cb * ca_.y + cc * ab.y) * inv,
-          (ca * bc.z + cb * ca_.z + cc * ab.z) * inv};
+// Vertex of planes a, b, c: solve [a; b; c] x = [ca, cb, cc].  Which products
+// are fused, and which of a sum's first two terms is rounded first, is written
+// out rather than left to the compiler, whose choice moves with the code around
+// it: the kernels of a clip and the state passed between them must agree on
+// every bit of a vertex, and so must one build with the next.  (FIRST: the first
+// term of det, not of y and z, as the float clip's rechecks have it; the double
+// clip has them the other way round.)
+template <bool FIRST>
+__device__ __forceinline__ V3<double> solve3(const V3<double>& a, double ca, const V3<double>& b, double cb,
+                                             const V3<double>& c, double cc) {
+#pragma clang fp contract(off)
+  auto fma = [](double x, double y, double z) { return __builtin_fma(x, y, z); };
+  auto cross_ = [&](const V3<double>& p, const V3<double>& q) -> V3<double> {
+    return {fma(p.y, q.z, -(p.z * q.y)), fma(p.z, q.x, -(p.x * q.z)), fma(p.x, q.y, -(p.y * q.x))};
+  };
+  // p q + r s with r s (last) or p q (first) rounded by itself
+  auto sum2 = [&](bool first, double p, double q, double r, double s) {
+    return first ? fma(r, s, p * q) : fma(p, q, r * s);
+  };
+  const V3<double> bc = cross_(b, c), cx = cross_(c, a), ab = cross_(a, b);
+  const double inv = 1.0 / fma(a.z, bc.z, sum2(FIRST, a.x, bc.x, a.y, bc.y));
+  return {fma(cc, ab.x, sum2(false, ca, bc.x, cb, cx.x)) * inv, fma(cc, ab.y, sum2(!FIRST, ca, bc.y, cb, cx.y)) * inv,
+          fma(cc, ab.z, sum2(!FIRST, ca, bc.z, cb, cx.z)) * inv};
 }
 
 // c - n.v as if in twice the working precision: each product split exactly
@@ -189,12 +204,8 @@ __device__ __forceinline__ V3<double> solve3_refined(const V3<double>& na, doubl
 
 // Float vertex of three planes with a first-order forward error bound (max
 // norm): rounding of the cross products, the sums, the division and of the
-// plane data (normals may be off by an ulp, offsets by two).  Which products
-// are fused is written out rather than left to the compiler, whose choice
-// moves with the code around it (it fuses a cross product's first product;
-// the order of the sums' first two terms is fixed, if not the same for z):
-// the kernels of a clip and the state passed between them must agree on every
-// bit of a vertex, and so must one build with the next.
+// plane data (normals may be off by an ulp, offsets by two).  What is fused is
+// written out, as in solve3.
 __device__ __forceinline__ V3<float> solve3_err(const V3<float>& a, float ca, const V3<float>& b, float cb,
                                                 const V3<float>& c, float cc, float& err) {
 #pragma clang fp contract(off)
@@ -488,7 +499,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     plane64(TC::a(u), na, ca);
     plane64(TC::b(u), nb, cb);
     plane64(TC::c(u), nc, cc);
-    return solve3<double>(na, ca, nb, cb, nc, cc);
+    return solve3<RECHECK>(na, ca, nb, cb, nc, cc);
   };
 
   auto vget = [&](int t) -> V3<R> {
@@ -650,7 +661,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         redone = true;
       }
     } else {
-      v = solve3<R>(na, ca, nb_, cb, {nx, ny, nz}, c);
+      v = solve3<RECHECK>(na, ca, nb_, cb, {nx, ny, nz}, c);
     }
     return v;
   };
@@ -1635,7 +1646,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       plane64(B, nb_, cb);
       plane64(C, nc, cc);
       v = refined ? solve3_refined(na, ca, pid(A) >= 0, nb_, cb, pid(B) >= 0, nc, cc, pid(C) >= 0)
-                  : solve3<double>(na, ca, nb_, cb, nc, cc);
+                  : solve3<RECHECK>(na, ca, nb_, cb, nc, cc);
     } else {
       V3<R> ra, rb, rc;
       R da, db, dc;
