@@ -24,7 +24,6 @@
 #include "internal.h"
 #include "device_common.h"
 
-#include <cfloat>
 #include <climits>
 
 namespace votess {
@@ -58,7 +57,8 @@ struct KeyOps<double> {
     int i;
   };
   __device__ static Key make(double d2, int j) { return {d2, j}; }
-  __device__ static Key inf() { return {DBL_MAX, INT_MAX}; }
+  // (above every point's key, the infinite d^2 of points too far apart included)
+  __device__ static Key inf() { return {__builtin_inf(), INT_MAX}; }
   __device__ static bool less(Key a, Key b) { return a.d < b.d || (a.d == b.d && a.i < b.i); }
   __device__ static bool finite(Key a) { return a.i != INT_MAX; }
   __device__ static double d2(Key a) { return a.d; }
