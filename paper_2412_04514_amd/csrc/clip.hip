@@ -1977,8 +1977,29 @@ void launch_all(const ClipArgs& ca, bool rest, hipStream_t st) {
 // outgrow the list kernel share the second launch: in one of their own they
 // leave the chip half empty (1.2M filament points: 36.3 ms together, 29.9 and
 // 10.2 ms apart).
+// Without the stream phase the list kernel does alone where it can: with lists
+// of at most kShortList planes, which with the box make no more vertices than it
+// has slots for (2^20 / 2 clustered cells by 16 planes: 1.19 ms with a second
+// launch that finds nothing and the marks' removal, 1.14 without; 2000 cells 57
+// and 54 us), and, with the stream kernel's 64 slots, over few cells, where the
+// second launch would wait for a handful that outgrew the first (64 planes: 2000
+// cells 201 and 113 us, 32,000 uniform ones 316 and 235, 128,000 728 and 739;
+// 32 planes: 8000 cells 252 and 178 us, 32,000 clustered ones 228 and 235).  A
+// cell's sums have the same order either way.
+constexpr int kShortList = (kListVert + 4) / 2 - 6;  // (f faces make 2 f - 4 vertices)
 template <typename P, typename R, bool RECHECK>
 votess_status run_fast(ClipArgs ca, bool split, hipStream_t st) {
+  if (split && !ca.stream) {
+    const bool few = ca.nc < (ca.k > 32 ? 65536 : 32768);
+    if (ca.k <= kShortList || few) {
+      if (ca.k <= kShortList)
+        launch<P, R, kListLanes, kListVert, 32, RECHECK, false>(ca, false, st);
+      else
+        launch<P, R, kListLanes, 64, 32, RECHECK, false>(ca, false, st);
+      VT_HIP(hipGetLastError());
+      return VOTESS_OK;
+    }
+  }
   if (split) {
     ca.save = ca.stream;
     ca.mark = 1 << VOTESS_CELL_CAPACITY | (ca.stream ? 1 << VOTESS_CELL_RADIUS : 0);
