@@ -14,7 +14,7 @@
 // looked up G at a time, one per lane; the candidates of the ranges found are
 // taken G at a time, and each that beats the current K-th is gathered in LDS.
 // G gathered ones are merged into the ascending list, which the group holds as
-// E = K / G consecutive entries per lane, by one bitonic network.
+// E consecutive entries per lane, by one bitonic network.
 // What bounds it: vector instructions (VALU ~90% busy).  With the rows of phase
 // B stepped through one by one by the whole group, in double, and candidates
 // inserted one by one (~40 instructions for each of ~80 per query at k = 64),
@@ -128,8 +128,14 @@ struct GroupList {
     for (int e = 0; e < E; ++e) key[e] = O::inf();
   }
   using LM = LaneMove<G>;
-  __device__ Key worst(int gb, int l) const {
-    return O::each_word(key[E - 1], [&](unsigned w) { return LM::last(w, gb, l); });
+  // the key of rank K0 - 1 (K0 a multiple of E)
+  template <int K0>
+  __device__ Key at(int gb, int l) const {
+    static_assert(K0 % E == 0 && K0 <= G * E, "a lane's last key");
+    return O::each_word(key[E - 1], [&](unsigned w) {
+      if constexpr (K0 == G * E) return LM::last(w, gb, l);
+      else return (unsigned)__shfl((int)w, gb + K0 / E - 1, 64);
+    });
   }
   // Compare-exchange of positions i = l N + e and i ^ js over the G N keys
   // that the group holds N per lane: inside a lane in registers, across lanes
@@ -203,13 +209,15 @@ struct GroupList {
 // block (b mod 8) per + b / 8 (per = blocks / 8, rounded up; the launch is
 // padded to 8 per) and each XCD works on one contiguous stretch of the
 // grid-sorted queries, whose candidates its own L2 then holds.
-template <typename T, typename D, int K, int GS>
+// The list holds LIST entries, of which the first K are asked for and bound the
+// search.
+template <typename T, typename D, int K, int LIST, int GS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(D) == 4 ? 7 : 6))) void k_knn(const typename Rec<T>::type* __restrict__ rec, int n, GridDev G,
                                              const int* __restrict__ cell_start, SubGrid sub,
-                                             const int* __restrict__ queries, int nq, int k, int* __restrict__ knn,
+                                             const int* __restrict__ queries, int nq, int* __restrict__ knn,
                                              unsigned* __restrict__ err, int nblocks) {
-  constexpr int E = K / GS;
-  static_assert(E * GS == K, "K must be a multiple of GS");
+  constexpr int E = LIST / GS;
+  static_assert(E * GS == LIST && K <= LIST, "LIST must be a multiple of GS, and hold K");
   using O = KeyOps<D>;
   using Key = typename O::Key;
   const int per = (nblocks + 7) / 8;
@@ -336,7 +344,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(D) =
       if (l < left) gbuf[l] = rest;
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       nbuf = left;
-      wk = L.worst(gb, l);
+      wk = L.template at<K>(gb, l);
       if (drain) continue;
     }
     drain = false;
@@ -557,11 +565,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(D) =
     rp = 0;
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
-  // the first k entries (the list may be longer than asked for)
-  int* out = knn + (size_t)q * k;
+  int* out = knn + (size_t)q * K;
 #pragma unroll
   for (int e = 0; e < E; ++e)
-    if (l * E + e < k) out[l * E + e] = O::idx(L.key[e]);
+    if (l * E + e < K) out[l * E + e] = O::idx(L.key[e]);
   if (l == 0 && O::finite(L.key[0]) && O::d2(L.key[0]) == 0.0) atomicOr(err, ERR_DUPLICATE);
 }
 
@@ -571,13 +578,15 @@ votess_status dispatch_k(int k, const void* sorted, int n, const GridDev& G, con
   using R4 = typename Rec<T>::type;
   const R4* rec = (const R4*)sorted;
   // A list is a power of two long, at least k; its first k entries are the
-  // k-list.  (Merging needs a power of two, and beats inserting by far: 2^20
-  // uniform points, float, lists of 64 2.0 ms, lists of 48 by insertion 3.2 ms.)
+  // k-list, and the k-th bounds the search (1M clustered points, double, k = 24:
+  // 2.81 ms, bounded by the 32nd 3.37).  (Merging needs a power of two, and beats
+  // inserting by far: 2^20 uniform points, float, lists of 64 2.0 ms, lists of 48
+  // by insertion 3.2 ms.)
 #define VT_KNN_CASE(KK, LIST, GG)                                                                 \
   case KK: {                                                                                      \
     const int blocks = (int)(((long long)nq * GG + 255) / 256);                                   \
     const unsigned launched = (unsigned)(8 * ((blocks + 7) / 8));                                 \
-    k_knn<T, D, LIST, GG><<<launched, 256, 0, st>>>(rec, n, G, cs, sub, qs, nq, k, knn, err, blocks); \
+    k_knn<T, D, KK, LIST, GG><<<launched, 256, 0, st>>>(rec, n, G, cs, sub, qs, nq, knn, err, blocks); \
     break;                                                                                        \
   }
   switch (k) {
