@@ -29,8 +29,12 @@ namespace {
 
 constexpr int kLdsSortMax = 4096; // larger cells sort their keys in global memory
 constexpr int kDenseBlocks = 2048; // blocks of the dense-cell pass (grid-stride over the dense cells)
-constexpr int kWavePoints = 256;   // dense cells of up to this many points are ordered by one wave each
+constexpr int kWavePoints = 256;   // in large sorts, dense cells of up to this many points are ordered by one wave each
 constexpr int kWaveBlocks = 8192;  // waves of that pass
+// Sorts of fewer points leave all dense cells to the blocks: a launch more takes
+// longer than their few cells do (30k clustered points, float: 50 us with the wave
+// pass, 46 without; 100k: 53 and 68).
+constexpr int kWaveSort = 32768;
 constexpr int kSmallCells = 1024;  // cells, one per thread, of a block of k_order_small
 
 template <typename T>
@@ -319,15 +323,15 @@ constexpr int kCntLds = 4096;
 // by the bitonic network instead of the per-sub-cell rank count below.
 constexpr int kCrowd = 256;
 
-// One block per dense cell of more than kWavePoints points (grid-stride over
-// their list): plan the cell's sub-grid (it spans, per axis, the central 90% of
-// the points, from a histogram of kSubBins bins over their bounding box; points
-// beyond fall in the edge sub-cells), then a counting sort by sub-cell -- LDS
-// atomic counts give each point its sub-cell and a provisional slot, a block
-// scan turns counts into the sub-cell starts (written to the record as they
-// are) -- and within a sub-cell each point's final rank is the number of its
-// points with a smaller original index.  Per-point scratch lives in global
-// memory at the cell's own range [b, b + len).
+// One block per dense cell that no wave takes (grid-stride over their list):
+// plan the cell's sub-grid (it spans, per axis, the central 90% of the points,
+// from a histogram of kSubBins bins over their bounding box; points beyond fall
+// in the edge sub-cells), then a counting sort by sub-cell -- LDS atomic counts
+// give each point its sub-cell and a provisional slot, a block scan turns counts
+// into the sub-cell starts (written to the record as they are) -- and within a
+// sub-cell each point's final rank is the number of its points with a smaller
+// original index.  Per-point scratch lives in global memory at the cell's own
+// range [b, b + len).
 template <typename T>
 __global__ __launch_bounds__(256) void k_order_dense(const typename Rec<T>::type* __restrict__ tmp,
                                                      const int* __restrict__ cell_start, const int* __restrict__ big,
@@ -711,7 +715,7 @@ votess_status launch_grid_sort(votess_ctx* ctx, const void* pts, votess_dtype dt
   VT_TRY(scan_i32(count, ncells, cell_start, ws, st));
   if (n > 0) {
     const unsigned cblk = (unsigned)((ncells + kSmallCells - 1) / kSmallCells);
-    const int split = subinfo ? kWavePoints : 0;
+    const int split = subinfo && n >= kWaveSort ? kWavePoints : 0;
     auto order = [&](auto zero, auto* rec, auto* dst) {
       using T = decltype(zero);
       k_scatter<T><<<nblk, TB, 0, st>>>((const T*)pts, n, cr, cell_start, rec);
@@ -719,7 +723,8 @@ votess_status launch_grid_sort(votess_ctx* ctx, const void* pts, votess_dtype dt
                                                      (int2*)subinfo);
       if (subinfo) {
         // as many blocks as there can be such cells, and no launch where there are none
-        const int nmid = std::min(kWaveBlocks, n / (kSubMin + 1)), ndense = std::min(kDenseBlocks, n / (kWavePoints + 1));
+        const int nmid = split ? std::min(kWaveBlocks, n / (kSubMin + 1)) : 0;
+        const int ndense = std::min(kDenseBlocks, n / (std::max(split, kSubMin) + 1));
         if (nmid)
           k_order_mid<T><<<nmid, 64, 0, st>>>(rec, cell_start, big, nbig, (int)ncells, G, dst, perm, (int2*)subinfo,
                                               sub_start);
