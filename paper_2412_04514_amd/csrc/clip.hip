@@ -364,7 +364,6 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   constexpr int G = 64 / L;
   constexpr int S = TMAX / L;
   constexpr int TP = TMAX + 1;
-  constexpr unsigned long long LOWL = (L == 64) ? ~0ull : ((1ull << L) - 1);
   constexpr M PFULL = (PMAX == 8 * (int)sizeof(M)) ? ~M(0) : ((M(1) << PMAX) - 1);
   static_assert(S <= 32, "slot mask is 32 bits");
   static_assert(TMAX % L == 0 && TMAX % 4 == 0, "the slots are taken L at a time, or 4");

@@ -42,7 +42,6 @@ struct KeyOps<float> {
   __device__ static bool finite(Key a) { return a != ~0ull; }
   __device__ static double d2(Key a) { return (double)__uint_as_float((unsigned)(a >> 32)); }
   __device__ static int idx(Key a) { return a == ~0ull ? -1 : (int)(unsigned)(a & 0xffffffffu); }
-  __device__ static Key shfl(Key a, int src) { return __shfl(a, src, 64); }
   __device__ static Key pick(bool c, Key a, Key b) { return c ? a : b; }
   // f applied to each 32-bit word of the key
   template <class F>
@@ -63,7 +62,6 @@ struct KeyOps<double> {
   __device__ static bool finite(Key a) { return a.i != INT_MAX; }
   __device__ static double d2(Key a) { return a.d; }
   __device__ static int idx(Key a) { return a.i == INT_MAX ? -1 : a.i; }
-  __device__ static Key shfl(Key a, int src) { return {__shfl(a.d, src, 64), __shfl(a.i, src, 64)}; }
   // field by field: a choice between two structs as lvalues would select
   // their addresses and keep the list in scratch memory
   __device__ static Key pick(bool c, Key a, Key b) { return {c ? a.d : b.d, c ? a.i : b.i}; }
@@ -76,19 +74,20 @@ struct KeyOps<double> {
 };
 
 // Moves of 32-bit words between the lanes of a group of G consecutive lanes.
-// For G = 4, 8 or 16 they are DPP row operations, which stay in the vector
+// For G = 8 or 16 they are DPP row operations, which stay in the vector
 // ALU (controls: quad_perm [1,0,3,2] = 0xB1 takes lane ^ 1, [2,3,0,1] = 0x4E
 // lane ^ 2, [3,2,1,0] = 0x1B reverses a quad, [3,3,3,3] = 0xFF broadcasts
 // its last lane; row_mirror = 0x140 takes lane 15 - i within the row, row_half_mirror =
-// 0x141 lane 7 - i within each eight); a group of 32 or 64 uses the LDS
-// permute.  Every lane of the group is active.
+// 0x141 lane 7 - i within each eight); a group of 32 uses the LDS permute.
+// Every lane of the group is active.
 template <int CTRL>
 __device__ __forceinline__ unsigned dpp_mov(unsigned v) {
   return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
 template <int G>
 struct LaneMove {
-  static constexpr bool kDpp = G == 4 || G == 8 || G == 16;
+  static_assert(G == 8 || G == 16 || G == 32, "the groups that have kernels");
+  static constexpr bool kDpp = G <= 16;
   // the word of lane l ^ m (m a power of two below G)
   __device__ static unsigned xor_(unsigned v, int m) {
     if constexpr (kDpp) {
@@ -101,9 +100,7 @@ struct LaneMove {
   }
   // the word of the group's last lane
   __device__ static unsigned last(unsigned v, int gb, int l) {
-    if constexpr (G == 4) {
-      return dpp_mov<0xFF>(v);
-    } else if constexpr (G == 8) {
+    if constexpr (G == 8) {
       const unsigned a = dpp_mov<0xFF>(v);  // each quad: its last lane
       const unsigned b = dpp_mov<0x141>(a);  // the other quad's
       return l < 4 ? b : a;
@@ -262,7 +259,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(D) =
   Place& E_ = splace[(threadIdx.x & 255) / GS];
   int nbuf = 0;
   const double p0 = (double)pr.x, p1 = (double)pr.y, p2 = (double)pr.z;
-  const unsigned long long gmask = (GS == 64) ? ~0ull : ((1ull << GS) - 1ull);
+  const unsigned long long gmask = (1ull << GS) - 1ull;
   const unsigned long long below = (1ull << l) - 1ull;
   auto gballot = [&](bool v) -> unsigned long long { return (__ballot(v) >> gb) & gmask; };
 
