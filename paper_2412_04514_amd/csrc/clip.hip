@@ -7,10 +7,13 @@
 // MI355X design
 //  * A group of L lanes owns one cell; a 64-lane wave (= one workgroup) holds
 //    64/L cells.  Lane j of a group handles vertex slots t = j, j+L, ...
-//  * Two launches: the list kernel (8 lanes per cell) clips every cell by its
+//  * Three kernels: the list kernel (8 lanes per cell) clips every cell by its
 //    list; cells that the list does not certify go on, with the polyhedron it
-//    left, in the stream kernel (16 lanes per cell).  Vector instructions bind
-//    the first (VALU busy 75-95%), loads and enumeration the second.
+//    left, in the stream kernel (16 lanes per cell), and cells that outgrow both
+//    go to the large-capacity kernel (32 lanes).  The stream kernel does both
+//    phases where there is no list, or no place for a cell's state.  Vector
+//    instructions bind the first (VALU busy 84%), loads, enumeration and the
+//    unlike lengths of its four cells the second (57%).
 //  * The polyhedron is kept in dual form in LDS: a list of clipping planes
 //    (box walls + bisectors, at most PMAX alive at once, slots recycled) and a
 //    list of triangles, one per vertex, each naming its three planes in
@@ -427,8 +430,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     int fb0, fb1, fb2, fb3, fb4, fb5;
     int rr, pq, np, zlo, ylo, nyr, rln, rlp;
     int rx, rx1, rrow, yy, zz;
-    int dm, dm0, dm1, dm2, dbase, dsx0, dsx1, dsy0, dsy1, dsz0, dsz1;
-    unsigned dsto;
+    int dm, dm0, dm1, dm2, dbase, dsx0, dsx1, dsy0, dsy1, dsz0, dsz1, dsto;
     int dq1, dq2, kyn, kzn, dq, dqn, srn, srp;
   };
   __shared__ Enum senum[STREAM ? G : 1];
@@ -1299,7 +1301,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     // next sub-row ordinal, their count; listed ranges, next one
     int &dq = E_.dq, &dqn = E_.dqn, &srn = E_.srn, &srp = E_.srp;
     dq = 0; dqn = 0; srn = 0; srp = 0;
-    unsigned& dsto = E_.dsto;  // the dense cell's sub-grid record: a.sub.start + dsto
+    int& dsto = E_.dsto;  // the dense cell's sub-grid record: a.sub.start + dsto
     dsto = 0;
     // entries of the reach list whose ball meets the dense cell's sub-block
     // (valid for the vertices they were listed for)
@@ -1462,7 +1464,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
             dm = hit ? 1 : 0;
           }
           if (dm) {
-            dsto = (unsigned)info.x;
+            dsto = info.x;
             dbase = a.cell_start[rrow + rx];
             dm0 = sc.m0;
             dm1 = sc.m1;
@@ -1896,8 +1898,9 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
 // hold: with triangles in 16 bits and planes without their offsets a list
 // wave takes 13.1 KB (double clip of float points 16.2, of double ones 19.3)
 // and a CU holds 12 (10, 8); with 32-bit triangles and offsets 14.9 (22.1) KB
-// and 10 (7).  Clip times with those and now: 3M clustered points in double
-// 58.9 and 51.1 ms, 16M in float 215.9 and 202.6 ms, 1M uniform 6.99 and 6.39.
+// and 10 (7).  Clip times with those and with these, one stretch of blocks per
+// XCD: 3M clustered points in double 58.9 and 51.1 ms, 16M in float 215.9 and
+// 202.6 ms, 1M uniform 6.99 and 6.39.
 template <typename P, typename R, int L, int TMAX, int PMAX, bool RECHECK, bool STREAM>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_clip(ClipArgs a) {
   constexpr int G = 64 / L;
@@ -1978,7 +1981,7 @@ void launch_all(const ClipArgs& ca, bool rest, hipStream_t st) {
 // 10.2 ms apart).
 // Without the stream phase the list kernel does alone where it can: with lists
 // of at most kShortList planes, which with the box make no more vertices than it
-// has slots for (2^20 / 2 clustered cells by 16 planes: 1.19 ms with a second
+// has slots for (500k clustered cells by 16 planes: 1.19 ms with a second
 // launch that finds nothing and the marks' removal, 1.14 without; 2000 cells 57
 // and 54 us), and, with the stream kernel's 64 slots, over few cells, where the
 // second launch would wait for a handful that outgrew the first (64 planes: 2000

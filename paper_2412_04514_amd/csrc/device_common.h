@@ -67,19 +67,19 @@ struct SubCell {
   double lo0, lo1, lo2, ih0, ih1, ih2;
   const int* start;  // m0 m1 m2 + 1 starts
 };
-// Position of a dense cell's record in sub_start: a function of the cell's
-// first point b, so that the cells need not agree on it.  A cell of len > 16
-// points spans 4 floor(7 len / 17) words or more from its position to the next
+// Position of a dense cell's record in sub_start, less `base`: a function of the
+// cell's first point b, so that the cells need not agree on it.  A cell of len >
+// 16 points spans 4 floor(7 len / 17) words or more from its position to the next
 // one's, and its record takes (kSubHead + len / 2 + 1, rounded up to 4) <= that;
-// all of them end before 28 n / 17 < sub_capacity(n).  Beyond 1.3e9 points the
-// position takes all 32 bits (a periodic box can come to that many with its
-// images): so a cell's info is (position as unsigned, sub-cells), and a cell is
-// dense when it has sub-cells.
-__host__ __device__ __forceinline__ unsigned sub_offset(int b) { return 4u * (unsigned)((long long)b * 7 / 17); }
-__host__ __device__ __forceinline__ bool is_dense(int2 info) { return info.y > 0; }
-__host__ __device__ __forceinline__ const int* sub_record(const SubGrid& s, int2 info) {
-  return s.start + (unsigned)info.x;
+// all of them end before 28 n / 17 < sub_capacity(n).  Positions count from
+// sub_base(n), so that they fit an int where the buffer is longer than 2^31 (a
+// periodic box can come to 2^31 points with its images); -1, no multiple of 4,
+// marks a cell without a record.
+__host__ __device__ __forceinline__ int sub_offset(int b, unsigned base) {
+  return (int)(4u * (unsigned)((long long)b * 7 / 17) - base);
 }
+__host__ __device__ __forceinline__ bool is_dense(int2 info) { return info.x != -1; }
+__host__ __device__ __forceinline__ const int* sub_record(const SubGrid& s, int2 info) { return s.start + info.x; }
 __device__ __forceinline__ SubCell sub_cell(const int* rec) {
   SubCell c;
   const int4 m = *(const int4*)rec;

@@ -340,7 +340,8 @@ __global__ __launch_bounds__(256) void k_order_dense(const typename Rec<T>::type
                                                      unsigned* __restrict__ g_sid, unsigned* __restrict__ g_rank,
                                                      unsigned* __restrict__ g_slot, int* __restrict__ g_cnt,
                                                      unsigned long long* __restrict__ gkey, unsigned* __restrict__ gval,
-                                                     int2* __restrict__ subinfo, int* __restrict__ sub_start) {
+                                                     int2* __restrict__ subinfo, int* __restrict__ sub_start,
+                                                     unsigned sub_base) {
   __shared__ int s_cnt[kCntLds];
   __shared__ double sbox[4][6];
   __shared__ int shist[3][kSubBins];
@@ -452,14 +453,14 @@ __global__ __launch_bounds__(256) void k_order_dense(const typename Rec<T>::type
     for (int sc = threadIdx.x; sc < ns; sc += blockDim.x) crowd |= cnt[sc] > kCrowd;
     if (crowd) s_crowd = 1;
     block_scan_inplace(cnt, ns + 1);  // cnt[sc] = first point of sub-cell sc, cnt[ns] = len
-    const unsigned soff = sub_offset(b);
+    const int soff = sub_offset(b, sub_base);
     int* rec = sub_start + soff;
     if (threadIdx.x == 0) {
       *(int4*)rec = make_int4(m0, m1, m2, 0);
       *(double2*)(rec + 4) = make_double2(lo0, lo1);
       *(double2*)(rec + 8) = make_double2(lo2, ih0);
       *(double2*)(rec + 12) = make_double2(ih1, ih2);
-      subinfo[c] = make_int2((int)soff, ns);
+      subinfo[c] = make_int2(soff, ns);
     }
     for (int sc = threadIdx.x; sc <= ns; sc += blockDim.x) rec[kSubHead + sc] = cnt[sc];
     if (!s_crowd) {
@@ -506,7 +507,8 @@ template <typename T, int R>
 __device__ __forceinline__ void order_mid(const typename Rec<T>::type* __restrict__ tmp, int c, int b, int len,
                                           const GridDev& G, typename Rec<T>::type* __restrict__ out,
                                           int* __restrict__ perm, int2* __restrict__ subinfo,
-                                          int* __restrict__ sub_start, int* cnt, unsigned* slot) {
+                                          int* __restrict__ sub_start, unsigned sub_base, int* cnt,
+                                          unsigned* slot) {
   const int lane = threadIdx.x;
   typename Rec<T>::type r[R];
 #pragma unroll
@@ -570,14 +572,14 @@ __device__ __forceinline__ void order_mid(const typename Rec<T>::type* __restric
     at[i] = lane + 64 * i < len ? atomicAdd(&cnt[sid[i]], 1) : 0;
   }
   __syncthreads();
-  const unsigned soff = sub_offset(b);
+  const int soff = sub_offset(b, sub_base);
   int* rec = sub_start + soff;
   if (lane == 0) {
     *(int4*)rec = make_int4(m0, m1, m2, 0);
     *(double2*)(rec + 4) = make_double2(lo_[0], lo_[1]);
     *(double2*)(rec + 8) = make_double2(lo_[2], ih0);
     *(double2*)(rec + 12) = make_double2(ih1, ih2);
-    subinfo[c] = make_int2((int)soff, ns);
+    subinfo[c] = make_int2(soff, ns);
   }
   int carry = 0;  // starts of the sub-cells
   for (int s0 = 0; s0 <= ns; s0 += 64) {
@@ -620,7 +622,8 @@ __global__ __launch_bounds__(64) void k_order_mid(const typename Rec<T>::type* _
                                                   const int* __restrict__ cell_start, const int* __restrict__ list,
                                                   const int* __restrict__ nlist, int ncells, GridDev G,
                                                   typename Rec<T>::type* __restrict__ out, int* __restrict__ perm,
-                                                  int2* __restrict__ subinfo, int* __restrict__ sub_start) {
+                                                  int2* __restrict__ subinfo, int* __restrict__ sub_start,
+                                                     unsigned sub_base) {
   __shared__ int cnt[kWavePoints / 2 + 1];
   __shared__ unsigned slot[kWavePoints];
   const int n = nlist[1];
@@ -628,9 +631,9 @@ __global__ __launch_bounds__(64) void k_order_mid(const typename Rec<T>::type* _
     const int c = list[ncells - 1 - q];
     const int b = cell_start[c], len = cell_start[c + 1] - b;
     if (len <= 64)
-      order_mid<T, 1>(tmp, c, b, len, G, out, perm, subinfo, sub_start, cnt, slot);
+      order_mid<T, 1>(tmp, c, b, len, G, out, perm, subinfo, sub_start, sub_base, cnt, slot);
     else
-      order_mid<T, kWavePoints / 64>(tmp, c, b, len, G, out, perm, subinfo, sub_start, cnt, slot);
+      order_mid<T, kWavePoints / 64>(tmp, c, b, len, G, out, perm, subinfo, sub_start, sub_base, cnt, slot);
   }
 }
 
@@ -715,6 +718,8 @@ votess_status launch_grid_sort(votess_ctx* ctx, const void* pts, votess_dtype dt
   VT_TRY(scan_i32(count, ncells, cell_start, ws, st));
   if (n > 0) {
     const unsigned cblk = (unsigned)((ncells + kSmallCells - 1) / kSmallCells);
+    const unsigned base = sub_base(n);
+    int* sub = sub_start ? sub_start + base : nullptr;
     const int split = subinfo && n >= kWaveSort ? kWavePoints : 0;
     auto order = [&](auto zero, auto* rec, auto* dst) {
       using T = decltype(zero);
@@ -727,10 +732,10 @@ votess_status launch_grid_sort(votess_ctx* ctx, const void* pts, votess_dtype dt
         const int ndense = std::min(kDenseBlocks, n / (std::max(split, kSubMin) + 1));
         if (nmid)
           k_order_mid<T><<<nmid, 64, 0, st>>>(rec, cell_start, big, nbig, (int)ncells, G, dst, perm, (int2*)subinfo,
-                                              sub_start);
+                                              sub, base);
         if (ndense)
           k_order_dense<T><<<ndense, 256, 0, st>>>(rec, cell_start, big, nbig, G, dst, perm, g_sid, g_rank, g_slot, g_cnt,
-                                                   gkey, gval, (int2*)subinfo, sub_start);
+                                                   gkey, gval, (int2*)subinfo, sub, base);
       } else {
         k_order_big<T><<<512, 256, 0, st>>>(rec, cell_start, big, nbig, dst, perm, gkey, gval);
       }

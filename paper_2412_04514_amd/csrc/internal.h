@@ -92,13 +92,14 @@ votess_status launch_grid_sort(votess_ctx* ctx, const void* pts, votess_dtype dt
                                int32_t* sub_start, Workspace& ws, hipStream_t st);
 int64_t sub_capacity(int64_t n);
 
-// Sub-grids of dense cells: subinfo[2 c] = offset into sub_start (or -1),
+// Sub-grids of dense cells: subinfo[2 c] = offset into sub_start (or -1), less sub_base(n),
 // subinfo[2 c + 1] = m; sub_start[offset + s] = first point of sub-cell s
 // relative to cell_start[c], for s = 0..m^3.
 struct SubGrid {
   const int2* info = nullptr;
-  const int* start = nullptr;
+  const int* start = nullptr;  // (past the first sub_base(n) entries)
 };
+inline unsigned sub_base(int64_t n) { return sub_capacity(n) > INT32_MAX ? 1u << 31 : 0u; }
 
 // exclusive scan: out[0..n] with out[n] = total (grid_sort.hip)
 size_t scan_workspace(int64_t n);

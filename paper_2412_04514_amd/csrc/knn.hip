@@ -15,7 +15,7 @@
 // taken G at a time, and each that beats the current K-th is gathered in LDS.
 // G gathered ones are merged into the ascending list, which the group holds as
 // E consecutive entries per lane, by one bitonic network.
-// What bounds it: vector instructions (VALU ~90% busy).  With the rows of phase
+// What bounds it: vector instructions (VALU 100% busy).  With the rows of phase
 // B stepped through one by one by the whole group, in double, and candidates
 // inserted one by one (~40 instructions for each of ~80 per query at k = 64),
 // 64-lists took 4.36 ms for 2^20 uniform points in float, 22.8 ms for 4M
@@ -197,10 +197,10 @@ struct GroupList {
   }
 };
 
-// Held to 7 waves per SIMD with float keys and 6 with double ones: the search
-// waits on loads, and at k = 64 on clustered input these measured faster than
-// one wave more or less (4M points, float: 15.1, 14.7 and 15.5 ms at 6, 7 and
-// 8; 3M points, double: 15.2, 14.8 and 16.1 ms at 5, 6 and 7), spills and all.
+// Held to 7 waves per SIMD with float keys and 6 with double ones, spills and
+// all: at k = 64 on clustered input one wave less leaves latencies open and one
+// more spills more (4M points, float: 15.1, 14.7 and 15.5 ms at 6, 7 and 8; 3M
+// points, double: 15.2, 14.8 and 16.1 ms at 5, 6 and 7).
 // Blocks are taken in an XCD-aware order: the hardware deals launched
 // blocks round-robin over the eight XCDs, so launched block b runs logical
 // block (b mod 8) per + b / 8 (per = blocks / 8, rounded up; the launch is

@@ -263,7 +263,7 @@ votess_status tessellate_periodic(votess_ctx* ctx, const void* pts, votess_dtype
     }
     SubGrid SG;
     SG.info = subinfo.get<int2>();
-    SG.start = sub_start.get<int>();
+    SG.start = sub_start.get<int>() + sub_base(n_ext);
     const GridDev GD = to_dev(grid);
     VT_TRY(launch_knn(ctx, sorted.p, xdt, n_ext, GD, cs.get<int>(), SG, cells.get<int>(), nc, k, dist,
                       knn.get<int>(), st));
