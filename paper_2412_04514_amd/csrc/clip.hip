@@ -406,6 +406,10 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   struct alignas(16) Ball {
     R x, y, z, r;
   };
+  // Tests against them read four at a time, so that their latency is met once: 200k
+  // clustered points, double clip, 7.36 -> 6.95 ms, 300k in float without lists
+  // 8.59 -> 7.95; by two 7.17 and 8.19, by eight spills.
+  constexpr int kAhead = 4;
   constexpr int RVF = STREAM && RECHECK ? G * kReach : 1, RVD = STREAM && !RECHECK ? G * kReach : 1;
   __shared__ Ball reachv[RVF];
   __shared__ R reachr[RVD];
@@ -1284,6 +1288,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       if (in_list_ball(ax - m, bx + m, ay - m, by + m, az - m, bz + m)) return false;
       const Box b = round_out(ax - m, bx + m, ay - m, by + m, az - m, bz + m);
       bool any = reach_all;
+#pragma unroll(kAhead)
       for (int i = 0; i < nrv; ++i) any = any || meets(b, ball(i));
       return any;
     };
@@ -1326,6 +1331,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       if (in_list_ball(ax, bx, ay, by, az, bz)) return false;
       const Box b = round_out(ax, bx, ay, by, az, bz);
       bool any = !okD || reach_all;
+#pragma unroll(kAhead)
       for (int i = 0; i < nD; ++i) any = any || meets(b, ball(rd[i]));
       return any;
     };
@@ -1551,11 +1557,13 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
       const R c = R(0.5) * myd2;
       R far = -c;
       if (rdense && okD) {
+#pragma unroll(kAhead)
         for (int i = 0; i < nD; ++i) {
           const Ball v = ball(rd[i]);
           far = fmax(far, myx * v.x + myy * v.y + myz * v.z);
         }
       } else {
+#pragma unroll(kAhead)
         for (int i = 0; i < nrv; ++i) {
           const Ball v = ball(i);
           far = fmax(far, myx * v.x + myy * v.y + myz * v.z);
