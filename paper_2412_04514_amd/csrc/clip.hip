@@ -402,7 +402,9 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   constexpr int kReach = TMAX <= 64 ? 48 : TMAX;
   constexpr int RVN = STREAM ? G * kReach : 1;
   // (float: centre and radius, one 16-byte read; double: the vertex slot and the
-  // radius, half the LDS of a copy: 3M clustered points 64.2 and 70.4 ms)
+  // radius, half the LDS of a copy: 3M clustered points 64.2 and 70.4 ms.  The few
+  // waves of the large kernel wait for each read and have LDS to spare: copies, 10k
+  // clustered points in double 2.80 and 2.59 ms.)
   struct alignas(16) Ball {
     R x, y, z, r;
   };
@@ -410,7 +412,8 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
   // clustered points, double clip, 7.36 -> 6.95 ms, 300k in float without lists
   // 8.59 -> 7.95; by two 7.17 and 8.19, by eight spills.
   constexpr int kAhead = 4;
-  constexpr int RVF = STREAM && RECHECK ? G * kReach : 1, RVD = STREAM && !RECHECK ? G * kReach : 1;
+  constexpr bool kCopies = RECHECK || TMAX > 64;
+  constexpr int RVF = STREAM && kCopies ? G * kReach : 1, RVD = STREAM && !kCopies ? G * kReach : 1;
   __shared__ Ball reachv[RVF];
   __shared__ R reachr[RVD];
   __shared__ unsigned char reachs[RVD];
@@ -1164,7 +1167,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
     // fit, every test passes (reach_all), which costs time only.
     const int rvb = STREAM ? g * kReach : 0;
     auto ball = [&](int i) -> Ball {
-      if constexpr (RECHECK) {
+      if constexpr (kCopies) {
         return reachv[rvb + i];
       } else {
         const int t = vb + reachs[rvb + i];
@@ -1188,7 +1191,7 @@ __device__ __forceinline__ void clip_group(const ClipArgs& a, long long t_idx, b
         const unsigned gbits = gballot(on);
         const int w = n + __popc(gbits & below);
         if (on && w < kReach) {
-          if constexpr (RECHECK) {
+          if constexpr (kCopies) {
             reachv[rvb + w] = {v.x, v.y, v.z, r};
           } else {
             reachr[rvb + w] = r;
